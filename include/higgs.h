@@ -407,8 +407,10 @@ higgs_status higgs_qmatmul_fused_noalloc(const void *x, higgs_dtype x_dtype, int
  * layers are computed by ONE launch: each block of the launch takes rows of
  * one layer, so the launch and prologue cost is paid once. On the
  * matrix-core path the layers share one activation conversion
- * launch (one rotated copy per distinct seed), one product launch and at most
- * one reduction launch per 64 batch rows. Otherwise the layers are computed
+ * launch (one rotated copy per distinct seed) and, up to 64 batch rows, one
+ * product launch and at most one reduction launch; above, a product launch
+ * per block shape that the layers use (at most three) and a reduction launch
+ * per layer whose rows are split. Otherwise the layers are computed
  * one after another on the stream, sharing the workspace.
  *
  *   layers     1..4.

@@ -30,6 +30,7 @@ SOURCES = {
     "encode.hip": [],
     "qgemv.hip": [],
     "qgemm.hip": [],
+    "qgemm_wide.hip": [],
     "scratch.hip": [],
 }
 

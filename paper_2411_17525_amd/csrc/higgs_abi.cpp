@@ -483,7 +483,7 @@ higgs_status higgs_qmatmul_fused_multi(int layers, const void* x, higgs_dtype x_
                 (long long)need_all);
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const int x_bf16 = x_dtype == HIGGS_BF16 ? 1 : 0;
-  if (higgs::use_qgemm(batch, p, n, in, g)) {  // one conversion, one product launch per 64 rows
+  if (higgs::use_qgemm(batch, p, n, in, g)) {  // shared activation conversion
     const hipError_t err = higgs::launch_qgemm_group(
         x, x_bf16 ? higgs::kQgemmRawBF16 : higgs::kQgemmRawF32, layers, rht_seeds, batch, codes,
         scales, grid, p, n, g, out, in, y, workspace, s);

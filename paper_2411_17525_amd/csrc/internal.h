@@ -150,8 +150,8 @@ hipError_t launch_qgemm(const void* x, int x_kind, uint64_t seed, int64_t batch,
                         hipStream_t stream);
 
 // Up to 4 layers that read the same activations (own codes, scales, rows,
-// seed and output) in one activation conversion, one product launch and at
-// most one reduction launch per 64 batch rows.
+// seed and output) in one activation conversion and, up to 64 batch rows, one
+// product launch and at most one reduction launch.
 int64_t qgemm_group_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
                                     int p, int n, int g);
 hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint64_t* seeds,
@@ -159,6 +159,18 @@ hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint6
                               const uint16_t* const* scales, const float* grid, int p, int n,
                               int g, const int64_t* outs, int64_t in, float* const* y,
                               void* workspace, hipStream_t stream);
+
+// The matrix-core product for prompt-sized batches (qgemm_wide.hip), same
+// arguments; launch_qgemm[_group] and the workspace sizes above go to it when
+// use_qgemm_wide says so.
+bool use_qgemm_wide(int64_t batch, int64_t in);
+int64_t qgemm_wide_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
+                                   int p, int n, int g);
+hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64_t* seeds,
+                             int64_t batch, const uint8_t* const* codes,
+                             const uint16_t* const* scales, const float* grid, int p, int n, int g,
+                             const int64_t* outs, int64_t in, float* const* y, void* workspace,
+                             hipStream_t stream);
 
 // The library's fixed device scratch (scratch.hip): its device address on
 // the current device, resolved once per device (hipGetSymbolAddress).

@@ -1,0 +1,1040 @@
+// Lookup-table GEMM for HIGGS layers at prompt-sized batches (more than 64
+// rows) on the matrix cores: the product of qgemm.hip,
+//   y[b][o] = sum_i scale[o][i] * sum_j < G[code(o,i,j)], x_rot[b, ig+jp : ig+(j+1)p] >,
+// in blocks of 128 or 256 rows x 128 or 256 batch columns instead of one
+// launch per 64 columns, so that a code is decoded once per 256 columns and the
+// products of a block outweigh what it reads. Measured on MI355X against the
+// 64-column launches: two 14336 x 4096 layers at 2048 rows 987 -> 472 us
+// (1.02 PFLOP/s; a plain fp16 product of that size in torch: 427 us), 4096 x
+// 14336 with 10-bit codes at 512 rows 217 -> 110 us, 11003 x 5120 at 300 rows
+// 153 -> 95 us. With nothing but the matrix instructions and barriers left in
+// the loop the first takes about 400 us: at full load the matrix cores run at
+// reduced clocks, and 896 blocks on 256 compute units leave half a round idle.
+//   * xprep_wide_kernel converts (and rotates) the activations once, to fp16
+//     with one power of two per (batch row, scale group), in the layout the
+//     product stages: per 256-row chunk, per 64 weights of K, one 128-byte
+//     row per batch row whose 16-byte pieces are permuted by the row's low
+//     bits, so that a stage goes to LDS as it lies in memory and is read back
+//     as matrix operands without bank conflicts.
+//   * qgemm_wide_kernel: 8 waves (two per SIMD), each owning 64 rows x 32 NB
+//     columns of the block in matrix registers. Activation stages of 64
+//     weights go straight from memory to LDS (no registers), three buffers
+//     deep; codes are read in the operand layout two stages at a time and
+//     turned into fp16 operands through the replicated LDS table as in
+//     qgemm.hip.
+// Scale groups: the sums are kept in units of the current group's scale times
+// activation exponent, u(o, b); at a group's end they are multiplied by
+// u(this group) / u(next group) (one rounding in fp32), so a wave needs one
+// set of accumulators, not a second one for the scaled totals. Where that
+// ratio cannot be formed (a zero, infinite or NaN scale) or the exponents
+// move by more than 2^20 from where the sums began, the wave adds its sums,
+// scaled, to y (or to the split's partial sums), which it alone owns, and
+// starts again from zero. Between such points |sum / u| stays below 2^120.
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "internal.h"
+#include "qgemm_common.h"
+#include "wave_fwht.h"
+
+namespace higgs {
+namespace {
+
+constexpr int kWaves = 8;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kChunk = 256;  // batch rows per chunk of the fp16 activations
+constexpr int kBufs = 3;     // activation stages in LDS
+
+typedef __attribute__((address_space(3))) void lds_void;
+// (left to itself the compiler calls the product's larger pieces as functions
+// and keeps the sums in memory)
+#define HIGGS_INLINE __attribute__((always_inline))
+
+// ---------------------------------------------------------------------------
+// Activations -> fp16 and one power of two per (batch row, group).
+// ---------------------------------------------------------------------------
+// 16-byte piece c (8 weights) of batch row r, stage s of a chunk of R rows:
+// byte ((s R + r) 8 + (c ^ (r & 7))) 16 of the chunk.
+__device__ inline int64_t xw_index(int64_t batch, int64_t in, int64_t row, int64_t k) {
+  const int64_t chunk = row / kChunk, r = row - chunk * kChunk;
+  const int64_t rows = batch - chunk * kChunk < kChunk ? batch - chunk * kChunk : kChunk;
+  return chunk * kChunk * in + (((k >> 6) * rows + r) * 8 + (((k >> 3) & 7) ^ (r & 7))) * 8 +
+         (k & 7);
+}
+
+// The power of two that a group's fp16 values are in units of: the group's
+// largest magnitude m scaled into [2^7, 2^15). The exponent is a multiple of
+// 8, so that neighbouring groups and rows mostly share it (the product's unit
+// changes are then cheap); fp16 keeps full precision down to 2^-21 of the
+// group's largest value. Near the ends of the fp32 range it is exact instead.
+__device__ inline int group_exponent(float m) {
+  if (!(m > 0.f)) return -8;
+  int e = ilogbf(m) - 14;
+  e = e < -126 ? -126 : (e > 127 ? 127 : e);
+  return (e < -112 || e > 112) ? e : (e + 7) & ~7;
+}
+
+// One wave per group of g = 64 E elements. 2048 x 4096 bf16
+// into two layers' copies: 25 us (38 us with four waves per group, a sign
+// generator per element and 2-byte stores).
+template <int E, typename InT, bool ROT>
+__global__ __launch_bounds__(256) void xprep_wide_kernel(const InT* __restrict__ x, int64_t batch,
+                                                         int64_t in, XSeeds seeds, float rscale,
+                                                         _Float16* __restrict__ x16,
+                                                         float* __restrict__ xe) {
+  constexpr int g = 64 * E;
+  // g = 1024 rotates through LDS (half the instructions of the cross-lane form)
+  constexpr bool kLds = ROT && E == 16;
+  __shared__ __align__(16) float s_rot[kLds ? 4 : 1][kLds ? kFwht1024Scratch : 4];
+  __shared__ uint64_t s_neg[kMaxGroup][E];  // sign bits of 64 elements each
+  const int lane = int(threadIdx.x) & 63;
+  const int wave = int(threadIdx.x) >> 6;
+  const int64_t gpr = in / g, ngroups = batch * gpr;
+  const int64_t nwaves = int64_t(gridDim.x) * 4;
+  const int nl = seeds.nl;
+  uint64_t neg[kMaxGroup] = {0, 0, 0, 0};  // of the lane's E elements
+  if constexpr (ROT) {
+    for (int w = wave; w < nl * E; w += 4) {
+      const int l = w / E, q = w % E;
+      uint64_t seed = seeds.s[0];
+#pragma unroll
+      for (int k = 1; k < kMaxGroup; ++k)
+        if (l == k) seed = seeds.s[k];
+      const uint64_t bits = __ballot(rht_sign_negative(seed, uint32_t(64 * q + lane)));
+      if (lane == 0) s_neg[l][q] = bits;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < kMaxGroup; ++l)
+      if (l < nl) neg[l] = s_neg[l][lane * E / 64] >> (lane * E % 64);
+  }
+  for (int64_t grp = int64_t(blockIdx.x) * 4 + wave; grp < ngroups; grp += nwaves) {
+    const int64_t row = grp / gpr;
+    const int64_t kg = (grp - row * gpr) * g;
+    const int64_t k0 = kg + lane * E;
+    const InT* src = x + row * in + k0;
+    float u[E];
+    if constexpr (E * sizeof(InT) % 16 == 0) {
+#pragma unroll
+      for (int q = 0; q < E * int(sizeof(InT)) / 16; ++q) {
+        const u32x4 d = reinterpret_cast<const u32x4*>(src)[q];
+        const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if constexpr (sizeof(InT) == 4) {
+            u[4 * q + k] = __uint_as_float(w[k]);
+          } else {
+            u[8 * q + 2 * k] = __uint_as_float(w[k] << 16);
+            u[8 * q + 2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        if constexpr (sizeof(InT) == 4)
+          u[i] = float(src[i]);
+        else
+          u[i] = __uint_as_float(uint32_t(reinterpret_cast<const uint16_t*>(src)[i]) << 16);
+      }
+    }
+#pragma unroll
+    for (int l = 0; l < kMaxGroup; ++l) {
+      if (l >= nl) break;  // uniform
+      float v[E];
+#pragma unroll
+      for (int i = 0; i < E; ++i) v[i] = ROT && ((neg[l] >> i) & 1) ? -u[i] : u[i];
+      if constexpr (ROT) {
+        if constexpr (kLds)
+          fwht1024_lds(v, s_rot[wave], lane);
+        else
+          fwht_wave<E>(v, lane, g);
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[i] *= rscale;
+      }
+      float m = 0.f;
+#pragma unroll
+      for (int i = 0; i < E; ++i) m = fmaxf(m, fabsf(v[i]));
+      m = wave_max(m, lane);
+      const int e = group_exponent(m);
+      _Float16* dst = x16 + int64_t(l) * batch * in;
+      if constexpr (kLds) {  // lane l holds elements 256 h + 4 l + j in v[4 h + j]
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          uint2 w;
+          w.x = pack_h2(ldexpf(v[4 * h], -e), ldexpf(v[4 * h + 1], -e));
+          w.y = pack_h2(ldexpf(v[4 * h + 2], -e), ldexpf(v[4 * h + 3], -e));
+          *reinterpret_cast<uint2*>(dst + xw_index(batch, in, row, kg + 256 * h + 4 * lane)) = w;
+        }
+      } else if constexpr (E % 8 == 0) {
+#pragma unroll
+        for (int q = 0; q < E / 8; ++q) {
+          u32x4 w;
+          w.x = pack_h2(ldexpf(v[8 * q], -e), ldexpf(v[8 * q + 1], -e));
+          w.y = pack_h2(ldexpf(v[8 * q + 2], -e), ldexpf(v[8 * q + 3], -e));
+          w.z = pack_h2(ldexpf(v[8 * q + 4], -e), ldexpf(v[8 * q + 5], -e));
+          w.w = pack_h2(ldexpf(v[8 * q + 6], -e), ldexpf(v[8 * q + 7], -e));
+          *reinterpret_cast<u32x4*>(dst + xw_index(batch, in, row, k0 + 8 * q)) = w;
+        }
+      } else if constexpr (E > 1) {  // 2 or 4 halves, inside one piece
+        uint32_t* p = reinterpret_cast<uint32_t*>(dst + xw_index(batch, in, row, k0));
+#pragma unroll
+        for (int q = 0; q < E / 2; ++q)
+          p[q] = pack_h2(ldexpf(v[2 * q], -e), ldexpf(v[2 * q + 1], -e));
+      } else {
+        dst[xw_index(batch, in, row, k0)] = static_cast<_Float16>(ldexpf(v[0], -e));
+      }
+      if (lane == 0) xe[int64_t(l) * ngroups + grp] = ldexpf(1.0f, e);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The product.
+// ---------------------------------------------------------------------------
+// One launch covers nl layers (1..kMaxGroup) that read the same activations.
+// Work items are numbered layer by layer, row tile by row tile, then by
+// K-split, then by column tile; XCD x (blocks are dealt to the XCDs round
+// robin) takes the x-th eighth of them, so that the column tiles that decode
+// the same codes, and neighbouring row tiles, which read the same
+// activations, run on one XCD and meet in its L2.
+struct QW {
+  const _Float16* x16;  // copy c: + c * x16_stride
+  const float* xe;      // [batch][gpr] powers of two (copy c: + c * xe_stride)
+  int64_t x16_stride, xe_stride;
+  const float* grid;
+  int batch, pair_table, log2g, in, gpr, nl, ctiles, items;
+  int item0[kMaxGroup];   // layer l's first work item
+  int xcopy[kMaxGroup];   // the layer's copy of the activations
+  int kps[kMaxGroup];     // weights of K per split (a multiple of 256)
+  int splits[kMaxGroup];
+  int out[kMaxGroup];
+  const uint8_t* codes[kMaxGroup];
+  const uint16_t* scales[kMaxGroup];
+  float* dst[kMaxGroup];  // [splits][batch][out]
+};
+
+// Waits until at most N of this wave's vector memory operations and none of
+// its LDS operations are outstanding.
+template <int N>
+__device__ inline void wait_loads() {
+  static_assert(N >= 0 && N < 64, "the counter has six bits");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+// G64: groups of 64 weights, which end at every stage; larger groups end at
+// even stages only (K-ranges start at multiples of 128, and such rows have an
+// even number of stages).
+template <int BITS, int NB, int KG, bool G64>
+__global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
+  using F = GFmt<BITS>;
+  constexpr int kW = F::kWords;
+  // 256-byte entry slots hold 32 copies in their low halves; the high halves
+  // of 16 slots hold the waves' row factors (rows_of below). 10-bit codes: 16
+  // copies, no such space.
+  constexpr int kCopies = F::kRL < 5 ? 1 << F::kRL : 32;
+  constexpr bool kRowLds = F::kStride == 8;
+  constexpr int kEntries = BITS == 16 ? 256 : 1 << BITS;
+  constexpr int kEntryU4 = (1 << F::kStride) / 16;
+  constexpr int kLutU4 = kEntries * kEntryU4;
+  constexpr int kCols = 64 * NB;
+  constexpr int kRows = 256 / KG;
+  constexpr int kGWaves = kWaves / KG;  // waves of a K-group
+  constexpr int kDma = NB * KG;         // activation loads per wave and stage
+  constexpr bool kTotals = NB == 2;
+  constexpr int kStageBytes = kCols * 128;  // 64 weights of kCols batch rows
+  constexpr bool kPair = BITS != 16;        // codes requested for two stages at a time
+  // code loads per stage: one per row set, two for 10- and 16-bit pairs
+  constexpr int kLoads = BITS >= 10 ? 4 : 2;
+  // LDS reads and address instructions per product that feed the next step
+  constexpr int kStepReads = NB + (BITS == 16 ? 16 : 8);
+  constexpr int kReads = (kStepReads + 2 * NB - 1) / (2 * NB);
+  constexpr int kValu = BITS == 8 ? kReads : 2 * kReads;
+  __shared__ u32x4 s_mem[kLutU4 + KG * kBufs * kStageBytes / 16];
+  const char* const s_lut = reinterpret_cast<const char*>(s_mem);
+
+  const int tid = int(threadIdx.x);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kgrp = wave / kGWaves, gwave = wave % kGWaves;
+  const int rw = gwave % (kRows / 64), cw = gwave / (kRows / 64);
+  char* const s_x0 = reinterpret_cast<char*>(s_mem + kLutU4);
+  char* const s_x = s_x0 + kgrp * kBufs * kStageBytes;  // the K-group's stages
+  const int ahalf = lane >> 5;
+
+  // ---- work item ----
+  const int per = a.items / 8, rem = a.items % 8;
+  const int xcd = int(blockIdx.x) % 8;
+  const int item = xcd * per + min(xcd, rem) + int(blockIdx.x) / 8;
+  int L = 0;
+#pragma unroll
+  for (int l = 1; l < kMaxGroup; ++l)
+    if (l < a.nl && item >= a.item0[l]) L = l;
+  const uint8_t* codes = a.codes[0];
+  const uint16_t* scales = a.scales[0];
+  float* dst = a.dst[0];
+  int out = a.out[0], item0 = 0, kps = a.kps[0], splits = a.splits[0], xcopy = a.xcopy[0];
+#pragma unroll
+  for (int l = 1; l < kMaxGroup; ++l)
+    if (L == l) {
+      codes = a.codes[l];
+      scales = a.scales[l];
+      dst = a.dst[l];
+      out = a.out[l];
+      item0 = a.item0[l];
+      kps = a.kps[l];
+      splits = a.splits[l];
+      xcopy = a.xcopy[l];
+    }
+  const int in = a.in, gpr = a.gpr, log2g = a.log2g, batch = a.batch;
+  // (uniform, but divided in vector registers: read back to scalar ones)
+  const int wl = item - item0;
+  const int wt = __builtin_amdgcn_readfirstlane(wl / a.ctiles);
+  const int ctile = wl - wt * a.ctiles;
+  const int rtile = __builtin_amdgcn_readfirstlane(wt / splits);
+  const int split = wt - rtile * splits;
+  const int row0 = rtile * kRows + rw * 64;  // the wave's first row
+  const int col0 = ctile * kCols;                             // the block's first batch row
+  // the K-group's part of the block's K-range: with two, group 0 takes the
+  // first half (rounded up to 128 weights), so it has at least as many stages
+  int kbeg = split * kps;
+  int kend = min(in, kbeg + kps);
+  const int khalf = KG == 1 ? kend - kbeg : ((kend - kbeg + 255) / 256) * 128;
+  const int nmax = khalf >> 6;
+  if (kgrp == 0)
+    kend = kbeg + khalf;
+  else
+    kbeg += khalf;
+  const int nst = (kend - kbeg) >> 6;  // stages (K-blocks of 64 weights)
+  const int last = max(nst - 1, 0);    // stage that requests past the end repeat
+  dst += int64_t(split) * batch * out;
+
+  // ---- activations of a stage: memory to LDS, 1 KiB (8 batch rows) per wave
+  //      instruction; rows past the batch repeat the chunk's last row (their
+  //      columns are never stored) ----
+  const int chunk = col0 / kChunk;
+  const int crows = min(kChunk, batch - chunk * kChunk);
+  const __amdgpu_buffer_rsrc_t xrs =
+      rsrc(a.x16 + int64_t(xcopy) * a.x16_stride + int64_t(chunk) * kChunk * in,
+           uint32_t(crows) * uint32_t(in) * 2u);
+  uint32_t xoff[kDma];
+#pragma unroll
+  for (int i = 0; i < kDma; ++i) {
+    const int r = col0 - chunk * kChunk + (i * kGWaves + gwave) * 8 + (lane >> 3);
+    xoff[i] = uint32_t(min(r, crows - 1)) * 128u + uint32_t(lane & 7) * 16u;
+  }
+  const uint32_t stage_stride = uint32_t(crows) * 128u;
+  auto issue_x = [&](int st, int buf) HIGGS_INLINE {
+    const uint32_t soff = uint32_t((kbeg >> 6) + min(st, last)) * stage_stride;
+#pragma unroll
+    for (int i = 0; i < kDma; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          xrs, (lds_void*)(s_x + buf * kStageBytes + (i * kGWaves + gwave) * 1024), 16,
+          int(xoff[i]), int(soff), 0, 0);
+  };
+
+  // ---- codes: lane l of row set m holds half l / 32 (32 weights) of each
+  //      K-block of row 32 m + l % 32 ----
+  constexpr uint32_t kKBBytes = 8 * kW;
+  const uint32_t row_bytes = uint32_t(in >> 6) * kKBBytes;
+  const __amdgpu_buffer_rsrc_t crs = rsrc(codes, uint32_t(out) * row_bytes);
+  uint32_t cbase[2];
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+    cbase[m] = uint32_t(min(row0 + 32 * m + (lane & 31), out - 1)) * row_bytes +
+               uint32_t(kbeg >> 6) * kKBBytes + 4u * kW * uint32_t(ahalf);
+  auto fetch = [&](int st, uint32_t (&d)[2][kW]) HIGGS_INLINE {
+    const uint32_t off = kKBBytes * uint32_t(min(st, last));
+#pragma unroll
+    for (int m = 0; m < 2; ++m) load_codes<BITS>(crs, cbase[m] + off, d[m]);
+  };
+
+  // ---- scales of a group: lane l -> row row0 + l; its columns' exponents ----
+  const __amdgpu_buffer_rsrc_t srs = rsrc(scales, uint32_t(out) * uint32_t(gpr) * 2u);
+  const uint32_t srow = uint32_t(min(row0 + lane, out - 1)) * uint32_t(gpr);
+  const float* xe = a.xe + int64_t(xcopy) * a.xe_stride;
+  const float* xep[NB];
+#pragma unroll
+  for (int t = 0; t < NB; ++t)
+    xep[t] = xe + int64_t(min(col0 + cw * 32 * NB + 32 * t + (lane & 31), batch - 1)) * gpr;
+  auto load_units = [&](int grp, float& s, float (&xs)[NB]) HIGGS_INLINE {
+    grp = min(grp, gpr - 1);
+    const uint16_t h = uint16_t(
+        __builtin_amdgcn_raw_buffer_load_b16(srs, int((srow + uint32_t(grp)) * 2u), 0, 0));
+    s = float(__builtin_bit_cast(_Float16, h));
+#pragma unroll
+    for (int t = 0; t < NB; ++t) xs[t] = xep[t][grp];
+  };
+
+  // the stages' loads are issued one stage after the other: the waits below
+  // count on that order
+  uint32_t cod0[2][kW], cod1[2][kW];
+  fetch(0, cod0);
+  if constexpr (kPair) fetch(1, cod1);
+  __builtin_amdgcn_sched_barrier(0);
+  issue_x(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  issue_x(1, 1);
+  __builtin_amdgcn_sched_barrier(0);
+  issue_x(2, 2);
+  __builtin_amdgcn_sched_barrier(0);
+  int grp = kbeg >> log2g;
+  float s_cur, s_nxt, x_cur[NB], x_nxt[NB], x_ref[NB];
+  load_units(grp, s_cur, x_cur);
+  load_units(grp + 1, s_nxt, x_nxt);
+#pragma unroll
+  for (int t = 0; t < NB; ++t) x_ref[t] = x_cur[t];
+
+  // ---- the table: kCopies copies of each entry, whole 16-byte words ----
+  {
+    constexpr int kPer = kCopies / 4;  // words per entry
+    for (int n = tid; n < kEntries * kPer; n += kThreads) {
+      const int e = n / kPer;
+      float gx, gy = 0.f;
+      if constexpr (BITS == 16) {
+        gx = a.grid[e];
+      } else {
+        gx = a.pair_table ? a.grid[e & 15] : a.grid[2 * e];
+        gy = a.pair_table ? a.grid[e >> 4] : a.grid[2 * e + 1];
+      }
+      const uint32_t v = pack_h2(gx, gy);
+      s_mem[e * kEntryU4 + n % kPer] = u32x4{v, v, v, v};
+    }
+  }
+  const uint32_t copy_off = uint32_t(lane & (kCopies - 1)) << 2;
+
+  f16x_acc acc[2][NB];
+  f16x_acc total[kTotals ? 2 : 1][kTotals ? NB : 1];  // scaled sums of whole groups
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[m][t][r] = 0.f;
+        if constexpr (kTotals) total[m][t][r] = 0.f;
+      }
+
+  // B operand of step s, tile t: piece 4 ahalf + s of column 32 t + l % 32
+  const int bcol = (cw * 32 * NB + (lane & 31)) * 128;
+  uint32_t bpos[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) bpos[s] = uint32_t(bcol + (((4 * ahalf + s) ^ (lane & 7)) << 4));
+
+  int buf = 0;  // the current stage's buffer
+
+  // Adds the wave's sums, scaled, to its part of dst (first time: stores
+  // them). Loads and stores are unconditional (out-of-range offsets
+  // read zero and store nothing), so the path is short; it is rarely taken.
+  bool flushed = false;
+  auto flush = [&]() HIGGS_INLINE {
+    // opaque, so that the 128 offsets below are formed here and not kept in
+    // registers through the main loop
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    __amdgpu_buffer_rsrc_t drs[NB];
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+      drs[t] = rsrc(dst + int64_t(col0 + cw * 32 * NB + 32 * t) * out, 0x7fffffffu);
+    const uint32_t coff = (uint32_t(ln & 31) * uint32_t(out) + uint32_t(row0)) * 4u;
+    const int cleft = batch - (col0 + cw * 32 * NB) - (ln & 31);  // t < cleft / 32: stored
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int rl = 32 * m + 8 * (r / 4) + 4 * (ln >> 5) + (r % 4);
+        const float sr = __shfl(s_cur, rl, 64);
+        const uint32_t roff = row0 + rl < out ? coff + 4u * uint32_t(rl) : kOffNone;
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+          const uint32_t off = 32 * t < cleft ? roff : kOffNone;
+          const float old = __builtin_bit_cast(
+              float, __builtin_amdgcn_raw_buffer_load_b32(drs[t], int(flushed ? off : kOffNone),
+                                                          0, 0));
+          const float v = acc[m][t][r] * (sr * x_cur[t]);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, flushed ? old + v : v),
+                                                drs[t], int(off), 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    flushed = true;
+  };
+
+  // ---- a stage: 4 steps of 16 weights per K-half, each 2 NB products. The
+  //      operands of a step are read from LDS while the step before it
+  //      multiplies; step 3 reads the next stage's first operands. ----
+  struct Step {
+    half8 a[2];
+    half8 b[NB];
+  };
+  Step ops[2];
+  auto load_step = [&](int buf, const uint32_t (&cod)[2][kW], int s, Step& o) HIGGS_INLINE {
+    const char* xb = s_x + buf * kStageBytes;
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+      o.b[t] = *reinterpret_cast<const half8*>(xb + bpos[s] + t * 4096);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      uint32_t a32[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (BITS == 16) {
+          const int cc = 4 * s + q;
+          const uint32_t o0 = lut_off_byte<kW>(cod[m], 2 * cc, copy_off);
+          const uint32_t o1 = lut_off_byte<kW>(cod[m], 2 * cc + 1, copy_off);
+          a32[q] = uint32_t(*reinterpret_cast<const uint16_t*>(s_lut + o0)) |
+                   (uint32_t(*reinterpret_cast<const uint16_t*>(s_lut + o1)) << 16);
+        } else {
+          a32[q] = *reinterpret_cast<const uint32_t*>(s_lut +
+                                                      lut_off<BITS>(cod[m], 4 * s + q, copy_off));
+        }
+      }
+      o.a[m] = __builtin_bit_cast(half8, u32x4{a32[0], a32[1], a32[2], a32[3]});
+    }
+  };
+  auto mul_step = [&](const Step& o) HIGGS_INLINE {
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+        acc[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(o.a[m], o.b[t], acc[m][t], 0, 0, 0);
+    // the next step's LDS reads between the products
+#pragma unroll
+    for (int i = 0; i < 2 * NB; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one product
+      __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // One stage (codes `cod`, buffer `buf`), then the first operands of the next
+  // one (codes `cnext`, buffer `bnext`). kLate: loads issued after those of
+  // stage st + 2 by the time of its wait (see below).
+  auto stage = [&](int st, const uint32_t (&cod)[2][kW], const uint32_t (&cnext)[2][kW],
+                   auto LATE) HIGGS_INLINE {
+    const int bnext = buf + 1 == kBufs ? 0 : buf + 1;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      load_step(buf, cod, s + 1, ops[(s + 1) & 1]);
+      mul_step(ops[s & 1]);
+    }
+    // Step 3's operands are in registers: this stage's buffer is free once
+    // every wave is here. Loads are counted in order: after stage st + 1's
+    // (issued two stages ago) came at least the kDma loads of stage st + 2 and
+    // kLate code loads, so waiting for all but those waits for stage st + 1.
+    constexpr int kWait = kDma + decltype(LATE)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    wait_loads<kWait>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    issue_x(st + 3, buf);
+    load_step(bnext, cnext, 0, ops[0]);
+    mul_step(ops[1]);
+    buf = bnext;
+  };
+  // Factor f of the lane's row (lane l: row l of the wave's 64) for the rows
+  // that the lane's accumulators hold: put_rows, then row_quad(m, q) gives
+  // those of rows 32 m + 8 q + 4 ahalf + 0..3.
+  char* const s_rows = reinterpret_cast<char*>(s_mem) + wave * 512 + 128;
+  float row_f = 0.f;
+  int half4 = 0;
+  auto put_rows = [&](float f) HIGGS_INLINE {
+    half4 = 4 * ahalf;  // opaque: addresses are formed here, not kept in registers
+    asm volatile("" : "+v"(half4));
+    row_f = f;
+    if constexpr (kRowLds) {
+      wave_lds_sync();
+      *reinterpret_cast<float*>(s_rows + ahalf * 256 + (lane & 31) * 4) = f;
+      wave_lds_sync();
+    }
+  };
+  auto row_quad = [&](int m, int q, float (&f)[4]) HIGGS_INLINE {
+    if constexpr (kRowLds) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(s_rows + m * 256 + 32 * q + 4 * half4);
+      f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) f[k] = __shfl(row_f, 32 * m + 8 * q + half4 + k, 64);
+    }
+  };
+  // Totals (NB = 2): in units of x_ref per column while every column's
+  // exponent stays what it was at the first group, else absolute (x_ref = 1).
+  auto add_totals = [&]() HIGGS_INLINE {
+    if constexpr (kTotals) {
+      bool same = true;
+#pragma unroll
+      for (int t = 0; t < NB; ++t) same = same && x_cur[t] == x_ref[t];
+      const bool fast = __all(same);  // uniform
+      if (!fast) {
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) total[m][t][r] *= x_ref[t];
+          x_ref[t] = 1.f;
+        }
+      }
+      put_rows(s_cur);
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float f[4];
+          row_quad(m, q, f);
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int t = 0; t < NB; ++t) {
+              const int r = 4 * q + k;
+              if (!fast) acc[m][t][r] *= x_cur[t];
+              total[m][t][r] = fmaf(acc[m][t][r], f[k], total[m][t][r]);
+              acc[m][t][r] = 0.f;
+            }
+        }
+    }
+  };
+  // after stage st: at the end of a scale group inside the block's K-range,
+  // the change of units
+  auto change_units = [&](int st) HIGGS_INLINE {
+    const int gn = (kbeg + (st + 1) * 64) >> log2g;
+    if (st + 1 < nst && gn != grp) {
+      if constexpr (kTotals) {
+        add_totals();
+      } else {
+        // exponents are powers of two (normal numbers): compared and divided
+        // by their bit patterns
+        bool ok = s_cur != 0.f && s_nxt != 0.f && fabsf(s_cur) <= 65504.f &&
+                  fabsf(s_nxt) <= 65504.f;
+        bool same = true;
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+          const int d = __float_as_int(x_nxt[t]) - __float_as_int(x_ref[t]);
+          ok = ok && d >= -(20 << 23) && d <= (20 << 23);
+          same = same && x_nxt[t] == x_cur[t];
+        }
+        const bool keep = __all(ok);  // uniform
+        if (!keep) flush();
+        const int keep_bits = keep ? -1 : 0;
+        // the columns' part of the ratio, where there is one
+        if (keep && !__all(same)) {
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            const float rx = __int_as_float(__float_as_int(x_cur[t]) - __float_as_int(x_nxt[t]) +
+                                            0x3f800000);
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) acc[m][t][r] *= rx;
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+          x_ref[t] = __int_as_float((__float_as_int(x_ref[t]) & keep_bits) |
+                                    (__float_as_int(x_nxt[t]) & ~keep_bits));
+        // the rows' part; zero where the sums start again
+        put_rows(keep ? s_cur / s_nxt : 0.f);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float f[4];
+            row_quad(m, q, f);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+              for (int t = 0; t < NB; ++t) acc[m][t][4 * q + k] *= f[k];
+          }
+      }
+      s_cur = s_nxt;
+#pragma unroll
+      for (int t = 0; t < NB; ++t) x_cur[t] = x_nxt[t];
+      grp = gn;
+      load_units(grp + 1, s_nxt, x_nxt);
+    }
+  };
+  // stage 0 is there, in every wave's part of it; so is the table
+  __builtin_amdgcn_sched_barrier(0);
+  wait_loads<2 * kDma>();
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  load_step(0, cod0, 0, ops[0]);
+
+  // Two stages per turn. Codes of pairs of K-blocks (64 bytes of a row for
+  // 8-bit codes) are requested together, two stages ahead; scalar 8-bit codes
+  // (64 bytes per K-block) one stage ahead.
+  constexpr int kLate = kPair ? 2 * kLoads : kLoads;
+  // a stage past the K-group's range, for the barriers of the other group
+  auto idle = [&]() HIGGS_INLINE {
+    if constexpr (KG == 2) {
+      wait_loads<0>();
+      __builtin_amdgcn_s_barrier();
+    }
+  };
+  for (int st = 0; st < nmax; st += 2) {
+    if (KG == 2 && st >= nst) {
+      idle();
+      idle();
+      continue;
+    }
+    if constexpr (kPair) {
+      uint32_t nxt0[2][kW], nxt1[2][kW];
+      fetch(st + 2, nxt0);
+      fetch(st + 3, nxt1);
+      __builtin_amdgcn_sched_barrier(0);
+      stage(st, cod0, cod1, std::integral_constant<int, kLate>{});
+      if constexpr (G64) change_units(st);
+      if (!G64 || st + 1 < nst) {
+        stage(st + 1, cod1, nxt0, std::integral_constant<int, 0>{});
+        change_units(st + 1);
+      } else {
+        idle();
+      }
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int w = 0; w < kW; ++w) {
+          cod0[m][w] = nxt0[m][w];
+          cod1[m][w] = nxt1[m][w];
+        }
+    } else {
+      fetch(st + 1, cod1);
+      __builtin_amdgcn_sched_barrier(0);
+      stage(st, cod0, cod1, std::integral_constant<int, kLate>{});
+      if constexpr (G64) change_units(st);
+      if (!G64 || st + 1 < nst) {
+        fetch(st + 2, cod0);
+        __builtin_amdgcn_sched_barrier(0);
+        stage(st + 1, cod1, cod0, std::integral_constant<int, kLate>{});
+        change_units(st + 1);
+      } else {
+        idle();
+      }
+    }
+  }
+  add_totals();
+
+  // No load may be on its way into LDS when a wave leaves or reuses a buffer.
+  wait_loads<0>();
+  __syncthreads();
+  if constexpr (!kTotals) {
+    if (flushed) {
+      flush();
+      return;
+    }
+  }
+  // ---- store through LDS (the activation buffers are free) so that lanes
+  //      write consecutive rows: 32 x 32 tiles; with two K-groups, group 0
+  //      adds group 1's sums for the same rows and columns ----
+  constexpr int kORow = 33;                // floats per staged column
+  constexpr int kOTile = 32 * kORow;
+  static_assert(kWaves * KG * kOTile * 4 <= KG * kBufs * kStageBytes, "output staging fits");
+  float* s_o = reinterpret_cast<float*>(s_x0) + wave * KG * kOTile;
+  // value of wave tile (m, t) into the wave's tile buffer o
+  auto put_tile = [&](int m, int t, float* o) HIGGS_INLINE {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int rl = 8 * (r / 4) + 4 * ahalf + (r % 4);
+      float v;
+      if constexpr (kTotals)
+        v = total[m][t][r] * x_ref[t];
+      else
+        v = acc[m][t][r] * (__shfl(s_cur, 32 * m + rl, 64) * x_cur[t]);
+      o[(lane & 31) * kORow + rl] = v;
+    }
+  };
+  auto store_tile = [&](int m, int t, const float* o) HIGGS_INLINE {
+    const int row = row0 + 32 * m + (lane & 31);
+    const int colt = col0 + cw * 32 * NB + 32 * t;
+    const __amdgpu_buffer_rsrc_t drs = rsrc(dst + int64_t(colt) * out, 0x7fffffffu);
+    // batch rows of this half of the wave that are stored (none past out)
+    const int nc = row < out ? batch - colt - ahalf : 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int c = 2 * i + ahalf;
+      float v = o[c * kORow + (lane & 31)];
+      if constexpr (KG == 2) v += o[kGWaves * KG * kOTile + c * kORow + (lane & 31)];
+      const uint32_t off = (uint32_t(c) * uint32_t(out) + uint32_t(row)) * 4u;
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), drs,
+                                            int(2 * i < nc ? off : kOffNone), 0, 0);
+    }
+  };
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    if constexpr (KG == 2) {
+      static_assert(KG == 1 || NB == 2, "a wave's two tiles of a row set, side by side");
+#pragma unroll
+      for (int t = 0; t < NB; ++t) put_tile(m, t, s_o + t * kOTile);
+      __syncthreads();
+      if (kgrp == 0) {
+#pragma unroll
+        for (int t = 0; t < NB; ++t) store_tile(m, t, s_o + t * kOTile);
+      }
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        wave_lds_sync();
+        put_tile(m, t, s_o);
+        wave_lds_sync();
+        store_tile(m, t, s_o);
+      }
+    }
+  }
+}
+
+// y = sum over splits of the partial products, in split order (split 0's
+// value first); one element per thread, grid-stride.
+__global__ __launch_bounds__(256) void wide_reduce_kernel(const float* __restrict__ part,
+                                                          int64_t n, int splits,
+                                                          float* __restrict__ y) {
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
+    float s = part[i];
+    for (int k = 1; k < splits; ++k) s += part[int64_t(k) * n + i];
+    y[i] = s;
+  }
+}
+
+int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
+
+int pair_bits(int p, int n) { return p == 1 ? 2 * code_bits(p, n) : code_bits(p, n); }
+
+// Block shapes: rows x batch columns, and the waves' arrangement; times in us
+// measured on MI355X for 8-bit codes: a stage of 64 weights of K with few
+// blocks running and with one on every compute unit (clocks and L2 shared),
+// and the change of units at a scale group's end.
+struct WShape {
+  int rows, cols;
+  double stage_few, stage_full, unit;
+};
+constexpr int kShapes = 3;
+constexpr WShape kShape[kShapes] = {
+    {256, 256, 1.15, 1.70, 1.3},   // one K-group of 8 waves, 64 x 128 each
+    {256, 128, 0.75, 1.10, 1.0},   // one K-group of 8 waves, 64 x 64 each
+    {128, 128, 0.44, 0.63, 0.55},  // two K-groups of 4 waves, 64 x 64 each
+};
+
+// A layer's block shape and K-split.
+struct WPlan {
+  int shape;
+  int64_t kps, splits;
+};
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// The shape and split with the least modelled time: rounds of one block per
+// compute unit, each a start and end (5 us) and its stages; a split adds the
+// reduction launch and the partial sums' traffic. Large tiles decode a code
+// for more columns; small ones, and splits, fill the chip when the layer or
+// the batch is small. The plan depends on the sizes only, and a split's
+// partial sums have to leave the workspace within the library's fixed scratch
+// (so every call that fits the 64-column product's workspace in there fits
+// here too, unsplit if need be).
+WPlan plan_wide(int64_t batch, int64_t out, int64_t in, int g, int bits) {
+  constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
+  const int64_t x_bytes = align256(batch * in * 2) + align256(batch * (in / g) * 4);
+  // measured stage times of the other code widths against 8-bit codes
+  const double width = bits == 8 ? 1.0 : bits == 6 ? 1.08 : bits == 10 ? 1.5 : 1.3;
+  WPlan best{1, ceil_div(in, 256) * 256, 1};
+  double best_t = 1e30;
+  // (g = 64: a change of units every stage, which 64 x 128 wave tiles have no
+  // registers for)
+  for (int sh = g == 64 ? 1 : 0; sh < kShapes; ++sh) {
+    const WShape& S = kShape[sh];
+    const int64_t blocks = ceil_div(out, S.rows) * ceil_div(batch, S.cols);
+    for (const int s : kSplits) {
+      const int64_t kps = ceil_div(ceil_div(in, s), 256) * 256;
+      if (ceil_div(in, kps) != s) continue;
+      if (s > 1 && x_bytes + align256(s * batch * out * 4) > kScratchBytes) break;
+      const double used = std::min(1.0, double(blocks * s) / 256.0);
+      const double stage = (S.stage_few + (S.stage_full - S.stage_few) * used) * width;
+      const double t = double(ceil_div(blocks * s, 256)) *
+                           (double(kps) / 64 * stage + double(kps) / g * S.unit + 5.0) +
+                       (s > 1 ? 4.0 + double((2 * s + 1) * batch * out) * 1e-6 : 0.0);
+      if (t < best_t * 0.97) {
+        best_t = t;
+        best = WPlan{sh, kps, s};
+      }
+    }
+  }
+  return best;
+}
+
+struct WLayout {
+  int64_t x16, xe, part[kMaxGroup], total;
+};
+
+WLayout wide_layout(int64_t batch, const int64_t* outs, int nl, int nx, int64_t in, int g,
+                    int bits) {
+  WLayout L;
+  L.x16 = 0;
+  L.xe = align256(nx * batch * in * 2);
+  int64_t at = L.xe + align256(nx * batch * (in / g) * 4);
+  for (int l = 0; l < nl; ++l) {
+    const WPlan sp = plan_wide(batch, outs[l], in, g, bits);
+    L.part[l] = at;
+    if (sp.splits > 1) at += align256(sp.splits * batch * outs[l] * 4);
+  }
+  L.total = at;
+  return L;
+}
+
+template <typename InT, bool ROT>
+hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, const XSeeds& seeds,
+                             _Float16* x16, float* xe, hipStream_t stream) {
+  const float rscale = float(1.0 / std::sqrt(double(g)));
+  const int64_t groups = batch * (in / g);
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((groups + 3) / 4, 2048));
+  switch (g) {
+#define HIGGS_XPREP(G)                                                                         \
+  case G:                                                                                      \
+    hipLaunchKernelGGL((xprep_wide_kernel<G / 64, InT, ROT>), dim3(unsigned(blocks)),         \
+                       dim3(256), 0, stream, x, batch, in, seeds, rscale, x16, xe);            \
+    return hipGetLastError();
+    HIGGS_XPREP(64)
+    HIGGS_XPREP(128)
+    HIGGS_XPREP(256)
+    HIGGS_XPREP(512)
+    HIGGS_XPREP(1024)
+    HIGGS_XPREP(2048)
+    HIGGS_XPREP(4096)
+#undef HIGGS_XPREP
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+
+template <int BITS, int NB, int KG>
+hipError_t launch_shape(const QW& a, hipStream_t stream) {
+  // g = 64 exists for scalar grids only (8- and 16-bit pairs), and takes no
+  // 256 x 256 blocks (plan_wide)
+  if constexpr ((BITS == 8 || BITS == 16) && NB == 2)
+    if (a.log2g == 6) {
+      hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, KG, true>), dim3(unsigned(a.items)),
+                         dim3(kThreads), 0, stream, a);
+      return hipGetLastError();
+    }
+  hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, KG, false>), dim3(unsigned(a.items)),
+                     dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
+template <int BITS>
+hipError_t launch_bits(const QW& a, int shape, hipStream_t stream) {
+  return shape == 0   ? launch_shape<BITS, 4, 1>(a, stream)
+         : shape == 1 ? launch_shape<BITS, 2, 1>(a, stream)
+                      : launch_shape<BITS, 2, 2>(a, stream);
+}
+
+}  // namespace
+
+// From 65 rows the wide blocks were never slower than the 64-column launches
+// (65 rows: 4096 x 4096 25.9 -> 25.7 us, 14336 x 4096 46 -> 33; 129 rows: 41 ->
+// 30, 72 -> 44); up to 64 rows those need one launch and half the columns of
+// the smallest block here. The limits on `in` keep byte offsets within 32 bits
+// and rows worth splitting.
+bool use_qgemm_wide(int64_t batch, int64_t in) {
+  return batch > 64 && batch < (int64_t(1) << 24) && in >= 512 && in <= (int64_t(1) << 20);
+}
+
+int64_t qgemm_wide_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
+                                   int p, int n, int g) {
+  return wide_layout(batch, outs, layers, layers, in, g, pair_bits(p, n)).total;
+}
+
+hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64_t* seeds,
+                             int64_t batch, const uint8_t* const* codes,
+                             const uint16_t* const* scales, const float* grid, int p, int n, int g,
+                             const int64_t* outs, int64_t in, float* const* y, void* workspace,
+                             hipStream_t stream) {
+  bool same = true;
+  for (int l = 1; l < layers; ++l) same = same && seeds[l] == seeds[0];
+  const int nx = (x_kind == kQgemmRotated || same) ? 1 : layers;
+  const int bits = pair_bits(p, n);
+  const WLayout L = wide_layout(batch, outs, layers, nx, in, g, bits);
+  char* ws = static_cast<char*>(workspace);
+  _Float16* x16 = reinterpret_cast<_Float16*>(ws + L.x16);
+  float* xe = reinterpret_cast<float*>(ws + L.xe);
+  XSeeds xs{};
+  xs.nl = nx;
+  for (int l = 0; l < nx; ++l) xs.s[l] = seeds[l];
+  hipError_t err;
+  switch (x_kind) {
+    case kQgemmRotated:
+      err = launch_xprep_wide<float, false>(static_cast<const float*>(x), batch, in, g, xs, x16, xe,
+                                            stream);
+      break;
+    case kQgemmRawF32:
+      err = launch_xprep_wide<float, true>(static_cast<const float*>(x), batch, in, g, xs, x16, xe,
+                                           stream);
+      break;
+    case kQgemmRawBF16:
+      err = launch_xprep_wide<uint16_t, true>(static_cast<const uint16_t*>(x), batch, in, g, xs,
+                                              x16, xe, stream);
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
+  if (err != hipSuccess) return err;
+
+  WPlan plan[kMaxGroup];
+  float* part[kMaxGroup];
+  for (int l = 0; l < layers; ++l) {
+    plan[l] = plan_wide(batch, outs[l], in, g, bits);
+    part[l] = plan[l].splits > 1 ? reinterpret_cast<float*>(ws + L.part[l]) : y[l];
+  }
+  // one launch per block shape that the layers use
+  for (int shape = 0; shape < kShapes; ++shape) {
+    QW a{};
+    a.xe_stride = nx > 1 ? batch * (in / g) : 0;
+    a.x16_stride = nx > 1 ? batch * in : 0;
+    a.x16 = x16;
+    a.xe = xe;
+    a.grid = grid;
+    a.batch = int(batch);
+    a.pair_table = p == 1 ? 1 : 0;
+    a.log2g = log2_exact(g);
+    a.in = int(in);
+    a.gpr = int(in / g);
+    a.ctiles = int(ceil_div(batch, kShape[shape].cols));
+    int64_t items = 0;
+    for (int l = 0; l < layers; ++l) {
+      if (plan[l].shape != shape) continue;
+      const int k = a.nl++;
+      a.item0[k] = int(items);
+      items += ceil_div(outs[l], kShape[shape].rows) * plan[l].splits * a.ctiles;
+      if (items >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+      a.xcopy[k] = nx > 1 ? l : 0;
+      a.kps[k] = int(plan[l].kps);
+      a.splits[k] = int(plan[l].splits);
+      a.out[k] = int(outs[l]);
+      a.codes[k] = codes[l];
+      a.scales[k] = scales[l];
+      a.dst[k] = part[l];
+    }
+    if (a.nl == 0) continue;
+    a.items = int(items);
+    switch (bits) {
+      case 6: err = launch_bits<6>(a, shape, stream); break;
+      case 8: err = launch_bits<8>(a, shape, stream); break;
+      case 10: err = launch_bits<10>(a, shape, stream); break;
+      case 16: err = launch_bits<16>(a, shape, stream); break;
+      default: return hipErrorInvalidValue;
+    }
+    if (err != hipSuccess) return err;
+  }
+  for (int l = 0; l < layers; ++l) {
+    if (plan[l].splits == 1) continue;
+    const int64_t count = batch * outs[l];
+    const int64_t blocks = std::min<int64_t>((count + 255) / 256, 8192);
+    hipLaunchKernelGGL(wide_reduce_kernel, dim3(unsigned(blocks)), dim3(256), 0, stream, part[l],
+                       count, int(plan[l].splits), y[l]);
+    err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
+}
+
+}  // namespace higgs

@@ -1,0 +1,118 @@
+"""GPU parity of the product at prompt-sized batches (more than 64 rows) against
+a plain PyTorch fp64 product of the same rotated activations, codes and scales.
+
+The sizes reach every block shape (256 x 256, 256 x 128, 128 x 128 with two
+K-groups), with and without a K-split, for every code width: one row past a
+tile, ragged rows, rows of an odd number of 64-weight blocks (g = 64)."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2411_17525_amd import synth
+from test_gpu_parity import check_qmm, grid_f32
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+FORMATS = ((2, 64), (2, 256), (2, 1024), (1, 16), (1, 256))
+# batch, out, in, g: shape and splits of the plan for 8-bit codes in the comments
+SIZES = [
+    (1000, 8200, 512, 128),   # 256 x 256
+    (129, 17000, 2048, 256),  # 256 x 256 or 256 x 128, three splits
+    (129, 17000, 512, 512),   # 256 x 128
+    (65, 100, 512, 128),      # 128 x 128
+    (65, 100, 640, 128),      # 128 x 128, three splits, the last one short
+    (257, 513, 4096, 4096),   # one group per row
+]
+SIZES_G64 = [
+    (129, 17000, 512, 64),  # 256 x 128
+    (65, 12000, 1088, 64),  # 256 x 128, five splits
+    (128, 129, 576, 64),    # 128 x 128, nine stages
+    (65, 100, 1088, 64),    # 128 x 128, five splits, the last one stage
+]
+CASES = [(p, n) + s for p, n in FORMATS for s in SIZES]
+CASES += [(p, n) + s for p, n in FORMATS if p == 1 for s in SIZES_G64]
+
+
+def make_layer(p, n, out, inp, g, seed):
+    from oracle import higgs_oracle as O
+    idx = synth.random_codes(out, inp // p, n, seed)
+    scales = synth.random_scales_f16(out, inp // g, seed + 1)
+    codes = torch.from_numpy(O.pack_codes(idx, n)).cuda()
+    return (codes, torch.from_numpy(scales.view(np.int16)).cuda().view(torch.float16),
+            torch.from_numpy(idx.astype(np.int64)).cuda())
+
+
+def reference(x_rot, idx, scales, grid, g):
+    """fp64 product and the sum of its terms' magnitudes."""
+    out, inp = idx.shape[0], x_rot.shape[1]
+    w = grid.double()[idx].reshape(out, inp // g, g) * scales.double()[:, :, None]
+    w = w.reshape(out, inp)
+    return x_rot.double() @ w.t(), x_rot.double().abs() @ w.abs().t()
+
+
+@pytest.mark.parametrize("p,n,batch,out,inp,g", CASES)
+def test_prompt_product(p, n, batch, out, inp, g):
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] prompt p={p} n={n} batch={batch} {out}x{inp} g={g}", file=sys.stderr,
+          flush=True)
+    grid = torch.from_numpy(grid_f32(p, n)).cuda()
+    codes, scales, idx = make_layer(p, n, out, inp, g, 7)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x = torch.randn((batch, inp), generator=gen, device="cuda")
+    x_rot = H.rht_activations(x, g, 3)
+    y = H.qmatmul(x_rot, codes, scales, grid, g, out)
+    fused = H.qmatmul_fused(x, codes, scales, grid, g, 3, out)
+    ref, _ = reference(x_rot, idx, scales, grid, g)
+    assert torch.equal(y, fused)
+    check_qmm(y.cpu().numpy(), ref.cpu().numpy())
+
+
+@pytest.mark.parametrize("p,n,batch,out,inp,g", [
+    (2, 256, 1000, 8200, 512, 128), (2, 1024, 129, 17000, 2048, 256), (1, 256, 129, 17000, 512, 64),
+    (2, 64, 65, 100, 1024, 128), (1, 16, 65, 100, 1088, 64)])
+def test_prompt_product_unit_changes(p, n, batch, out, inp, g):
+    """Scale groups whose magnitudes, and scales, differ by up to 2^90, zero
+    scales and zero activation groups: the sums change units at every group,
+    or are written out and started again."""
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] prompt units p={p} n={n} batch={batch} {out}x{inp} g={g}",
+          file=sys.stderr, flush=True)
+    grid = torch.from_numpy(grid_f32(p, n)).cuda()
+    codes, scales, idx = make_layer(p, n, out, inp, g, 9)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    groups = inp // g
+    x = torch.randn((batch, groups, g), generator=gen, device="cuda")
+    x *= torch.exp2(torch.randint(-45, 46, (batch, groups, 1), generator=gen,
+                                  device="cuda").float())
+    x[:, 0] *= torch.rand((batch, 1), generator=gen, device="cuda") > 0.3
+    x[::5, 1] = 0
+    x = x.reshape(batch, inp).contiguous()
+    scales[torch.rand(scales.shape, generator=gen, device="cuda") < 0.02] = 0
+    scales[3] = 0
+    scales[:, groups // 2] *= 2.0 ** -9
+    y = H.qmatmul(x, codes, scales, grid, g, out)
+    ref, terms = reference(x, idx, scales, grid, g)
+    # each term's two factors are rounded to fp16 once: (1 + 2^-11)^2 - 1 of
+    # its magnitude, and a little for the fp32 sums
+    assert bool(torch.isfinite(y).all())
+    assert bool(((y.double() - ref).abs() <= 1.02 * 2.0 ** -10 * terms).all())
+    assert bool((y[:, 3] == 0).all())
+
+
+def test_prompt_group_and_noalloc_match_single_calls():
+    from paper_2411_17525_amd import higgs as H
+    p, n, g, batch, inp = 2, 256, 256, 300, 1024
+    grid = torch.from_numpy(grid_f32(p, n)).cuda()
+    x = torch.randn((batch, inp), device="cuda").to(torch.bfloat16)
+    layers = []
+    for k, out in enumerate((8200, 129, 1000)):
+        codes, scales, _ = make_layer(p, n, out, inp, g, 20 + k)
+        layers.append((codes, scales, 40 + k, out))
+    ys = H.qmatmul_fused_multi(x, layers, grid, g)
+    for (codes, scales, seed, out), y in zip(layers, ys):
+        assert torch.equal(y, H.qmatmul_fused(x, codes, scales, grid, g, seed, out))
+        assert torch.equal(y, H.qmatmul_fused_noalloc(x, codes, scales, grid, g, seed, out))
