@@ -95,6 +95,46 @@ __device__ inline void load_group(const InT* __restrict__ src, double (&v)[E]) {
   }
 }
 
+// The same in two parts, so that a group's loads can be issued while the one
+// before it is worked on: the values as they lie in memory, then in fp64.
+template <int E, typename InT>
+struct RawGroup {
+  static constexpr int kBytes = E * int(sizeof(InT));
+  static constexpr bool kVec = kBytes % 16 == 0;
+  u32x4 u[kVec ? kBytes / 16 : 1];
+  InT e[kVec ? 1 : E];
+  __device__ inline void load(const InT* __restrict__ src) {
+    if constexpr (kVec) {
+#pragma unroll
+      for (int q = 0; q < kBytes / 16; ++q)
+        u[q] = load_stream16(reinterpret_cast<const char*>(src) + 16 * q);
+    } else {
+#pragma unroll
+      for (int i = 0; i < E; ++i) e[i] = src[i];
+    }
+  }
+  __device__ inline void expand(double (&v)[E]) const {
+    if constexpr (kVec) {
+#pragma unroll
+      for (int q = 0; q < kBytes / 16; ++q) {
+        const uint32_t w[4] = {u[q].x, u[q].y, u[q].z, u[q].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if constexpr (sizeof(InT) == 4) {
+            v[4 * q + k] = double(__uint_as_float(w[k]));
+          } else {
+            v[8 * q + 2 * k] = double(__uint_as_float(w[k] << 16));
+            v[8 * q + 2 * k + 1] = double(__uint_as_float(w[k] & 0xffff0000u));
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < E; ++i) v[i] = to_f64<InT>(e[i]);
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Search index: exact pruning of the nearest-point search. The square
 // [-kBR, kBR)^P is cut into kNB^P buckets. Point k may be left out of bucket
@@ -701,36 +741,116 @@ __global__ __launch_bounds__(64 * kWaves) void quantize_scan_kernel(
 }
 
 
+// Sign bits of the group's elements (bit j of word q: element 64 q + j is
+// negated), computed by all the waves of the block. Ends with a barrier.
+template <int E, int kNW>
+__device__ inline void block_signs(uint64_t seed, uint64_t (&s_neg)[E], int wave, int lane) {
+  for (int q = wave; q < E; q += kNW) {
+    const uint64_t bits = __ballot(rht_sign_negative(seed, uint32_t(64 * q + lane)));
+    if (lane == 0) s_neg[q] = bits;
+  }
+  __syncthreads();
+}
+
+// Little-endian dword at any byte address.
+struct __attribute__((packed, aligned(1))) AnyU32 {
+  uint32_t v;
+};
+
 // Quantization error of a layer, measured in the rotated space: the rotation
 // R = H diag(sigma) / sqrt(g) is orthonormal, so per group (Parseval)
 //   ||w - w_hat||^2 = || H (sigma * w) / sqrt(g) - scale * concat_j G[code_j] ||^2
 // with w_hat the dequantised group (App. G). One wavefront per group writes
 // that sum and ||w||^2 as two fp64 values (row-major group order); the layer's
-// relative error t^2 (Sec. 3.4) is their ratio of sums. Codes are read from
-// the packed row (LSB-first, `bits` per code, up to three bytes per code).
-template <int E, int P, typename InT>
+// relative error t^2 (Sec. 3.4) is their ratio of sums. The group's codes are
+// read as whole dwords into the wave's LDS and the grid is kept in LDS: read
+// from memory per code (three bytes and a gather each), the vector memory
+// unit was the bound (4096 x 14336 bf16, 6-bit codes: 152 us; 100 us with both
+// in LDS, 70 us with the rotation through LDS for g = 1024 and the next group's
+// loads issued ahead). Now bound by the vector ALU: about 480 instructions per
+// 1024 weights and lane, two thirds of them fp64.
+template <int E, int P, int BITS, typename InT>
 __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
     const InT* __restrict__ w, int64_t rows, int64_t in, uint64_t seed,
-    const float* __restrict__ grid, int bits, const uint8_t* __restrict__ codes, int64_t row_bytes,
+    const float* __restrict__ grid, const uint8_t* __restrict__ codes, int64_t row_bytes,
     const uint16_t* __restrict__ scales, double* __restrict__ out) {
   constexpr int G = 64 * E;
+  constexpr int V = E / P;                      // codes per lane
+  constexpr int kWords = G / P * BITS / 32;     // dwords of a group's codes
+  constexpr int kLaneWords = (V * BITS + 31) / 32;
   static_assert(E % P == 0, "a lane must hold whole p-vectors");
+  static_assert(G / P * BITS % 32 == 0, "group must fill whole dwords");
+  // g = 1024: rotated through LDS, which leaves a lane other elements than it
+  // read; the unpacked codes go through LDS as well
+  constexpr bool kRows = E == 16;
+  // small grids are kept in fp64 (no conversion per element)
+  using GridT = typename std::conditional<((P << BITS) <= 512), double, float>::type;
+  __shared__ GridT s_grid[P << BITS];
+  __shared__ uint32_t s_words[kWaves][kWords + 2];  // a lane's window may end past its codes
+  __shared__ __align__(16) double s_rot[kWaves][kRows ? kFwht1024Rows : 2];
+  __shared__ __align__(16) uint16_t s_code[kWaves][kRows ? G / P : 8];
+  __shared__ uint64_t s_neg[E];
   const int lane = int(threadIdx.x) & 63;
   const int wave = int(threadIdx.x) >> 6;
-  uint64_t neg = 0;
-#pragma unroll
-  for (int i = 0; i < E; ++i) neg |= uint64_t(rht_sign_negative(seed, uint32_t(lane * E + i))) << i;
+  for (int k = int(threadIdx.x); k < P << BITS; k += 64 * kWaves) s_grid[k] = GridT(grid[k]);
+  if (lane < 2) s_words[wave][kWords + lane] = 0;
+  block_signs<E, kWaves>(seed, s_neg, wave, lane);
+  const uint64_t neg = s_neg[lane * E / 64] >> (lane * E % 64);
   const int64_t groups_per_row = in / G;
   const int64_t total = rows * groups_per_row;
   const double inv_sqrt_g = 1.0 / sqrt(double(G));
-  const uint32_t mask = (1u << bits) - 1u;
-  // no barrier below: each wave walks its own groups
-  for (int64_t grp = int64_t(blockIdx.x) * kWaves + wave; grp < total;
-       grp += int64_t(gridDim.x) * kWaves) {
+  const int bit0 = lane * V * BITS;
+  const uint32_t* mine = &s_words[wave][bit0 >> 5];
+  const int n0 = fwht1024_rows_lane(lane);
+  // what a group needs from memory, requested one group ahead
+  RawGroup<E, InT> raw;
+  uint32_t cd[(kWords + 63) / 64];
+  uint16_t sc = 0;
+  auto request = [&](int64_t grp) {
     const int64_t row = grp / groups_per_row;
     const int64_t gi = grp - row * groups_per_row;
+    raw.load(w + row * in + gi * G + lane * E);
+    const AnyU32* cw =
+        reinterpret_cast<const AnyU32*>(codes + row * row_bytes + gi * int64_t(kWords * 4));
+#pragma unroll
+    for (int q = 0; q < (kWords + 63) / 64; ++q)
+      cd[q] = 64 * q + lane < kWords ? cw[64 * q + lane].v : 0u;
+    sc = scales[grp];
+  };
+  // no barrier below: each wave walks its own groups
+  const int64_t step = int64_t(gridDim.x) * kWaves;
+  int64_t grp = int64_t(blockIdx.x) * kWaves + wave;
+  if (grp < total) request(grp);
+  for (; grp < total; grp += step) {
+    const double sh = double(__builtin_bit_cast(_Float16, sc));
     double v[E];
-    load_group<E, InT>(w + row * in + gi * G + lane * E, v);
+    raw.expand(v);
+    wave_sync();  // the last group's words have been read
+#pragma unroll
+    for (int q = 0; q < (kWords + 63) / 64; ++q)
+      if (64 * q + lane < kWords) s_words[wave][64 * q + lane] = cd[q];
+    wave_sync();
+    if (grp + step < total) request(grp + step);
+    // the lane's codes: of its own vectors
+    uint32_t win[kLaneWords], code[V];
+#pragma unroll
+    for (int q = 0; q < kLaneWords; ++q)
+      win[q] = __builtin_amdgcn_alignbit(mine[q + 1], mine[q], uint32_t(bit0 & 31));
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      const int b = t * BITS, wq = b >> 5, o = b & 31;
+      uint32_t c = win[wq] >> o;
+      if (o + BITS > 32) c |= win[wq + 1 < kLaneWords ? wq + 1 : wq] << (32 - o);
+      code[t] = c & ((1u << BITS) - 1u);
+    }
+    if constexpr (kRows) {
+      u32x4* dst = reinterpret_cast<u32x4*>(&s_code[wave][lane * V]);
+#pragma unroll
+      for (int q = 0; q < V / 8; ++q)
+        dst[q] = u32x4{code[8 * q] | code[8 * q + 1] << 16, code[8 * q + 2] | code[8 * q + 3] << 16,
+                       code[8 * q + 4] | code[8 * q + 5] << 16,
+                       code[8 * q + 6] | code[8 * q + 7] << 16};
+    }
     double ss = 0.0;
 #pragma unroll
     for (int i = 0; i < E; ++i) ss += v[i] * v[i];
@@ -738,24 +858,27 @@ __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
 #pragma unroll
     for (int i = 0; i < E; ++i)
       if ((neg >> i) & 1) v[i] = -v[i];
-    fwht_wave<E>(v, lane, G);
-    const double sh = double(__builtin_bit_cast(_Float16, scales[row * groups_per_row + gi]));
-    const uint8_t* crow = codes + row * row_bytes;
     double e = 0.0;
+    if constexpr (kRows) {
+      fwht1024_rows(v, s_rot[wave], lane);
 #pragma unroll
-    for (int t = 0; t < E / P; ++t) {
-      const int64_t m = gi * (G / P) + lane * (E / P) + t;  // code index in the row
-      const int64_t bit = m * bits;
-      const int64_t b0 = bit >> 3;
-      uint32_t win = crow[b0];
-      if (b0 + 1 < row_bytes) win |= uint32_t(crow[b0 + 1]) << 8;
-      if (b0 + 2 < row_bytes) win |= uint32_t(crow[b0 + 2]) << 16;
-      const uint32_t code = (win >> (bit & 7)) & mask;
-#pragma unroll
-      for (int c = 0; c < P; ++c) {
-        const double d = v[t * P + c] * inv_sqrt_g - sh * double(grid[code * P + c]);
+      for (int r = 0; r < E; ++r) {
+        const int n = n0 + fwht1024_rows_reg(r);
+        const uint32_t c = s_code[wave][n / P];
+        // in units of 1 / sqrt(g) = 1 / 32: exact, one multiply less
+        const double d = fma(-32.0 * sh, double(s_grid[c * P + (n & (P - 1))]), v[r]);
         e += d * d;
       }
+      e *= inv_sqrt_g * inv_sqrt_g;
+    } else {
+      fwht_wave<E>(v, lane, G);
+#pragma unroll
+      for (int t = 0; t < V; ++t)
+#pragma unroll
+        for (int c = 0; c < P; ++c) {
+          const double d = v[t * P + c] * inv_sqrt_g - sh * double(s_grid[code[t] * P + c]);
+          e += d * d;
+        }
     }
     e = wave_sum(e, lane);
     if (lane == 0) {
@@ -766,22 +889,37 @@ __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
 }
 
 // t^2 = sum_q err_q / sum_q norm_q over the per-group pairs of
-// layer_error_kernel (Sec. 3.4's relative error of the layer). One block:
-// thread t adds the pairs t, t + 256, ... in order, then a fixed tree over
-// the threads (deterministic). A layer of norm 0 gets t^2 = 0.
-__global__ __launch_bounds__(256) void layer_t2_kernel(const double* __restrict__ pairs,
-                                                       int64_t groups, double* __restrict__ t2) {
-  __shared__ double s_e[256], s_n[256];
+// layer_error_kernel (Sec. 3.4's relative error of the layer). One block (no
+// memory for partial sums here): thread t adds the pairs t, t + 1024, ... in
+// order, sixteen loads in flight, then a fixed tree over the threads
+// (deterministic). A layer of norm 0 gets t^2 = 0. Bound by one compute unit's
+// loads: 57344 groups take 12 us (57 us with 256 threads and one load at a time).
+__global__ __launch_bounds__(1024) void layer_t2_kernel(const double* __restrict__ pairs,
+                                                        int64_t groups, double* __restrict__ t2) {
+  __shared__ double s_e[1024], s_n[1024];
   const int tid = int(threadIdx.x);
   double e = 0.0, nrm = 0.0;
-  for (int64_t q = tid; q < groups; q += 256) {
-    e += pairs[2 * q];
-    nrm += pairs[2 * q + 1];
+  constexpr int kAhead = 16;
+  for (int64_t q0 = tid; q0 < groups; q0 += 1024 * kAhead) {
+    double pe[kAhead], pn[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int64_t q = q0 + 1024 * i;
+      const int64_t at = q < groups ? q : q0;
+      pe[i] = pairs[2 * at];
+      pn[i] = pairs[2 * at + 1];
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if (q0 + 1024 * i < groups) {
+        e += pe[i];
+        nrm += pn[i];
+      }
   }
   s_e[tid] = e;
   s_n[tid] = nrm;
   __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
+  for (int h = 512; h > 0; h >>= 1) {
     if (tid < h) {
       s_e[tid] += s_e[tid + h];
       s_n[tid] += s_n[tid + h];
@@ -791,19 +929,21 @@ __global__ __launch_bounds__(256) void layer_t2_kernel(const double* __restrict_
   if (tid == 0) t2[0] = s_n[0] > 0.0 ? s_e[0] / s_n[0] : 0.0;
 }
 
-template <int P, typename InT>
-hipError_t launch_error_p(const InT* w, int64_t out_rows, int64_t in, const float* grid, int bits,
-                          int g, uint64_t seed, const uint8_t* codes, int64_t row_bytes,
+template <int P, int BITS, typename InT>
+hipError_t launch_error_p(const InT* w, int64_t out_rows, int64_t in, const float* grid, int g,
+                          uint64_t seed, const uint8_t* codes, int64_t row_bytes,
                           const uint16_t* scales, double* err, hipStream_t stream) {
   const int64_t total = out_rows * (in / g);
-  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((total + kWaves - 1) / kWaves, 8192));
+  // eight blocks per compute unit: a block reads the grid and forms the signs
+  // once, then its waves take groups in turn
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((total + kWaves - 1) / kWaves, 2048));
   const dim3 grid_dim{unsigned(blocks)}, block{64 * kWaves};
   switch (g) {
 #define HIGGS_E_CASE(GV)                                                                     \
   case GV:                                                                                   \
     if constexpr ((GV / 64) % P == 0) {                                                      \
-      hipLaunchKernelGGL((layer_error_kernel<GV / 64, P, InT>), grid_dim, block, 0, stream, \
-                         w, out_rows, in, seed, grid, bits, codes, row_bytes, scales, err);  \
+      hipLaunchKernelGGL((layer_error_kernel<GV / 64, P, BITS, InT>), grid_dim, block, 0,    \
+                         stream, w, out_rows, in, seed, grid, codes, row_bytes, scales, err); \
       return hipGetLastError();                                                              \
     }                                                                                        \
     break;
@@ -818,6 +958,24 @@ hipError_t launch_error_p(const InT* w, int64_t out_rows, int64_t in, const floa
     default:
       break;
   }
+  return hipErrorInvalidValue;
+}
+
+template <typename InT>
+hipError_t launch_error_typed(const InT* w, int64_t out, int64_t in, const float* grid, int p,
+                              int bits, int g, uint64_t seed, const uint8_t* codes,
+                              int64_t row_bytes, const uint16_t* scales, double* err,
+                              hipStream_t stream) {
+#define HIGGS_E_FORMAT(PV, BV)                                                              \
+  if (p == PV && bits == BV)                                                                \
+    return launch_error_p<PV, BV>(w, out, in, grid, g, seed, codes, row_bytes, scales, err, \
+                                  stream);
+  HIGGS_E_FORMAT(1, 4)
+  HIGGS_E_FORMAT(1, 8)
+  HIGGS_E_FORMAT(2, 6)
+  HIGGS_E_FORMAT(2, 8)
+  HIGGS_E_FORMAT(2, 10)
+#undef HIGGS_E_FORMAT
   return hipErrorInvalidValue;
 }
 
@@ -1156,22 +1314,14 @@ hipError_t launch_layer_error(const void* w, higgs_dtype dtype, int64_t out, int
                               hipStream_t stream) {
   const int bits = code_bits(p, n);
   const int64_t row_bytes = in / p * bits / 8;
-  hipError_t st;
-  if (dtype == HIGGS_F32) {
-    const float* wf = static_cast<const float*>(w);
-    st = p == 1 ? launch_error_p<1>(wf, out, in, grid, bits, g, seed, codes, row_bytes, scales,
-                                    err, stream)
-                : launch_error_p<2>(wf, out, in, grid, bits, g, seed, codes, row_bytes, scales,
-                                    err, stream);
-  } else {
-    const uint16_t* wb = static_cast<const uint16_t*>(w);
-    st = p == 1 ? launch_error_p<1>(wb, out, in, grid, bits, g, seed, codes, row_bytes, scales,
-                                    err, stream)
-                : launch_error_p<2>(wb, out, in, grid, bits, g, seed, codes, row_bytes, scales,
-                                    err, stream);
-  }
+  const hipError_t st =
+      dtype == HIGGS_F32
+          ? launch_error_typed(static_cast<const float*>(w), out, in, grid, p, bits, g, seed,
+                               codes, row_bytes, scales, err, stream)
+          : launch_error_typed(static_cast<const uint16_t*>(w), out, in, grid, p, bits, g, seed,
+                               codes, row_bytes, scales, err, stream);
   if (st != hipSuccess || t2 == nullptr) return st;
-  hipLaunchKernelGGL(layer_t2_kernel, dim3(1), dim3(256), 0, stream, err, out * (in / g), t2);
+  hipLaunchKernelGGL(layer_t2_kernel, dim3(1), dim3(1024), 0, stream, err, out * (in / g), t2);
   return hipGetLastError();
 }
 

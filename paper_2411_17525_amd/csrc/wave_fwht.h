@@ -162,6 +162,17 @@ __device__ inline void fwht_lane_stage_deferred(T (&v)[E], int lane) {
 #pragma unroll
     for (int i = 0; i < E; ++i)
       v[i] = fma_t(s, __builtin_bit_cast(T, lo[i]), __builtin_bit_cast(T, hi[i]));
+  } else if constexpr (M >= 16) {
+    // the pair's values in both lanes (as for float): no selects
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const uint64_t u = __builtin_bit_cast(uint64_t, v[i]);
+      uint32_t l0, h0, l1, h1;
+      lane_pair<M>(uint32_t(u), l0, h0);
+      lane_pair<M>(uint32_t(u >> 32), l1, h1);
+      v[i] = fma_t(s, __builtin_bit_cast(T, uint64_t(l0) | (uint64_t(l1) << 32)),
+                   __builtin_bit_cast(T, uint64_t(h0) | (uint64_t(h1) << 32)));
+    }
   } else {
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = fma_t(lane_xor<M>(v[i], lane), s, v[i]);
@@ -267,6 +278,82 @@ __device__ inline void fwht1024_lds(float (&v)[16], float* w, int lane) {
         v[i] = x0 + x1;
         v[i + st] = x0 - x1;
       }
+}
+
+// Exchanges lane bit M (16 or 32) with a register bit: on return a holds, in
+// lanes without M, a of the same lane and, in lanes with M, b of lane - M; b
+// holds a of lane + M and b of the same lane. So a + b and a - b are the
+// butterfly over lane bit M of the old a (lanes without M) and of the old b.
+template <int M>
+__device__ inline void lane_swap(double& a, double& b) {
+  const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+  uint32_t x0, y0, x1, y1;
+  if constexpr (M == 16) {
+    const auto r0 = __builtin_amdgcn_permlane16_swap(uint32_t(ua), uint32_t(ub), false, false);
+    const auto r1 =
+        __builtin_amdgcn_permlane16_swap(uint32_t(ua >> 32), uint32_t(ub >> 32), false, false);
+    x0 = r0[0]; y0 = r0[1]; x1 = r1[0]; y1 = r1[1];
+  } else {
+    static_assert(M == 32, "permlane distance");
+    const auto r0 = __builtin_amdgcn_permlane32_swap(uint32_t(ua), uint32_t(ub), false, false);
+    const auto r1 =
+        __builtin_amdgcn_permlane32_swap(uint32_t(ua >> 32), uint32_t(ub >> 32), false, false);
+    x0 = r0[0]; y0 = r0[1]; x1 = r1[0]; y1 = r1[1];
+  }
+  a = __builtin_bit_cast(double, uint64_t(x0) | (uint64_t(x1) << 32));
+  b = __builtin_bit_cast(double, uint64_t(y0) | (uint64_t(y1) << 32));
+}
+
+// LDS doubles of fwht1024_rows's scratch (one per wave, 16-byte aligned).
+constexpr int kFwht1024Rows = 4 * 304;
+
+// Unnormalised FWHT of 1024 fp64 values held 16 per lane (lane l: elements
+// 16 l .. 16 l + 15), the stages in the order of the element bits and each
+// (a + b, a - b), as in fwht_wave, so the values are the same bit for bit; they
+// come back in other places. Element bits 0-3 in the lane; bits 4-7 in the
+// lane after the 16 lanes of a row exchange their values through LDS; bits 8
+// and 9 by exchanging lane bits 4 and 5 with register bits 3 and 2, two
+// elements per exchange (one swap and one add per element, where the
+// cross-lane form moves both halves of every value to its partner). About 200
+// instructions instead of 500. On return v[r] of lane l is element
+// fwht1024_rows_lane(l) + fwht1024_rows_reg(r).
+__device__ inline void fwht1024_rows(double (&v)[16], double* w, int lane) {
+  typedef double f64x2_v __attribute__((ext_vector_type(2)));
+  wave_lds_sync();  // this wave's earlier accesses of w come first
+  fwht_in_lane<16>(v);
+  double* row = w + 304 * (lane >> 4);
+  {
+    f64x2_v* p = reinterpret_cast<f64x2_v*>(row + 18 * (lane & 15));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = f64x2_v{v[2 * k], v[2 * k + 1]};
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = row[18 * i + (lane & 15)];
+  fwht_in_lane<16>(v);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    lane_swap<16>(v[i], v[i + 8]);
+    const double x = v[i], y = v[i + 8];
+    v[i] = x + y;
+    v[i + 8] = x - y;
+  }
+#pragma unroll
+  for (int h = 0; h < 16; h += 8)
+#pragma unroll
+    for (int i = h; i < h + 4; ++i) {
+      lane_swap<32>(v[i], v[i + 4]);
+      const double x = v[i], y = v[i + 4];
+      v[i] = x + y;
+      v[i + 4] = x - y;
+    }
+}
+// (its lane part and its register part; they share no bits)
+__device__ inline constexpr int fwht1024_rows_lane(int lane) {
+  return (lane & 15) | ((lane >> 5) & 1) << 6 | ((lane >> 4) & 1) << 7;
+}
+__device__ inline constexpr int fwht1024_rows_reg(int r) {
+  return (r & 3) << 4 | ((r >> 3) & 1) << 8 | ((r >> 2) & 1) << 9;
 }
 
 }  // namespace higgs
