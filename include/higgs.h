@@ -252,7 +252,7 @@ higgs_status higgs_layer_error(const void *W, higgs_dtype w_dtype, int64_t out, 
  * point of v sqrt(g) / s (lowest index on ties), and with e = v - (s /
  * sqrt(g)) G[q] and E = e U_pp^-1 (U_pp the diagonal p x p block of U) every
  * later column j moves by -E U[p-vector, j]. fp64 throughout; the update of a
- * block of 64 columns runs in the block, later columns get one GEMM per
+ * block of 64 columns runs in the block, later columns are updated by one GEMM per
  * block. With a diagonal H the codes are those of higgs_quantize (up to the
  * fp64 rounding of the normalisation).
  *   factor     [in]  device, as written by higgs_gptq_factor for this `in`.

@@ -1067,8 +1067,8 @@ hipError_t launch_typed(const InT* w, int64_t out, int64_t in, const float* grid
 // v sqrt(g) / s, s the group's norm), the error e = v - (s / sqrt(g)) G[q] is
 // scaled, E = e U_pp^-1 (U_pp the p x p diagonal block), and later columns
 // move by -E U[p-vector, later]. Within a block of 64 columns the update runs
-// here, one wavefront per row (lane j holds column c0 + j); the block's E go
-// to `err` and the columns after the block are updated by one GEMM.
+// here; E takes the place of the block's columns of W', and later columns get
+// their updates from it by matrix products (gptq.cpp).
 // ---------------------------------------------------------------------------
 
 // Rotated weights W' (fp64), each group's norm s (fp64) and the stored scale
@@ -1078,11 +1078,13 @@ __global__ __launch_bounds__(64 * kWaves) void gptq_prepare_kernel(
     const InT* __restrict__ w, int64_t rows, int64_t in, uint64_t seed, double* __restrict__ wr,
     double* __restrict__ norms, uint16_t* __restrict__ scales) {
   constexpr int G = 64 * E;
+  constexpr bool kRows = E == 16;  // g = 1024: rotated through LDS
+  __shared__ __align__(16) double s_rot[kWaves][kRows ? kFwht1024Rows : 2];
+  __shared__ uint64_t s_neg[E];
   const int lane = int(threadIdx.x) & 63;
   const int wave = int(threadIdx.x) >> 6;
-  uint64_t neg = 0;
-#pragma unroll
-  for (int i = 0; i < E; ++i) neg |= uint64_t(rht_sign_negative(seed, uint32_t(lane * E + i))) << i;
+  block_signs<E, kWaves>(seed, s_neg, wave, lane);
+  const uint64_t neg = s_neg[lane * E / 64] >> (lane * E % 64);
   const int64_t groups_per_row = in / G;
   const int64_t total = rows * groups_per_row;
   const double inv_sqrt_g = 1.0 / sqrt(double(G));
@@ -1100,10 +1102,17 @@ __global__ __launch_bounds__(64 * kWaves) void gptq_prepare_kernel(
 #pragma unroll
     for (int i = 0; i < E; ++i)
       if ((neg >> i) & 1) v[i] = -v[i];
-    fwht_wave<E>(v, lane, G);
-    double* dst = wr + row * in + gi * G + lane * E;
+    double* dst = wr + row * in + gi * G;
+    if constexpr (kRows) {
+      fwht1024_rows(v, s_rot[wave], lane);
 #pragma unroll
-    for (int i = 0; i < E; ++i) dst[i] = v[i] * inv_sqrt_g;
+      for (int i = 0; i < E; ++i)
+        dst[fwht1024_rows_lane(lane) + fwht1024_rows_reg(i)] = v[i] * inv_sqrt_g;
+    } else {
+      fwht_wave<E>(v, lane, G);
+#pragma unroll
+      for (int i = 0; i < E; ++i) dst[lane * E + i] = v[i] * inv_sqrt_g;
+    }
     if (lane == 0) {
       norms[grp] = sn;
       scales[grp] = f64_to_f16_rne(sn * inv_sqrt_g);
@@ -1111,115 +1120,190 @@ __global__ __launch_bounds__(64 * kWaves) void gptq_prepare_kernel(
   }
 }
 
-__device__ inline double readlane_f64(double v, int l) {
+// min(a, b) of values that are not NaN (fmin would first quieten both).
+__device__ inline double min_f64(double a, double b) {
+  double r;
+  __asm__("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// The value of lane L of this lane's row of 16 lanes.
+template <int L>
+__device__ inline double row16_lane(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u)), l));
-  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u >> 32)), l));
+  const uint32_t lo =
+      uint32_t(__builtin_amdgcn_mov_dpp(int(uint32_t(u)), 0x150 + L, 0xF, 0xF, true));
+  const uint32_t hi =
+      uint32_t(__builtin_amdgcn_mov_dpp(int(uint32_t(u >> 32)), 0x150 + L, 0xF, 0xF, true));
   return __builtin_bit_cast(double, uint64_t(lo) | (uint64_t(hi) << 32));
 }
 
-// One block of 64 columns [c0, c0 + 64) for every row (one wavefront per row).
-template <int P>
-__global__ __launch_bounds__(64 * kWaves) void gptq_block_kernel(
-    const double* __restrict__ wr, const double* __restrict__ norms,
-    const double* __restrict__ u, const float* __restrict__ grid, int n, int64_t rows,
-    int64_t in, int log2g, int64_t c0, int bits, uint8_t* __restrict__ codes, int64_t row_bytes,
-    double* __restrict__ err) {
+// f(0), f(1), ..., f(N - 1) with compile-time arguments.
+template <int N, int I = 0, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// One block of 64 columns [c0, c0 + 64) for every row of W'. LPR lanes share a
+// row of W' (16, 32 or 64 for grids of 16, up to 256, and 1024 points): lane s
+// of them holds the grid points s, s + LPR, ... (16 at most) in registers, and
+// each of their 16-lane rows holds all 64 columns (lane c: columns c, c + 16,
+// ...), so that a column's value reaches every lane by one DPP broadcast. The
+// p-vectors of a row are a serial chain, and a layer has few rows for a chip,
+// so the chain's length is the time: per p-vector the broadcast, the lane's
+// candidates (two fma and a minimum each), a minimum over the row's lanes, the
+// lowest index that has it, the error, and the later columns' update. 32 lanes
+// per row give 4096 rows two wavefronts per SIMD, which hide each other's
+// latencies (16 lanes, one wavefront: 36 us per block of columns; 32 lanes: 24
+// us; a wavefront per row with the candidates in LDS and the minimum found by
+// LDS shuffles of (value, index): 90 us). Quotients by U's diagonal are formed
+// from its reciprocals with one correction step.
+constexpr int kGptqWaves = 8;
+
+template <int P, int N>
+__global__ __launch_bounds__(64 * kGptqWaves, 2) void gptq_block_kernel(
+    double* __restrict__ wr, const double* __restrict__ norms, const double* __restrict__ u,
+    const float* __restrict__ grid, int64_t rows, int64_t in, int log2g, int64_t c0,
+    uint8_t* __restrict__ codes, int64_t row_bytes) {
   constexpr int kB = 64;
+  constexpr int kBits = N == 16 ? 4 : N == 64 ? 6 : N == 256 ? 8 : 10;
+  constexpr int LPR = N > 256 ? 64 : N > 16 ? 32 : 16;
+  constexpr int kRowsPerWave = 64 / LPR;
+  constexpr int KC = kB / 16;                  // columns per lane
+  constexpr int kCand = N / LPR;               // grid points per lane
   constexpr int kVecs = kB / P;
-  __shared__ double s_u[kB][kB + 1];
-  __shared__ double s_grid[kMaxN * (P + 1)];
-  __shared__ uint16_t s_codes[kWaves][kVecs];
+  constexpr int kWordsPerRow = kVecs * kBits / 32;
+  static_assert(kWordsPerRow <= LPR, "one lane per packed dword");
+  __shared__ double s_u[kB][kB];
+  __shared__ double s_r[kB];                   // 1 / U's diagonal
+  __shared__ double s_grid[N * P];
+  __shared__ uint16_t s_codes[kGptqWaves * kRowsPerWave][kVecs];
   const int tid = int(threadIdx.x);
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  for (int i = tid; i < kB * kB; i += 64 * kWaves) {
+  const int sub = lane % LPR;  // candidates sub, sub + LPR, ...
+  const int col = lane & 15;   // columns col, col + 16, ...
+  const int rslot = wave * kRowsPerWave + lane / LPR;
+  for (int i = tid; i < kB * kB; i += 64 * kGptqWaves) {
     const int r = i / kB, c = i % kB;
-    s_u[r][c] = c >= r ? u[(c0 + r) * in + c0 + c] : 0.0;  // upper triangle only
+    const double x = c >= r ? u[(c0 + r) * in + c0 + c] : 0.0;  // upper triangle only
+    s_u[r][c] = x;
+    if (r == c) s_r[r] = 1.0 / x;
   }
-  for (int k = tid; k < n; k += 64 * kWaves) {
+  for (int k = tid; k < N * P; k += 64 * kGptqWaves) s_grid[k] = double(grid[k]);
+  __syncthreads();
+  const int64_t row_id = int64_t(blockIdx.x) * (kGptqWaves * kRowsPerWave) + rslot;
+  const bool valid = row_id < rows;            // rows past the end repeat the last one
+  const int64_t row = valid ? row_id : rows - 1;
+  // the lane's candidates: coordinates and |G|^2 / 2
+  double cg[kCand][P], ch[kCand];
+#pragma unroll
+  for (int j = 0; j < kCand; ++j) {
     double h = 0.0;
 #pragma unroll
-    for (int t = 0; t < P; ++t) {
-      const double c = double(grid[k * P + t]);
-      s_grid[k * (P + 1) + t] = c;
-      h += c * c;
+    for (int d = 0; d < P; ++d) {
+      cg[j][d] = s_grid[(sub + LPR * j) * P + d];
+      h += cg[j][d] * cg[j][d];
     }
-    s_grid[k * (P + 1) + P] = 0.5 * h;
+    ch[j] = 0.5 * h;
   }
-  __syncthreads();
-  const int64_t row = int64_t(blockIdx.x) * kWaves + wave;
-  if (row >= rows) return;  // no barrier below
   const int g = 1 << log2g;
   const double sn = norms[row * (in >> log2g) + (c0 >> log2g)];  // the block is in one group
   const double fwd = sn > 0.0 ? sqrt(double(g)) / sn : 0.0;      // W' -> grid units
   const double back = sn / sqrt(double(g));                      // grid units -> W'
-  double wv = wr[row * in + c0 + lane];
-  double my_err = 0.0;
-  for (int t = 0; t < kVecs; ++t) {
-    double v[P], uv[P];
+  double* wrow = wr + row * in + c0;
+  double wv[KC];
 #pragma unroll
-    for (int k = 0; k < P; ++k) {
-      v[k] = readlane_f64(wv, t * P + k);
-      uv[k] = v[k] * fwd;
-    }
-    // nearest grid point: lane l scans candidates l, l + 64, ...; then the
-    // wave keeps the least (c, index) pair (lowest index on ties)
-    double best = INFINITY;
-    int bk = 0;
-    for (int k = lane; k < n; k += 64) {
-      double c = s_grid[k * (P + 1) + P];
+  for (int k = 0; k < KC; ++k) wv[k] = wrow[col + 16 * k];
+  // columns 16 k .. 16 k + 15 are in wv[0] at turn k
+  for (int k = 0; k < KC; ++k) {
+    double my_err = 0.0;
+    uint32_t my_q = 0;
+    const double* uk = &s_u[16 * k][16 * k];  // row 16 k, from column 16 k on
+    static_for<16 / P>([&](auto T) __attribute__((always_inline)) {
+      constexpr int i0 = decltype(T)::value * P;  // column inside the turn
+      double v[P], uv[P];
+      static_for<P>([&](auto D) __attribute__((always_inline)) {
+        constexpr int d = decltype(D)::value;
+        v[d] = row16_lane<i0 + d>(wv[0]);
+        uv[d] = v[d] * fwd;
+      });
+      // nearest grid point, the lowest index on ties: the least value over the
+      // lane's candidates and the row's lanes, then the least index that has it
+      double c[kCand], best;
 #pragma unroll
-      for (int d = 0; d < P; ++d) c = fma(-uv[d], s_grid[k * (P + 1) + d], c);
-      if (c < best) {
-        best = c;
-        bk = k;
+      for (int j = 0; j < kCand; ++j) {
+        c[j] = ch[j];
+#pragma unroll
+        for (int d = 0; d < P; ++d) c[j] = fma(-uv[d], cg[j][d], c[j]);
       }
-    }
+      double m[kCand];
 #pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-      const double ob = __shfl_xor(best, m, 64);
-      const int ok = __shfl_xor(bk, m, 64);
-      if (ob < best || (ob == best && ok < bk)) {
-        best = ob;
-        bk = ok;
+      for (int j = 0; j < kCand; ++j) m[j] = c[j];
+#pragma unroll
+      for (int h = kCand / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int j = 0; j < h; ++j) m[j] = min_f64(m[j], m[j + h]);
+      best = m[0];
+      best = min_f64(best, lane_xor<1>(best, lane));
+      best = min_f64(best, lane_xor<2>(best, lane));
+      best = min_f64(best, lane_xor<4>(best, lane));
+      best = min_f64(best, lane_xor<8>(best, lane));
+      if constexpr (LPR >= 32) best = min_f64(best, lane_xor<16>(best, lane));
+      if constexpr (LPR == 64) best = min_f64(best, lane_xor<32>(best, lane));
+      uint32_t q = N - 1;  // (kept if no value compares equal: NaN)
+#pragma unroll
+      for (int j = kCand - 1; j >= 0; --j) q = c[j] == best ? uint32_t(sub + LPR * j) : q;
+      q = min(q, lane_xor_u32<1>(q, lane));
+      q = min(q, lane_xor_u32<2>(q, lane));
+      q = min(q, lane_xor_u32<4>(q, lane));
+      q = min(q, lane_xor_u32<8>(q, lane));
+      if constexpr (LPR >= 32) q = min(q, lane_xor_u32<16>(q, lane));
+      if constexpr (LPR == 64) q = min(q, lane_xor_u32<32>(q, lane));
+      double e[P], es[P];
+#pragma unroll
+      for (int d = 0; d < P; ++d) e[d] = v[d] - back * s_grid[q * P + d];
+      // E = e U_pp^-1 (U_pp upper triangular)
+      const double* u0 = uk + i0 * (kB + 1);  // U's diagonal at the p-vector
+#pragma unroll
+      for (int d = 0; d < P; ++d) {
+        double num = e[d];
+        if (d > 0) num = e[d] - es[0] * u0[1];
+        const double rd = s_r[16 * k + i0 + d], ud = u0[d * (kB + 1)];
+        const double q0 = num * rd;
+        es[d] = fma(fma(-q0, ud, num), rd, q0);
       }
-    }
-    const int q = __builtin_amdgcn_readfirstlane(bk);
-    double e[P], es[P];
+      // later columns (U is zero below its diagonal; the p-vector's own
+      // columns are done with)
 #pragma unroll
-    for (int k = 0; k < P; ++k) e[k] = v[k] - back * s_grid[q * (P + 1) + k];
-    // E = e U_pp^-1 (U_pp upper triangular)
-    const int i0 = t * P;
-    if constexpr (P == 1) {
-      es[0] = e[0] / s_u[i0][i0];
-    } else {
-      es[0] = e[0] / s_u[i0][i0];
-      es[1] = (e[1] - es[0] * s_u[i0][i0 + 1]) / s_u[i0 + 1][i0 + 1];
-    }
-    if (lane >= i0 + P) {
+      for (int j = 0; j < KC; ++j) {
+        const int cj = min(col + 16 * j, kB - 1 - 16 * k);  // past the block: unused
 #pragma unroll
-      for (int k = 0; k < P; ++k) wv = fma(-es[k], s_u[i0 + k][lane], wv);
-    }
+        for (int d = 0; d < P; ++d) wv[j] = fma(-es[d], uk[(i0 + d) * kB + cj], wv[j]);
+      }
 #pragma unroll
-    for (int k = 0; k < P; ++k)
-      if (lane == i0 + k) my_err = es[k];
-    if (lane == 0) s_codes[wave][t] = uint16_t(q);
+      for (int d = 0; d < P; ++d)
+        my_err = col == i0 + d ? es[d] : my_err;
+      my_q = col == i0 / P ? q : my_q;  // lane t of a row keeps the turn's t-th code
+    });
+    if (valid && sub < 16) wrow[16 * k + col] = my_err;
+    if (sub < 16 / P) s_codes[rslot][16 / P * k + sub] = uint16_t(my_q);
+#pragma unroll
+    for (int j = 0; j + 1 < KC; ++j) wv[j] = wv[j + 1];
   }
-  err[row * kB + lane] = my_err;
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  // pack the block's codes: kVecs * bits bits, whole dwords
-  const int words = kVecs * bits / 32;
-  uint32_t* dst = reinterpret_cast<uint32_t*>(codes + row * row_bytes + (c0 / P) * bits / 8);
-  if (lane < words) {
-    const int bit0 = lane * 32;
-    int c = bit0 / bits;
-    uint32_t word = uint32_t(s_codes[wave][c]) >> (bit0 - c * bits);
-    for (++c; c * bits < bit0 + 32 && c < kVecs; ++c)
-      word |= uint32_t(s_codes[wave][c]) << (c * bits - bit0);
-    dst[lane] = word;
+  wave_sync();
+  // pack the block's codes: whole dwords
+  uint32_t* dst = reinterpret_cast<uint32_t*>(codes + row * row_bytes + (c0 / P) * kBits / 8);
+  if (valid && sub < kWordsPerRow) {
+    const int bit0 = sub * 32;
+    int c = bit0 / kBits;
+    uint32_t word = uint32_t(s_codes[rslot][c]) >> (bit0 - c * kBits);
+    for (++c; c * kBits < bit0 + 32 && c < kVecs; ++c)
+      word |= uint32_t(s_codes[rslot][c]) << (c * kBits - bit0);
+    dst[sub] = word;
   }
 }
 
@@ -1281,19 +1365,26 @@ hipError_t launch_gptq_prepare(const void* w, higgs_dtype dtype, int64_t out, in
   }
 }
 
-hipError_t launch_gptq_block(const double* wr, const double* norms, const double* u,
-                             const float* grid, int p, int n, int64_t out, int64_t in, int g,
-                             int64_t c0, uint8_t* codes, double* err, hipStream_t stream) {
-  const int bits = code_bits(p, n);
-  const int64_t row_bytes = in / p * bits / 8;
-  const dim3 grid_dim{unsigned((out + kWaves - 1) / kWaves)}, block{64 * kWaves};
-  if (p == 1)
-    hipLaunchKernelGGL((gptq_block_kernel<1>), grid_dim, block, 0, stream, wr, norms, u, grid, n,
-                       out, in, log2_exact(g), c0, bits, codes, row_bytes, err);
-  else
-    hipLaunchKernelGGL((gptq_block_kernel<2>), grid_dim, block, 0, stream, wr, norms, u, grid, n,
-                       out, in, log2_exact(g), c0, bits, codes, row_bytes, err);
-  return hipGetLastError();
+hipError_t launch_gptq_block(double* wr, const double* norms, const double* u, const float* grid,
+                             int p, int n, int64_t out, int64_t in, int g, int64_t c0,
+                             uint8_t* codes, hipStream_t stream) {
+  const int64_t row_bytes = in / p * code_bits(p, n) / 8;
+#define HIGGS_B_CASE(PV, NV)                                                                    \
+  if (p == PV && n == NV) {                                                                     \
+    constexpr int kRowsPerBlock = kGptqWaves * (NV > 256 ? 1 : NV > 16 ? 2 : 4);                \
+    hipLaunchKernelGGL((gptq_block_kernel<PV, NV>),                                             \
+                       dim3(unsigned((out + kRowsPerBlock - 1) / kRowsPerBlock)),               \
+                       dim3(64 * kGptqWaves), 0, stream, wr, norms, u, grid, out, in,           \
+                       log2_exact(g), c0, codes, row_bytes);                                    \
+    return hipGetLastError();                                                                   \
+  }
+  HIGGS_B_CASE(1, 16)
+  HIGGS_B_CASE(1, 256)
+  HIGGS_B_CASE(2, 64)
+  HIGGS_B_CASE(2, 256)
+  HIGGS_B_CASE(2, 1024)
+#undef HIGGS_B_CASE
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_to_f64(const float* src, int64_t count, double* dst, hipStream_t stream) {

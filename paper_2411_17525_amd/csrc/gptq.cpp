@@ -11,11 +11,17 @@
 //
 // Quantize: the rotated weights W' and group norms (one kernel), then per
 // block of 64 columns the block kernel (rounding, in-block error feedback,
-// codes) and one fp64 GEMM  W'[:, after] -= E_block U[block, after].
+// codes; E takes the block's place in W') and one fp64 GEMM: after block b the
+// errors of the last 2^k blocks, 2^k the largest power of two dividing b + 1,
+// update the next 2^k blocks' columns. 4096 x 4096, (2,256): 8.3 -> 2.9 ms (64
+// block kernels of 24 us, and 1.3 ms of products, of which the one over half
+// the row takes 0.7; with one product of all later columns per block they took
+// 2.6 ms, bound by reading and writing W' for an inner dimension of 64).
 
 #include <rocblas/rocblas.h>
 #include <rocsolver/rocsolver.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <mutex>
 
@@ -57,7 +63,7 @@ int64_t gptq_factor_workspace_bytes(int64_t samples, int64_t in) {
 }
 
 int64_t gptq_quantize_workspace_bytes(int64_t out, int64_t in, int g) {
-  return align256(out * in * 8) + align256(out * (in / g) * 8) + align256(out * 64 * 8);
+  return align256(out * in * 8) + align256(out * (in / g) * 8);  // W' / E, group norms
 }
 
 int gptq_factor(const float* x_rot, int64_t samples, int64_t in, double damp, double* factor,
@@ -126,27 +132,37 @@ int gptq_quantize(const void* w, higgs_dtype dtype, int64_t out, int64_t in, con
   char* ws = static_cast<char*>(workspace);
   double* wr = reinterpret_cast<double*>(ws);
   double* norms = reinterpret_cast<double*>(ws + align256(out * in * 8));
-  double* err = reinterpret_cast<double*>(ws + align256(out * in * 8) + align256(out * (in / g) * 8));
   if (launch_gptq_prepare(w, dtype, out, in, g, seed, wr, norms, scales, stream) != hipSuccess) {
     std::snprintf(msg, size_t(msg_len), "rotation launch failed");
     return HIGGS_ERR_DEVICE;
   }
+  // Blocks of 64 columns left to right. After block b, with 2^k the largest
+  // power of two that divides b + 1, the errors of the last 2^k blocks update
+  // the next 2^k blocks of columns (fewer at the row's end) in one matrix
+  // product: every block's errors reach every later column, each product's
+  // inner dimension is as long as what it updates, and W' is read and written
+  // log2(in / 64) times in all instead of half of in / 64 times.
   const double minus_one = -1.0, one = 1.0;
-  for (int64_t c0 = 0; c0 < in; c0 += 64) {
-    if (launch_gptq_block(wr, norms, factor, grid, p, n, out, in, g, c0, codes, err, stream) !=
+  const int64_t nb = in / 64;
+  for (int64_t b = 0; b < nb; ++b) {
+    if (launch_gptq_block(wr, norms, factor, grid, p, n, out, in, g, 64 * b, codes, stream) !=
         hipSuccess) {
-      std::snprintf(msg, size_t(msg_len), "block launch failed at column %lld", (long long)c0);
+      std::snprintf(msg, size_t(msg_len), "block launch failed at column %lld",
+                    (long long)(64 * b));
       return HIGGS_ERR_DEVICE;
     }
-    const int64_t rest = in - (c0 + 64);
-    if (rest <= 0) break;
-    // column-major views: W'^T[c0+64:, :] (rest x out, ld in) -=
-    //   U[c0:c0+64, c0+64:]^T (rest x 64, ld in) * E^T (64 x out, ld 64)
-    if (rocblas_dgemm(h, rocblas_operation_none, rocblas_operation_none, rocblas_int(rest),
-                      rocblas_int(out), 64, &minus_one, factor + c0 * in + c0 + 64,
-                      rocblas_int(in), err, 64, &one, wr + c0 + 64,
+    const int64_t len = (b + 1) & -(b + 1);            // blocks whose errors are applied
+    const int64_t c0 = 64 * (b + 1 - len);             // their first column
+    const int64_t c1 = 64 * (b + 1);                   // the first column updated
+    const int64_t cols = std::min(64 * len, in - c1);  // columns updated
+    if (cols <= 0) break;
+    // column-major views: W'^T[c1:c1+cols, :] (cols x out, ld in) -=
+    //   U[c0:c1, c1:c1+cols]^T (cols x K, ld in) * E^T[c0:c1, :] (K x out, ld in)
+    if (rocblas_dgemm(h, rocblas_operation_none, rocblas_operation_none, rocblas_int(cols),
+                      rocblas_int(out), rocblas_int(c1 - c0), &minus_one, factor + c0 * in + c1,
+                      rocblas_int(in), wr + c0, rocblas_int(in), &one, wr + c1,
                       rocblas_int(in)) != rocblas_status_success) {
-      std::snprintf(msg, size_t(msg_len), "rocblas_dgemm failed at column %lld", (long long)c0);
+      std::snprintf(msg, size_t(msg_len), "rocblas_dgemm failed at column %lld", (long long)c1);
       return HIGGS_ERR_DEVICE;
     }
   }

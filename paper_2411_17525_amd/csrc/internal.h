@@ -91,9 +91,10 @@ hipError_t launch_layer_error(const void* w, higgs_dtype dtype, int64_t out, int
 hipError_t launch_gptq_prepare(const void* w, higgs_dtype dtype, int64_t out, int64_t in, int g,
                                uint64_t seed, double* wr, double* norms, uint16_t* scales,
                                hipStream_t stream);
-hipError_t launch_gptq_block(const double* wr, const double* norms, const double* u,
-                             const float* grid, int p, int n, int64_t out, int64_t in, int g,
-                             int64_t c0, uint8_t* codes, double* err, hipStream_t stream);
+// Columns [c0, c0 + 64) of wr (W'): codes; the columns become the errors E.
+hipError_t launch_gptq_block(double* wr, const double* norms, const double* u, const float* grid,
+                             int p, int n, int64_t out, int64_t in, int g, int64_t c0,
+                             uint8_t* codes, hipStream_t stream);
 hipError_t launch_to_f64(const float* src, int64_t count, double* dst, hipStream_t stream);
 hipError_t launch_damp_diag(double* h, int64_t in, double damp, hipStream_t stream);
 // Host orchestration; return a higgs_status and fill msg on failure.

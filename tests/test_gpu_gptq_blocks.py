@@ -1,0 +1,39 @@
+"""GPU parity of GPTQ rounding where the blocks of 64 columns are no power of
+two and the rows fill no block of the kernel, for every code width."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import higgs_oracle as O
+from paper_2411_17525_amd import synth
+from test_gpu_parity import GAP_EXEMPT, _calib, grid_f32, weight_dev
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("p,n,g,out,inp,dtype", [
+    (1, 16, 64, 33, 320, "f32"),     # five blocks of columns, 32 rows per block of the kernel
+    (1, 256, 64, 17, 448, "bf16"),   # seven, 16 rows
+    (2, 64, 128, 17, 384, "bf16"),   # six
+    (2, 256, 128, 1, 640, "f32"),    # ten, one row
+    (2, 1024, 128, 9, 896, "bf16"),  # fourteen, 8 rows
+    (2, 256, 1024, 18, 3072, "bf16"),
+])
+def test_gptq_ragged_blocks(p, n, g, out, inp, dtype):
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] gptq blocks p={p} n={n} g={g} {out}x{inp} {dtype}", file=sys.stderr,
+          flush=True)
+    grid = grid_f32(p, n)
+    wt = synth.student_t_weight(out, inp, seed=out + inp, dtype=dtype)
+    x_rot = _calib(2 * inp, inp, out)
+    factor = H.gptq_factor(torch.from_numpy(x_rot).cuda(), 0.01)
+    codes, scales = H.quantize_gptq(weight_dev(wt), torch.from_numpy(grid).cuda(), g, 4, factor)
+    got = O.unpack_codes(codes.cpu().numpy(), n, inp // p)
+    # the library's own factor, so that only the rounding is compared
+    ref = O.quantize_gptq(wt.values.astype(np.float64), grid.astype(np.float64), g, 4,
+                          np.triu(factor.cpu().numpy()), follow=got, follow_tol=GAP_EXEMPT)
+    assert np.array_equal(scales.cpu().numpy().view(np.uint16), ref["scales"].view(np.uint16))
+    assert not ref["mismatch"].any()
+    assert np.array_equal(got, ref["codes"])
