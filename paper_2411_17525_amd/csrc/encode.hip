@@ -1,6 +1,7 @@
 // HIGGS encoder (Alg. 1, RHT-VQ, with the grid of Alg. 2) on the GPU.
 //
-// One wavefront encodes one group of g consecutive weights of one row:
+// Per group of g consecutive weights of one row (a wavefront takes 1024 weights
+// at a time, 1024 / g groups of up to 1024):
 //   s = ||w||_2                      (fp64 sum of squares, fixed reduction tree)
 //   w_dag = H (sigma * (w / s))      (fp64, in-register / cross-lane butterflies)
 //   code_j = argmin_k ||w_dag[jp:(j+1)p] - G_k||^2, lowest k on ties
@@ -111,6 +112,35 @@ struct RawGroup {
     } else {
 #pragma unroll
       for (int i = 0; i < E; ++i) e[i] = src[i];
+    }
+  }
+  // flips signs (masks below)
+  __device__ inline void flip(const uint32_t (&mask)[kVec ? kBytes / 4 : E]) {
+    if constexpr (kVec) {
+#pragma unroll
+      for (int q = 0; q < kBytes / 16; ++q)
+        u[q] ^= u32x4{mask[4 * q], mask[4 * q + 1], mask[4 * q + 2], mask[4 * q + 3]};
+    } else {
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        if constexpr (sizeof(InT) == 4)
+          e[i] = __uint_as_float(__float_as_uint(e[i]) ^ mask[i]);
+        else
+          e[i] = InT(e[i] ^ InT(mask[i]));
+      }
+    }
+  }
+  static constexpr int kMasks = kVec ? kBytes / 4 : E;
+  // flip's masks for sign bits neg of the lane's elements
+  __device__ static inline void masks(uint64_t neg, uint32_t (&mask)[kMasks]) {
+#pragma unroll
+    for (int i = 0; i < kMasks; ++i) {
+      if constexpr (sizeof(InT) == 4)
+        mask[i] = uint32_t(neg >> i) << 31;
+      else if constexpr (kVec)
+        mask[i] = (uint32_t(neg >> (2 * i)) & 1u) << 15 | uint32_t(neg >> (2 * i + 1)) << 31;
+      else
+        mask[i] = (uint32_t(neg >> i) & 1u) << 15;
     }
   }
   __device__ inline void expand(double (&v)[E]) const {
@@ -234,10 +264,13 @@ __device__ inline void box_d2(const double* g, const double (&lo)[P], double w, 
   }
 }
 
-// Bucket index along one axis, or -1 outside [-kBR, kBR) (or for NaN).
+// Bucket index along one axis for |v| < kBR: floor((v + kBR) nb / (2 kBR)) as
+// the nearest integer to that value less 1/2, read from the low mantissa bits
+// after adding 3 2^51 (no change of binade around it). On a bucket's edge it may name either neighbour, and its
+// roundings are below 1e-12: both are covered by the widening of the boxes.
 __device__ inline int bucket_axis(double v, int nb) {
-  const double f = floor((v + kBR) * (double(nb) / (2.0 * kBR)));
-  return (f >= 0.0 && f < double(nb)) ? int(f) : -1;
+  const double f = fma(v, double(nb) / (2.0 * kBR), 0.5 * double(nb) - 0.5) + 0x1.8p52;
+  return int(uint32_t(__builtin_bit_cast(uint64_t, f)));
 }
 
 // In place: counts a[0 .. n) -> exclusive offsets, a[n] = total (n + 1
@@ -404,6 +437,31 @@ __global__ __launch_bounds__(1024) void index_finish_kernel(const float* __restr
   }
 }
 
+// min(a, b) of values that are not NaN (fmin would first quieten both).
+__device__ inline double min_f64(double a, double b) {
+  double r;
+  __asm__("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// Minimum over the 64 lanes of the wave, in every lane (no NaNs).
+__device__ inline double wave_min(double v, int lane) {
+  v = min_f64(v, lane_xor<32>(v, lane));
+  v = min_f64(v, lane_xor<16>(v, lane));
+  v = min_f64(v, lane_xor<8>(v, lane));
+  v = min_f64(v, lane_xor<4>(v, lane));
+  v = min_f64(v, lane_xor<2>(v, lane));
+  v = min_f64(v, lane_xor<1>(v, lane));
+  return v;
+}
+
+__device__ inline double readlane_f64(double v, int l) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u)), l));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u >> 32)), l));
+  return __builtin_bit_cast(double, uint64_t(lo) | (uint64_t(hi) << 32));
+}
+
 // grid point in LDS: its coordinates as read (fp32, exact in fp64), one
 // 8-byte read per candidate; the search constant is formed in registers
 struct __align__(8) GridPt {
@@ -419,28 +477,75 @@ __device__ inline double search_const(const GridPt& q, double shift) {
   return fma(0.5, h, shift);
 }
 
+// Sum of v over the lane's aligned run of L lanes, in every lane of it (for
+// L = 64 in wave_sum's order).
+template <int L>
+__device__ inline double lanes_sum(double v, int lane) {
+  if constexpr (L > 32) v += lane_xor<32>(v, lane);
+  if constexpr (L > 16) v += lane_xor<16>(v, lane);
+  if constexpr (L > 8) v += lane_xor<8>(v, lane);
+  if constexpr (L > 4) v += lane_xor<4>(v, lane);
+  if constexpr (L > 2) v += lane_xor<2>(v, lane);
+  if constexpr (L > 1) v += lane_xor<1>(v, lane);
+  return v;
+}
+
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// E: weights per lane (g = 64 E); P: grid dimension; BITS: packed code width;
-// kQW: waves per block. The waves of a block share the grid and the index in
-// LDS and then take groups independently (no block barrier after the
-// prologue).
-template <int E, int P, int BITS, int kQW, typename InT>
+// Sign bits of the group's elements (bit j of word q: element 64 q + j is
+// negated), computed by all the waves of the block. Ends with a barrier.
+template <int E, int kNW>
+__device__ inline void block_signs(uint64_t seed, uint64_t (&s_neg)[E], int wave, int lane) {
+  for (int q = wave; q < E; q += kNW) {
+    const uint64_t bits = __ballot(rht_sign_negative(seed, uint32_t(64 * q + lane)));
+    if (lane == 0) s_neg[q] = bits;
+  }
+  __syncthreads();
+}
+
+// Copies `bytes` (a multiple of 16) of device memory to LDS by the kQW waves of
+// a block, with no registers between; complete after the waves' own wait for
+// vector memory and a block barrier.
+template <int kQW>
+__device__ inline void copy_to_lds(const uint8_t* src, void* dst, int bytes, int wave, int lane) {
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(src), 0, bytes, 0x00020000);
+  for (int o = wave * 1024; o < bytes; o += kQW * 1024)
+    if (o + lane * 16 < bytes)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, (__attribute__((address_space(3))) void*)(static_cast<char*>(dst) + o), 16,
+          o + lane * 16, 0, 0, 0);
+}
+
+// Bound by the vector ALU (about 1200 instructions per 1024 weights and lane,
+// busy 77% of the time at 14336 x 4096, 256 points, bf16: 155 us, 250 before):
+// the fp64 rotation is a third, the walk of the lists (12 instructions per
+// candidate, four candidates deep) another. The prologue's index arrives in one
+// memory round trip (1024 x 1024: 41 us before, 15 now).
+// G: group size (64 .. 1024); P: grid dimension; BITS: packed code width; kQW:
+// waves per block. A wave takes 1024 weights at a time, 1024 / G groups of them
+// (16 weights per lane whatever the group size: with G / 64 per lane, small
+// groups left a lane one or two vectors, and every read of their search waited
+// on its own; 4096 x 4096 fp32, 1024 points, G = 256: 97 us
+// against 87; 256-point scalar grid, G = 128: 88 against 45). The waves of a
+// block share the grid and the index in LDS and then take their weights
+// independently (no block barrier after the prologue).
+template <int G, int P, int BITS, int kQW, typename InT>
 __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
-    const InT* __restrict__ w, int64_t rows, int64_t in, uint64_t seed,
-    const float* __restrict__ grid, int n, const uint8_t* __restrict__ index,
-    uint8_t* __restrict__ codes, int64_t row_bytes, uint16_t* __restrict__ scales) {
-  constexpr int G = 64 * E;
+    const InT* __restrict__ w, int64_t groups, uint64_t seed, const float* __restrict__ grid, int n,
+    const uint8_t* __restrict__ index, uint8_t* __restrict__ codes,
+    uint16_t* __restrict__ scales) {
+  constexpr int E = 16;           // weights per lane
+  constexpr int kSeg = 64 * E;    // per wave and turn
+  constexpr int kSegGroups = kSeg / G;
+  constexpr int kGroupLanes = G / E;
   constexpr int kVecPerLane = E / P;
-  constexpr int kCodesPerGroup = G / P;
-  constexpr int kWordsPerGroup = kCodesPerGroup * BITS / 32;
-  static_assert(E % P == 0, "a lane must hold whole p-vectors");
-  static_assert(E <= 16, "groups above 1024 weights take quantize_scan_kernel");
-  static_assert((kCodesPerGroup * BITS) % 32 == 0, "group must fill whole dwords");
+  constexpr int kSegCodes = kSeg / P;
+  constexpr int kWordsPerGroup = G / P * BITS / 32;
   constexpr int kN = 1 << BITS;  // grid points of the format (the host passes n = 2^BITS)
   static_assert(kN <= kMaxN, "grid size");
   using BK = Buckets<P, kN>;
@@ -448,8 +553,11 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
   constexpr IndexLayout kL = index_layout(P, kN);
   using CodeT = typename std::conditional<(BITS <= 8), uint8_t, uint16_t>::type;
 
+  // the rotation's scratch, which then takes the codes
+  static_assert(kFwhtRows * 4 >= int(kSegCodes * sizeof(CodeT)), "codes fit the scratch");
   __shared__ GridPt s_grid[kN];
-  __shared__ CodeT s_codes[kQW][kCodesPerGroup];
+  __shared__ __align__(16) uint32_t s_scratch[kQW][kFwhtRows];
+  __shared__ uint64_t s_neg[G / 64];
   __shared__ __align__(16) uint16_t s_off[align16((BK::kCells + 1) * 2) / 2];
   __shared__ __align__(16) uint16_t s_list[kCap];
   __shared__ double s_r2[kQW];
@@ -457,7 +565,19 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
 
   const int tid = int(threadIdx.x);
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // The index's offsets and lists straight into LDS, and its header, all
+  // requested before anything else is done (an index holds these regions
+  // whatever its header says): read after the header's checks, field by field
+  // and through registers, they took a dozen memory round trips per block.
+  u32x4 hdr[4] = {};
+  if (index != nullptr) {
+    copy_to_lds<kQW>(index + kL.offsets, s_off, int(sizeof(s_off)), wave, lane);
+    copy_to_lds<kQW>(index + kL.list, s_list, int(sizeof(s_list)), wave, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) hdr[q] = reinterpret_cast<const u32x4*>(index)[q];
+  }
 
   // the grid, its largest squared norm and (with an index) its hash
   double r2 = 0.0;
@@ -491,56 +611,72 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
   }
   const double shift = search_shift(r2, G);
 
-  // the index, when it was built from this grid and fits
-  bool pruned = false;
-  if (index != nullptr) {
-    const IndexHeader* hd = reinterpret_cast<const IndexHeader*>(index);
-    pruned = hd->magic == kIndexMagic && hd->p == uint32_t(P) && hd->n == uint32_t(n) &&
-             hd->nb == uint32_t(BK::kNB) && hd->usable == 1u && hd->total <= uint32_t(kCap) &&
-             hd->hash == hsh && hd->half_side == kBR && hd->margin >= ldexp(shift, -30);
-    if (pruned) {
-      const int total = int(hd->total);
-      const u32x4* so = reinterpret_cast<const u32x4*>(index + kL.offsets);
-      u32x4* d_off = reinterpret_cast<u32x4*>(s_off);
-      for (int i = tid; i < int(sizeof(s_off) / 16); i += 64 * kQW) d_off[i] = so[i];
-      const u32x4* sl = reinterpret_cast<const u32x4*>(index + kL.list);
-      u32x4* d_list = reinterpret_cast<u32x4*>(s_list);
-      for (int i = tid; i < (total + 7) / 8; i += 64 * kQW) d_list[i] = sl[i];
-    }
-  }
+  // the index counts when it was built from this grid and fits
+  static_assert(sizeof(hdr) == sizeof(IndexHeader), "header");
+  const IndexHeader hd = __builtin_bit_cast(IndexHeader, hdr);
+  const bool pruned =
+      index != nullptr &&
+      ((hd.magic == kIndexMagic) & (hd.p == uint32_t(P)) & (hd.n == uint32_t(n)) &
+       (hd.nb == uint32_t(BK::kNB)) & (hd.usable == 1u) & (hd.total <= uint32_t(kCap)) &
+       (hd.hash == hsh) & (hd.half_side == kBR) & (hd.margin >= ldexp(shift, -30)));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the copies into LDS
 
-  uint64_t neg = 0;
-#pragma unroll
-  for (int i = 0; i < E; ++i) neg |= uint64_t(rht_sign_negative(seed, uint32_t(lane * E + i))) << i;
+  block_signs<G / 64, kQW>(seed, s_neg, wave, lane);  // (its barrier also covers the index)
+  uint32_t flips[RawGroup<E, InT>::kMasks];
+  const int in_group = lane * E % G;  // the lane's first weight inside its group
+  RawGroup<E, InT>::masks(s_neg[in_group / 64] >> (in_group % 64), flips);
 
-  const int64_t groups_per_row = in / G;
-  const int64_t total = rows * groups_per_row;
   const double inv_sqrt_g = 1.0 / sqrt(double(G));
   const uint32_t index_mask = kIndexMask;
-  __syncthreads();
+  CodeT* const s_codes = reinterpret_cast<CodeT*>(s_scratch[wave]);
+  // place, in the wave's 1024 weights, of the code of the lane's first vector
+  // after the rotation (and, for P = 2, the exchange below)
+  const int code0 = P == 2 ? (fwht_rows_lane<G>(lane & ~1) >> 1) | (lane & 1) << 3
+                           : fwht_rows_lane<G>(lane);
 
-  for (int64_t grp = int64_t(blockIdx.x) * kQW + wave; grp < total;
-       grp += int64_t(gridDim.x) * kQW) {
-    const int64_t row = grp / groups_per_row;
-    const int64_t gi = grp - row * groups_per_row;
-
+  // groups, their scales and their codes all lie back to back; the next turn's
+  // weights are requested one turn ahead. Past the last group a lane has zeros.
+  const int64_t segs = (groups + kSegGroups - 1) / kSegGroups;
+  const int64_t step = int64_t(gridDim.x) * kQW;
+  int64_t seg = int64_t(blockIdx.x) * kQW + wave;
+  RawGroup<E, InT> raw = {};
+  auto request = [&](int64_t sg) {
+    if (kSegGroups == 1 || sg * kSegGroups + lane / kGroupLanes < groups)
+      raw.load(w + sg * kSeg + lane * E);
+    else
+      raw = RawGroup<E, InT>{};
+  };
+  if (seg < segs) request(seg);
+  for (; seg < segs; seg += step) {
     double v[E];
-    load_group<E, InT>(w + row * in + gi * G + lane * E, v);
+    raw.flip(flips);  // sigma
+    raw.expand(v);
+    if (seg + step < segs) request(seg + step);
 
     double ss = 0.0;
 #pragma unroll
     for (int i = 0; i < E; ++i) ss += v[i] * v[i];
-    ss = wave_sum(ss, lane);
+    ss = lanes_sum<kGroupLanes>(ss, lane);  // over the group's lanes
     const double s = sqrt(ss);
 
     // w / s as w * (1 / s): within an ulp of the quotient
     const double inv_s = s > 0.0 ? 1.0 / s : 0.0;
 #pragma unroll
-    for (int i = 0; i < E; ++i) {
-      const double u = v[i] * inv_s;
-      v[i] = ((neg >> i) & 1) ? -u : u;
+    for (int i = 0; i < E; ++i) v[i] *= inv_s;
+    fwht_rows<G>(v, s_scratch[wave], lane);
+    if constexpr (P == 2) {
+      // a vector's two coordinates are in lanes l and l ^ 1: exchange lane bit
+      // 0 with register bit 0, so that lane l has the vector of registers 2 q
+      // (even l) or 2 q + 1 (odd l) in v[2 q], v[2 q + 1]
+      const bool odd = lane & 1;
+#pragma unroll
+      for (int q = 0; q < E / 2; ++q) {
+        const double x = v[2 * q], y = v[2 * q + 1];
+        const double got = lane_xor<1>(odd ? x : y, lane);
+        v[2 * q] = odd ? got : x;
+        v[2 * q + 1] = odd ? y : got;
+      }
     }
-    fwht_wave<E>(v, lane, G);
 
     // search value of point k for vector j, folded into best[j]
     double best[kVecPerLane];
@@ -560,21 +696,20 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
       int steps = 0;
 #pragma unroll
       for (int j = 0; j < kVecPerLane; ++j) {
+        bool in_box = fabs(v[j * P]) < kBR;  // (false for NaN)
         int b = bucket_axis(v[j * P], BK::kNB);
         if constexpr (P == 2) {
-          const int by = bucket_axis(v[j * P + 1], BK::kNB);
-          b = (b < 0 || by < 0) ? -1 : by * BK::kNB + b;
+          in_box = in_box && fabs(v[j * P + 1]) < kBR;
+          b += bucket_axis(v[j * P + 1], BK::kNB) * BK::kNB;
         }
-        at[j] = 0;
-        last[j] = 0;
-        if (b >= 0) {
-          const int o = s_off[b], e = s_off[b + 1];
-          at[j] = o;
-          last[j] = e - o - 1;
-          steps = max(steps, e - o);
-          full &= ~(uint64_t(1) << j);
-        }
+        b = in_box ? b : 0;  // (its list is walked all the same)
+        const int o = s_off[b], e = s_off[b + 1];
+        at[j] = o;
+        last[j] = e - o - 1;
+        if (in_box) full &= ~(uint64_t(1) << j);
       }
+#pragma unroll
+      for (int j = 0; j < kVecPerLane; ++j) steps = max(steps, last[j] + 1);
       for (int i = 0; i < steps; ++i) {
         // all reads of the step first (the folds below are opaque to the
         // scheduler, so reads placed between them would wait one by one)
@@ -588,29 +723,80 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
         for (int j = 0; j < kVecPerLane; ++j) fold(j, k[j], q[j]);
       }
     }
-    if (full != 0) {
+    // Vectors that scan every point. Without an index that is every vector:
+    // each lane scans for its own, a point read once for all of them. With one
+    // it is the few per thousand outside the buckets, one after the
+    // other over the whole wave, lane l taking points l, l + 64, ...: a scan by
+    // the vector's own lane is a chain of n LDS reads that the rest of the wave
+    // waits for (14336 x 4096, 256 points: 247 us against 189; 4096 x 4096, 1024
+    // points, g = 256: 268 against 110).
+    if (!pruned) {
+#pragma unroll 4
+      for (int k = 0; k < n; ++k) {
+        const GridPt q = s_grid[k];
+#pragma unroll
+        for (int j = 0; j < kVecPerLane; ++j) fold(j, k, q);
+      }
+    } else if (kN <= 16) {  // (a scan is short)
 #pragma unroll
       for (int j = 0; j < kVecPerLane; ++j)
         if ((full >> j) & 1)
           for (int k = 0; k < n; ++k) fold(j, k, s_grid[k]);
+    } else if (__any(full != 0)) {
+#pragma unroll
+      for (int j = 0; j < kVecPerLane; ++j) {
+        uint64_t todo = __ballot((full >> j) & 1);
+        while (todo != 0) {  // uniform
+          const int src = __builtin_ctzll(todo);
+          todo &= todo - 1;
+          double x[P];
+#pragma unroll
+          for (int t = 0; t < P; ++t) x[t] = readlane_f64(v[j * P + t], src);
+          double b = INFINITY;
+          for (int k = lane; k < n; k += 64) {
+            const GridPt q = s_grid[k];
+            double c = fma(-x[0], double(q.x[0]), search_const<P>(q, shift));
+            if constexpr (P == 2) c = fma(-x[P - 1], double(q.x[1]), c);
+            // (the index differs by lane here)
+            const uint64_t u = __builtin_bit_cast(uint64_t, c);
+            b = min_f64(b, __builtin_bit_cast(
+                               double, (u & ~uint64_t(kIndexMask)) | uint64_t(uint32_t(k))));
+          }
+          b = wave_min(b, lane);
+          if (lane == src) best[j] = b;
+        }
+      }
     }
 
 #pragma unroll
     for (int j = 0; j < kVecPerLane; ++j)
-      s_codes[wave][lane * kVecPerLane + j] =
+      s_codes[code0 + (P == 2 ? fwht_rows_reg<G>(2 * j) >> 1 : fwht_rows_reg<G>(j))] =
           CodeT(__builtin_bit_cast(uint64_t, best[j]) & kIndexMask);
     wave_sync();
-    uint32_t* dst = reinterpret_cast<uint32_t*>(codes + row * row_bytes +
-                                                gi * (int64_t(kCodesPerGroup) * BITS / 8));
-    for (int wi = lane; wi < kWordsPerGroup; wi += 64) {
+    const int64_t grp0 = seg * kSegGroups;
+    const int here = groups - grp0 < kSegGroups ? int(groups - grp0) : kSegGroups;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(codes) + grp0 * kWordsPerGroup;
+    for (int wi = lane; wi < here * kWordsPerGroup; wi += 64) {
+      if constexpr (BITS == 8) {  // packed as they are
+        dst[wi] = reinterpret_cast<const uint32_t*>(s_codes)[wi];
+        continue;
+      }
+      if constexpr (BITS == 4) {  // eight bytes to eight nibbles
+        const uint2 b = reinterpret_cast<const uint2*>(s_codes)[wi];
+        const uint32_t x = (b.x | b.x >> 4) & 0x00ff00ffu, y = (b.y | b.y >> 4) & 0x00ff00ffu;
+        dst[wi] = ((x | x >> 8) & 0xffffu) | (y | y >> 8) << 16;
+        continue;
+      }
       const int bit0 = wi * 32;
       int c = bit0 / BITS;
-      uint32_t word = uint32_t(s_codes[wave][c]) >> (bit0 - c * BITS);
-      for (++c; c * BITS < bit0 + 32 && c < kCodesPerGroup; ++c)
-        word |= uint32_t(s_codes[wave][c]) << (c * BITS - bit0);
+      uint32_t word = uint32_t(s_codes[c]) >> (bit0 - c * BITS);
+      for (++c; c * BITS < bit0 + 32 && c < kSegCodes; ++c)
+        word |= uint32_t(s_codes[c]) << (c * BITS - bit0);
       dst[wi] = word;
     }
-    if (lane == 0) scales[row * groups_per_row + gi] = f64_to_f16_rne(s * inv_sqrt_g);
+    const int lg = lane / kGroupLanes;
+    if (lane % kGroupLanes == 0 && lg < here)
+      scales[grp0 + lg] = f64_to_f16_rne(s * inv_sqrt_g);
     wave_sync();
   }
 }
@@ -741,17 +927,6 @@ __global__ __launch_bounds__(64 * kWaves) void quantize_scan_kernel(
 }
 
 
-// Sign bits of the group's elements (bit j of word q: element 64 q + j is
-// negated), computed by all the waves of the block. Ends with a barrier.
-template <int E, int kNW>
-__device__ inline void block_signs(uint64_t seed, uint64_t (&s_neg)[E], int wave, int lane) {
-  for (int q = wave; q < E; q += kNW) {
-    const uint64_t bits = __ballot(rht_sign_negative(seed, uint32_t(64 * q + lane)));
-    if (lane == 0) s_neg[q] = bits;
-  }
-  __syncthreads();
-}
-
 // Little-endian dword at any byte address.
 struct __attribute__((packed, aligned(1))) AnyU32 {
   uint32_t v;
@@ -766,13 +941,13 @@ struct __attribute__((packed, aligned(1))) AnyU32 {
 // read as whole dwords into the wave's LDS and the grid is kept in LDS: read
 // from memory per code (three bytes and a gather each), the vector memory
 // unit was the bound (4096 x 14336 bf16, 6-bit codes: 152 us; 100 us with both
-// in LDS, 70 us with the rotation through LDS for g = 1024 and the next group's
-// loads issued ahead). Now bound by the vector ALU: about 480 instructions per
+// in LDS, 64 us with the rotation through LDS for g = 1024 and the next group's
+// loads issued ahead). Now bound by the vector ALU: about 450 instructions per
 // 1024 weights and lane, two thirds of them fp64.
 template <int E, int P, int BITS, typename InT>
 __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
     const InT* __restrict__ w, int64_t rows, int64_t in, uint64_t seed,
-    const float* __restrict__ grid, const uint8_t* __restrict__ codes, int64_t row_bytes,
+    const float* __restrict__ grid, const uint8_t* __restrict__ codes,
     const uint16_t* __restrict__ scales, double* __restrict__ out) {
   constexpr int G = 64 * E;
   constexpr int V = E / P;                      // codes per lane
@@ -787,7 +962,7 @@ __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
   using GridT = typename std::conditional<((P << BITS) <= 512), double, float>::type;
   __shared__ GridT s_grid[P << BITS];
   __shared__ uint32_t s_words[kWaves][kWords + 2];  // a lane's window may end past its codes
-  __shared__ __align__(16) double s_rot[kWaves][kRows ? kFwht1024Rows : 2];
+  __shared__ __align__(16) uint32_t s_rot[kWaves][kRows ? kFwhtRows : 4];
   __shared__ __align__(16) uint16_t s_code[kWaves][kRows ? G / P : 8];
   __shared__ uint64_t s_neg[E];
   const int lane = int(threadIdx.x) & 63;
@@ -795,23 +970,21 @@ __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
   for (int k = int(threadIdx.x); k < P << BITS; k += 64 * kWaves) s_grid[k] = GridT(grid[k]);
   if (lane < 2) s_words[wave][kWords + lane] = 0;
   block_signs<E, kWaves>(seed, s_neg, wave, lane);
-  const uint64_t neg = s_neg[lane * E / 64] >> (lane * E % 64);
-  const int64_t groups_per_row = in / G;
-  const int64_t total = rows * groups_per_row;
+  uint32_t flips[RawGroup<E, InT>::kMasks];
+  RawGroup<E, InT>::masks(s_neg[lane * E / 64] >> (lane * E % 64), flips);
+  // groups, their scales and their codes all lie back to back
+  const int64_t total = rows * (in / G);
   const double inv_sqrt_g = 1.0 / sqrt(double(G));
   const int bit0 = lane * V * BITS;
   const uint32_t* mine = &s_words[wave][bit0 >> 5];
-  const int n0 = fwht1024_rows_lane(lane);
+  const int n0 = fwht_rows_lane<1024>(lane);
   // what a group needs from memory, requested one group ahead
   RawGroup<E, InT> raw;
   uint32_t cd[(kWords + 63) / 64];
   uint16_t sc = 0;
   auto request = [&](int64_t grp) {
-    const int64_t row = grp / groups_per_row;
-    const int64_t gi = grp - row * groups_per_row;
-    raw.load(w + row * in + gi * G + lane * E);
-    const AnyU32* cw =
-        reinterpret_cast<const AnyU32*>(codes + row * row_bytes + gi * int64_t(kWords * 4));
+    raw.load(w + grp * G + lane * E);
+    const AnyU32* cw = reinterpret_cast<const AnyU32*>(codes) + grp * kWords;
 #pragma unroll
     for (int q = 0; q < (kWords + 63) / 64; ++q)
       cd[q] = 64 * q + lane < kWords ? cw[64 * q + lane].v : 0u;
@@ -824,6 +997,7 @@ __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
   for (; grp < total; grp += step) {
     const double sh = double(__builtin_bit_cast(_Float16, sc));
     double v[E];
+    raw.flip(flips);  // sigma
     raw.expand(v);
     wave_sync();  // the last group's words have been read
 #pragma unroll
@@ -855,15 +1029,12 @@ __global__ __launch_bounds__(64 * kWaves) void layer_error_kernel(
 #pragma unroll
     for (int i = 0; i < E; ++i) ss += v[i] * v[i];
     ss = wave_sum(ss, lane);
-#pragma unroll
-    for (int i = 0; i < E; ++i)
-      if ((neg >> i) & 1) v[i] = -v[i];
     double e = 0.0;
     if constexpr (kRows) {
-      fwht1024_rows(v, s_rot[wave], lane);
+      fwht_rows<1024>(v, s_rot[wave], lane);
 #pragma unroll
       for (int r = 0; r < E; ++r) {
-        const int n = n0 + fwht1024_rows_reg(r);
+        const int n = n0 + fwht_rows_reg<1024>(r);
         const uint32_t c = s_code[wave][n / P];
         // in units of 1 / sqrt(g) = 1 / 32: exact, one multiply less
         const double d = fma(-32.0 * sh, double(s_grid[c * P + (n & (P - 1))]), v[r]);
@@ -931,8 +1102,8 @@ __global__ __launch_bounds__(1024) void layer_t2_kernel(const double* __restrict
 
 template <int P, int BITS, typename InT>
 hipError_t launch_error_p(const InT* w, int64_t out_rows, int64_t in, const float* grid, int g,
-                          uint64_t seed, const uint8_t* codes, int64_t row_bytes,
-                          const uint16_t* scales, double* err, hipStream_t stream) {
+                          uint64_t seed, const uint8_t* codes, const uint16_t* scales,
+                          double* err, hipStream_t stream) {
   const int64_t total = out_rows * (in / g);
   // eight blocks per compute unit: a block reads the grid and forms the signs
   // once, then its waves take groups in turn
@@ -943,7 +1114,7 @@ hipError_t launch_error_p(const InT* w, int64_t out_rows, int64_t in, const floa
   case GV:                                                                                   \
     if constexpr ((GV / 64) % P == 0) {                                                      \
       hipLaunchKernelGGL((layer_error_kernel<GV / 64, P, BITS, InT>), grid_dim, block, 0,    \
-                         stream, w, out_rows, in, seed, grid, codes, row_bytes, scales, err); \
+                         stream, w, out_rows, in, seed, grid, codes, scales, err);           \
       return hipGetLastError();                                                              \
     }                                                                                        \
     break;
@@ -964,12 +1135,10 @@ hipError_t launch_error_p(const InT* w, int64_t out_rows, int64_t in, const floa
 template <typename InT>
 hipError_t launch_error_typed(const InT* w, int64_t out, int64_t in, const float* grid, int p,
                               int bits, int g, uint64_t seed, const uint8_t* codes,
-                              int64_t row_bytes, const uint16_t* scales, double* err,
-                              hipStream_t stream) {
+                              const uint16_t* scales, double* err, hipStream_t stream) {
 #define HIGGS_E_FORMAT(PV, BV)                                                              \
   if (p == PV && bits == BV)                                                                \
-    return launch_error_p<PV, BV>(w, out, in, grid, g, seed, codes, row_bytes, scales, err, \
-                                  stream);
+    return launch_error_p<PV, BV>(w, out, in, grid, g, seed, codes, scales, err, stream);
   HIGGS_E_FORMAT(1, 4)
   HIGGS_E_FORMAT(1, 8)
   HIGGS_E_FORMAT(2, 6)
@@ -984,23 +1153,22 @@ hipError_t launch_bits(const InT* w, int64_t out, int64_t in, const float* grid,
                        const uint8_t* index, int g, uint64_t seed, uint8_t* codes,
                        int64_t row_bytes, uint16_t* scales, hipStream_t stream) {
   const int64_t total = out * (in / g);
-  // a block loads the grid and the index into LDS once, then its waves
-  // take groups in turn. The 1024-point grid's index fills a compute unit's
-  // LDS, and scalar grids run 2 waves per SIMD (registers): there one block
-  // per compute unit with 12 or 8 waves; else blocks of 4 waves, up to 2048
-  // (measured faster there)
+  // a block loads the grid and the index into LDS once, then its waves take
+  // 1024 weights at a time. The 256- and 1024-point grids' indexes nearly fill
+  // a compute unit's LDS, and scalar grids run 2 waves per SIMD (registers):
+  // there one block per compute unit with 12 or 8 waves; else blocks of 4
+  // waves, up to 2048 (measured faster there)
   constexpr int kQW = P == 1 ? 8 : (BITS >= 8 ? 12 : 4);
   constexpr int64_t kMaxBlocks = kQW == 4 ? 2048 : 256;
-  const int64_t blocks =
-      std::max<int64_t>(1, std::min<int64_t>((total + kQW - 1) / kQW, kMaxBlocks));
+  const int64_t segs = (total + std::max(1, 1024 / g) - 1) / std::max(1, 1024 / g);
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((segs + kQW - 1) / kQW, kMaxBlocks));
   const dim3 grid_dim{unsigned(blocks)}, block{64 * kQW}, scan_block{64 * kWaves};
   switch (g) {
 #define HIGGS_Q_CASE(GV)                                                                     \
   case GV:                                                                                   \
-    if constexpr ((GV / 64) % P == 0) {                                                      \
-      hipLaunchKernelGGL((quantize_kernel<GV / 64, P, BITS, kQW, InT>), grid_dim, block, 0,  \
-                         stream, w, out, in, seed, grid, n, index, codes, row_bytes,         \
-                         scales);                                                            \
+    if constexpr (GV >= 64 * P) {                                                            \
+      hipLaunchKernelGGL((quantize_kernel<GV, P, BITS, kQW, InT>), grid_dim, block, 0,       \
+                         stream, w, total, seed, grid, n, index, codes, scales);             \
       return hipGetLastError();                                                              \
     }                                                                                        \
     break;
@@ -1079,21 +1247,18 @@ __global__ __launch_bounds__(64 * kWaves) void gptq_prepare_kernel(
     double* __restrict__ norms, uint16_t* __restrict__ scales) {
   constexpr int G = 64 * E;
   constexpr bool kRows = E == 16;  // g = 1024: rotated through LDS
-  __shared__ __align__(16) double s_rot[kWaves][kRows ? kFwht1024Rows : 2];
+  __shared__ __align__(16) uint32_t s_rot[kWaves][kRows ? kFwhtRows : 4];
   __shared__ uint64_t s_neg[E];
   const int lane = int(threadIdx.x) & 63;
   const int wave = int(threadIdx.x) >> 6;
   block_signs<E, kWaves>(seed, s_neg, wave, lane);
   const uint64_t neg = s_neg[lane * E / 64] >> (lane * E % 64);
-  const int64_t groups_per_row = in / G;
-  const int64_t total = rows * groups_per_row;
+  const int64_t total = rows * (in / G);  // groups lie back to back
   const double inv_sqrt_g = 1.0 / sqrt(double(G));
   for (int64_t grp = int64_t(blockIdx.x) * kWaves + wave; grp < total;
        grp += int64_t(gridDim.x) * kWaves) {
-    const int64_t row = grp / groups_per_row;
-    const int64_t gi = grp - row * groups_per_row;
     double v[E];
-    load_group<E, InT>(w + row * in + gi * G + lane * E, v);
+    load_group<E, InT>(w + grp * G + lane * E, v);
     double ss = 0.0;
 #pragma unroll
     for (int i = 0; i < E; ++i) ss += v[i] * v[i];
@@ -1102,12 +1267,12 @@ __global__ __launch_bounds__(64 * kWaves) void gptq_prepare_kernel(
 #pragma unroll
     for (int i = 0; i < E; ++i)
       if ((neg >> i) & 1) v[i] = -v[i];
-    double* dst = wr + row * in + gi * G;
+    double* dst = wr + grp * G;
     if constexpr (kRows) {
-      fwht1024_rows(v, s_rot[wave], lane);
+      fwht_rows<1024>(v, s_rot[wave], lane);
 #pragma unroll
       for (int i = 0; i < E; ++i)
-        dst[fwht1024_rows_lane(lane) + fwht1024_rows_reg(i)] = v[i] * inv_sqrt_g;
+        dst[fwht_rows_lane<1024>(lane) + fwht_rows_reg<1024>(i)] = v[i] * inv_sqrt_g;
     } else {
       fwht_wave<E>(v, lane, G);
 #pragma unroll
@@ -1118,13 +1283,6 @@ __global__ __launch_bounds__(64 * kWaves) void gptq_prepare_kernel(
       scales[grp] = f64_to_f16_rne(sn * inv_sqrt_g);
     }
   }
-}
-
-// min(a, b) of values that are not NaN (fmin would first quieten both).
-__device__ inline double min_f64(double a, double b) {
-  double r;
-  __asm__("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
 }
 
 // The value of lane L of this lane's row of 16 lanes.
@@ -1404,13 +1562,12 @@ hipError_t launch_layer_error(const void* w, higgs_dtype dtype, int64_t out, int
                               int p, int n, int g, uint64_t seed, double* err, double* t2,
                               hipStream_t stream) {
   const int bits = code_bits(p, n);
-  const int64_t row_bytes = in / p * bits / 8;
   const hipError_t st =
       dtype == HIGGS_F32
           ? launch_error_typed(static_cast<const float*>(w), out, in, grid, p, bits, g, seed,
-                               codes, row_bytes, scales, err, stream)
+                               codes, scales, err, stream)
           : launch_error_typed(static_cast<const uint16_t*>(w), out, in, grid, p, bits, g, seed,
-                               codes, row_bytes, scales, err, stream);
+                               codes, scales, err, stream);
   if (st != hipSuccess || t2 == nullptr) return st;
   hipLaunchKernelGGL(layer_t2_kernel, dim3(1), dim3(1024), 0, stream, err, out * (in / g), t2);
   return hipGetLastError();

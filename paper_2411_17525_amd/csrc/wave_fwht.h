@@ -304,56 +304,88 @@ __device__ inline void lane_swap(double& a, double& b) {
   b = __builtin_bit_cast(double, uint64_t(y0) | (uint64_t(y1) << 32));
 }
 
-// LDS doubles of fwht1024_rows's scratch (one per wave, 16-byte aligned).
-constexpr int kFwht1024Rows = 4 * 304;
+// LDS dwords of fwht_rows's scratch (one per wave, 16-byte aligned).
+constexpr int kFwhtRows = 4 * 272;
 
-// Unnormalised FWHT of 1024 fp64 values held 16 per lane (lane l: elements
-// 16 l .. 16 l + 15), the stages in the order of the element bits and each
-// (a + b, a - b), as in fwht_wave, so the values are the same bit for bit; they
-// come back in other places. Element bits 0-3 in the lane; bits 4-7 in the
-// lane after the 16 lanes of a row exchange their values through LDS; bits 8
-// and 9 by exchanging lane bits 4 and 5 with register bits 3 and 2, two
-// elements per exchange (one swap and one add per element, where the
-// cross-lane form moves both halves of every value to its partner). About 200
-// instructions instead of 500. On return v[r] of lane l is element
-// fwht1024_rows_lane(l) + fwht1024_rows_reg(r).
-__device__ inline void fwht1024_rows(double (&v)[16], double* w, int lane) {
-  typedef double f64x2_v __attribute__((ext_vector_type(2)));
+// Unnormalised FWHT of the 1024 / G blocks of G (64 .. 1024) in 1024 fp64
+// values held 16 per lane (lane l: elements 16 l .. 16 l + 15), the stages in
+// the order of the element bits and each (a + b, a - b), as in fwht_wave, so
+// the values are the same bit for bit; they come back in other places. Element
+// bits 0-3 in the lane; bits 4-7 in the lane after the 16 lanes of a row
+// exchange their values through LDS (the low dwords, then the high ones, so
+// that the scratch stays small; a lane's quads are permuted by its high bits,
+// so that writes and reads hit distinct banks); bits 8 and 9 by exchanging lane
+// bits 4 and 5 with register bits 3 and 2, two elements per exchange (one swap
+// and one add per element, where the cross-lane form moves both halves of every
+// value to its partner). About 250 instructions for G = 1024 instead of 500. On
+// return v[r] of lane l is element fwht_rows_lane<G>(l) + fwht_rows_reg<G>(r).
+template <int G>
+__device__ inline void fwht_rows(double (&v)[16], uint32_t* w, int lane) {
+  static_assert(G == 64 || G == 128 || G == 256 || G == 512 || G == 1024, "block size");
+  typedef uint32_t u32x4_v __attribute__((ext_vector_type(4)));
   wave_lds_sync();  // this wave's earlier accesses of w come first
   fwht_in_lane<16>(v);
-  double* row = w + 304 * (lane >> 4);
-  {
-    f64x2_v* p = reinterpret_cast<f64x2_v*>(row + 18 * (lane & 15));
+  uint32_t* row = w + 272 * (lane >> 4);
+  const int c = lane & 15, ch = c >> 2;
+  uint32_t half[2][16];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) p[k] = f64x2_v{v[2 * k], v[2 * k + 1]};
+  for (int h = 0; h < 2; ++h) {
+    uint32_t d[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      d[i] = uint32_t(__builtin_bit_cast(uint64_t, v[i]) >> (32 * h));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<u32x4_v*>(row + 16 * c + 4 * (q ^ ch)) =
+          u32x4_v{d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]};
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) half[h][i] = row[16 * i + 4 * (ch ^ (i >> 2)) + (c & 3)];
+    wave_lds_sync();
   }
-  wave_lds_sync();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = row[18 * i + (lane & 15)];
-  fwht_in_lane<16>(v);
+  for (int i = 0; i < 16; ++i)
+    v[i] = __builtin_bit_cast(double, uint64_t(half[0][i]) | (uint64_t(half[1][i]) << 32));
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    lane_swap<16>(v[i], v[i + 8]);
-    const double x = v[i], y = v[i + 8];
-    v[i] = x + y;
-    v[i + 8] = x - y;
-  }
+  for (int h = 1; h < 16 && 16 * h < G; h <<= 1)
 #pragma unroll
-  for (int h = 0; h < 16; h += 8)
+    for (int i = 0; i < 16; ++i)
+      if ((i & h) == 0) {
+        const double x = v[i], y = v[i + h];
+        v[i] = x + y;
+        v[i + h] = x - y;
+      }
+  if constexpr (G >= 512) {
 #pragma unroll
-    for (int i = h; i < h + 4; ++i) {
-      lane_swap<32>(v[i], v[i + 4]);
-      const double x = v[i], y = v[i + 4];
+    for (int i = 0; i < 8; ++i) {
+      lane_swap<16>(v[i], v[i + 8]);
+      const double x = v[i], y = v[i + 8];
       v[i] = x + y;
-      v[i + 4] = x - y;
+      v[i + 8] = x - y;
     }
+  }
+  if constexpr (G == 1024) {
+#pragma unroll
+    for (int h = 0; h < 16; h += 8)
+#pragma unroll
+      for (int i = h; i < h + 4; ++i) {
+        lane_swap<32>(v[i], v[i + 4]);
+        const double x = v[i], y = v[i + 4];
+        v[i] = x + y;
+        v[i + 4] = x - y;
+      }
+  }
 }
 // (its lane part and its register part; they share no bits)
-__device__ inline constexpr int fwht1024_rows_lane(int lane) {
-  return (lane & 15) | ((lane >> 5) & 1) << 6 | ((lane >> 4) & 1) << 7;
+template <int G>
+__device__ inline constexpr int fwht_rows_lane(int lane) {
+  return (lane & 15) | ((lane >> 5) & 1) << (G == 1024 ? 6 : 9) |
+         ((lane >> 4) & 1) << (G >= 512 ? 7 : 8);
 }
-__device__ inline constexpr int fwht1024_rows_reg(int r) {
-  return (r & 3) << 4 | ((r >> 3) & 1) << 8 | ((r >> 2) & 1) << 9;
+template <int G>
+__device__ inline constexpr int fwht_rows_reg(int r) {
+  return (r & 3) << 4 | ((r >> 3) & 1) << (G >= 512 ? 8 : 7) |
+         ((r >> 2) & 1) << (G == 1024 ? 9 : 6);
 }
 
 }  // namespace higgs
