@@ -164,7 +164,7 @@ hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint6
 // The matrix-core product for prompt-sized batches (qgemm_wide.hip), same
 // arguments; launch_qgemm[_group] and the workspace sizes above go to it when
 // use_qgemm_wide says so.
-bool use_qgemm_wide(int64_t batch, int64_t in);
+bool use_qgemm_wide(int64_t batch, int64_t in, int p, int n, int g);
 int64_t qgemm_wide_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
                                    int p, int n, int g);
 hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64_t* seeds,

@@ -1188,14 +1188,14 @@ int pair_bits(int p, int n) { return p == 1 ? 2 * code_bits(p, n) : code_bits(p,
 }  // namespace
 
 int64_t qgemm_workspace_bytes(int64_t batch, int64_t out, int64_t in, int p, int n, int g) {
-  if (use_qgemm_wide(batch, in)) return qgemm_wide_workspace_bytes(1, batch, &out, in, p, n, g);
+  if (use_qgemm_wide(batch, in, p, n, g)) return qgemm_wide_workspace_bytes(1, batch, &out, in, p, n, g);
   return layout(batch, &out, 1, 1, in, g, pair_bits(p, n)).total;
 }
 
 int64_t qgemm_group_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
                                     int p, int n, int g) {
   if (layers < 1 || layers > kMaxGroup) return -1;
-  if (use_qgemm_wide(batch, in)) return qgemm_wide_workspace_bytes(layers, batch, outs, in, p, n, g);
+  if (use_qgemm_wide(batch, in, p, n, g)) return qgemm_wide_workspace_bytes(layers, batch, outs, in, p, n, g);
   return layout(batch, outs, layers, layers, in, g, pair_bits(p, n)).total;
 }
 
@@ -1206,7 +1206,7 @@ hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint6
                               void* workspace, hipStream_t stream) {
   if (!qgemm_format(p, n) || layers < 1 || layers > kMaxGroup)
     return hipErrorInvalidValue;
-  if (use_qgemm_wide(batch, in))
+  if (use_qgemm_wide(batch, in, p, n, g))
     return launch_qgemm_wide(x, x_kind, layers, seeds, batch, codes, scales, grid, p, n, g, outs,
                              in, y, workspace, stream);
   const int bits = pair_bits(p, n);

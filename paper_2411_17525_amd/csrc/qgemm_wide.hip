@@ -1,7 +1,7 @@
 // Lookup-table GEMM for HIGGS layers at prompt-sized batches (more than 64
-// rows) on the matrix cores: the product of qgemm.hip,
+// rows; fewer for small groups, use_qgemm_wide) on the matrix cores: the product of qgemm.hip,
 //   y[b][o] = sum_i scale[o][i] * sum_j < G[code(o,i,j)], x_rot[b, ig+jp : ig+(j+1)p] >,
-// in blocks of 128 or 256 rows x 128 or 256 batch columns instead of one
+// in blocks of 128 or 256 rows x 64 to 256 batch columns instead of one
 // launch per 64 columns, so that a code is decoded once per 256 columns and the
 // products of a block outweigh what it reads. Measured on MI355X against the
 // 64-column launches: two 14336 x 4096 layers at 2048 rows 987 -> 472 us
@@ -227,7 +227,7 @@ __device__ inline void wait_loads() {
 // G64: groups of 64 weights, which end at every stage; larger groups end at
 // even stages only (K-ranges start at multiples of 128, and such rows have an
 // even number of stages).
-template <int BITS, int NB, int KG, bool G64>
+template <int BITS, int NB, int CW, int KG, bool G64>
 __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   using F = GFmt<BITS>;
   constexpr int kW = F::kWords;
@@ -239,10 +239,10 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   constexpr int kEntries = BITS == 16 ? 256 : 1 << BITS;
   constexpr int kEntryU4 = (1 << F::kStride) / 16;
   constexpr int kLutU4 = kEntries * kEntryU4;
-  constexpr int kCols = 64 * NB;
-  constexpr int kRows = 256 / KG;
+  constexpr int kCols = 32 * NB * CW;       // CW waves side by side
+  constexpr int kRows = 64 * kWaves / (CW * KG);
   constexpr int kGWaves = kWaves / KG;  // waves of a K-group
-  constexpr int kDma = NB * KG;         // activation loads per wave and stage
+  constexpr int kDma = kCols / 8 / kGWaves;  // activation loads per wave and stage
   constexpr bool kTotals = NB == 2;
   constexpr int kStageBytes = kCols * 128;  // 64 weights of kCols batch rows
   constexpr bool kPair = BITS != 16;        // codes requested for two stages at a time
@@ -297,16 +297,14 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   const int split = wt - rtile * splits;
   const int row0 = rtile * kRows + rw * 64;  // the wave's first row
   const int col0 = ctile * kCols;                             // the block's first batch row
-  // the K-group's part of the block's K-range: with two, group 0 takes the
-  // first half (rounded up to 128 weights), so it has at least as many stages
+  // the K-group's part of the block's K-range: with several, equal parts
+  // (rounded up to 128 weights) in turn, so group 0 has the most stages
   int kbeg = split * kps;
   int kend = min(in, kbeg + kps);
-  const int khalf = KG == 1 ? kend - kbeg : ((kend - kbeg + 255) / 256) * 128;
-  const int nmax = khalf >> 6;
-  if (kgrp == 0)
-    kend = kbeg + khalf;
-  else
-    kbeg += khalf;
+  const int kpart = KG == 1 ? kend - kbeg : (kend - kbeg + 128 * KG - 1) / (128 * KG) * 128;
+  const int nmax = kpart >> 6;
+  kbeg = min(kend, kbeg + kgrp * kpart);
+  kend = min(kend, kbeg + kpart);
   const int nst = (kend - kbeg) >> 6;  // stages (K-blocks of 64 weights)
   const int last = max(nst - 1, 0);    // stage that requests past the end repeat
   dst += int64_t(split) * batch * out;
@@ -668,13 +666,13 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   constexpr int kLate = kPair ? 2 * kLoads : kLoads;
   // a stage past the K-group's range, for the barriers of the other group
   auto idle = [&]() HIGGS_INLINE {
-    if constexpr (KG == 2) {
+    if constexpr (KG > 1) {
       wait_loads<0>();
       __builtin_amdgcn_s_barrier();
     }
   };
   for (int st = 0; st < nmax; st += 2) {
-    if (KG == 2 && st >= nst) {
+    if (KG > 1 && st >= nst) {
       idle();
       idle();
       continue;
@@ -714,7 +712,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
       }
     }
   }
-  add_totals();
+  if (KG == 1 || nst > 0) add_totals();
 
   // No load may be on its way into LDS when a wave leaves or reuses a buffer.
   wait_loads<0>();
@@ -726,12 +724,13 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
     }
   }
   // ---- store through LDS (the activation buffers are free) so that lanes
-  //      write consecutive rows: 32 x 32 tiles; with two K-groups, group 0
-  //      adds group 1's sums for the same rows and columns ----
+  //      write consecutive rows: 32 x 32 tiles; with several K-groups, group 0
+  //      adds the others' sums for the same rows and columns, in turn ----
   constexpr int kORow = 33;                // floats per staged column
   constexpr int kOTile = 32 * kORow;
-  static_assert(kWaves * KG * kOTile * 4 <= KG * kBufs * kStageBytes, "output staging fits");
-  float* s_o = reinterpret_cast<float*>(s_x0) + wave * KG * kOTile;
+  constexpr int kOTiles = KG == 1 ? 1 : NB;  // tiles per wave at a time
+  static_assert(kWaves * kOTiles * kOTile * 4 <= KG * kBufs * kStageBytes, "output staging fits");
+  float* s_o = reinterpret_cast<float*>(s_x0) + wave * kOTiles * kOTile;
   // value of wave tile (m, t) into the wave's tile buffer o
   auto put_tile = [&](int m, int t, float* o) HIGGS_INLINE {
 #pragma unroll
@@ -755,7 +754,9 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
     for (int i = 0; i < 16; ++i) {
       const int c = 2 * i + ahalf;
       float v = o[c * kORow + (lane & 31)];
-      if constexpr (KG == 2) v += o[kGWaves * KG * kOTile + c * kORow + (lane & 31)];
+#pragma unroll
+      for (int q = 1; q < KG; ++q)
+        v += o[q * kGWaves * kOTiles * kOTile + c * kORow + (lane & 31)];
       const uint32_t off = (uint32_t(c) * uint32_t(out) + uint32_t(row)) * 4u;
       __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), drs,
                                             int(2 * i < nc ? off : kOffNone), 0, 0);
@@ -763,8 +764,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   };
 #pragma unroll
   for (int m = 0; m < 2; ++m) {
-    if constexpr (KG == 2) {
-      static_assert(KG == 1 || NB == 2, "a wave's two tiles of a row set, side by side");
+    if constexpr (KG > 1) {
 #pragma unroll
       for (int t = 0; t < NB; ++t) put_tile(m, t, s_o + t * kOTile);
       __syncthreads();
@@ -809,11 +809,12 @@ struct WShape {
   int rows, cols;
   double stage_few, stage_full, unit;
 };
-constexpr int kShapes = 3;
+constexpr int kShapes = 4;
 constexpr WShape kShape[kShapes] = {
     {256, 256, 1.15, 1.70, 1.3},   // one K-group of 8 waves, 64 x 128 each
     {256, 128, 0.75, 1.10, 1.0},   // one K-group of 8 waves, 64 x 64 each
     {128, 128, 0.44, 0.63, 0.55},  // two K-groups of 4 waves, 64 x 64 each
+    {128, 64, 0.26, 0.36, 0.20},   // four K-groups of 2 waves, 64 x 64 each
 };
 
 // A layer's block shape and K-split.
@@ -833,15 +834,16 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // (so every call that fits the 64-column product's workspace in there fits
 // here too, unsplit if need be).
 WPlan plan_wide(int64_t batch, int64_t out, int64_t in, int g, int bits) {
-  constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
+  constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 19, 24, 28, 32, 48, 56};
   const int64_t x_bytes = align256(batch * in * 2) + align256(batch * (in / g) * 4);
   // measured stage times of the other code widths against 8-bit codes
   const double width = bits == 8 ? 1.0 : bits == 6 ? 1.08 : bits == 10 ? 1.5 : 1.3;
-  WPlan best{1, ceil_div(in, 256) * 256, 1};
+  WPlan best{batch <= 64 ? 3 : 1, ceil_div(in, 256) * 256, 1};
   double best_t = 1e30;
   // (g = 64: a change of units every stage, which 64 x 128 wave tiles have no
   // registers for)
-  for (int sh = g == 64 ? 1 : 0; sh < kShapes; ++sh) {
+  const int first = batch <= 64 ? 3 : g == 64 ? 1 : 0, end = batch <= 64 ? 4 : 3;
+  for (int sh = first; sh < end; ++sh) {
     const WShape& S = kShape[sh];
     const int64_t blocks = ceil_div(out, S.rows) * ceil_div(batch, S.cols);
     for (const int s : kSplits) {
@@ -906,37 +908,51 @@ hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, con
   }
 }
 
-template <int BITS, int NB, int KG>
+template <int BITS, int NB, int CW, int KG>
 hipError_t launch_shape(const QW& a, hipStream_t stream) {
   // g = 64 exists for scalar grids only (8- and 16-bit pairs), and takes no
   // 256 x 256 blocks (plan_wide)
   if constexpr ((BITS == 8 || BITS == 16) && NB == 2)
     if (a.log2g == 6) {
-      hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, KG, true>), dim3(unsigned(a.items)),
+      hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, CW, KG, true>), dim3(unsigned(a.items)),
                          dim3(kThreads), 0, stream, a);
       return hipGetLastError();
     }
-  hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, KG, false>), dim3(unsigned(a.items)),
+  hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, CW, KG, false>), dim3(unsigned(a.items)),
                      dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 
 template <int BITS>
 hipError_t launch_bits(const QW& a, int shape, hipStream_t stream) {
-  return shape == 0   ? launch_shape<BITS, 4, 1>(a, stream)
-         : shape == 1 ? launch_shape<BITS, 2, 1>(a, stream)
-                      : launch_shape<BITS, 2, 2>(a, stream);
+  return shape == 0   ? launch_shape<BITS, 4, 2, 1>(a, stream)
+         : shape == 1 ? launch_shape<BITS, 2, 2, 1>(a, stream)
+         : shape == 2 ? launch_shape<BITS, 2, 2, 2>(a, stream)
+                      : launch_shape<BITS, 2, 1, 4>(a, stream);
 }
 
 }  // namespace
 
 // From 65 rows the wide blocks were never slower than the 64-column launches
 // (65 rows: 4096 x 4096 25.9 -> 25.7 us, 14336 x 4096 46 -> 33; 129 rows: 41 ->
-// 30, 72 -> 44); up to 64 rows those need one launch and half the columns of
-// the smallest block here. The limits on `in` keep byte offsets within 32 bits
+// 30, 72 -> 44). Up to 64 rows those are as fast or faster (64 rows, 4096 x
+// 14336, 256 points: 28 us against 34) except where their folds of many small
+// groups or two lookups per pair weigh: g = 64 (64 rows, 4096 x 14336: 16 points
+// 82 -> 38, 256 scalar points 167 -> 42; 32 rows, 14336 x 4096: 65 -> 32, 89 ->
+// 36; 4096 x 4096, 16 points: 21.5 against 21.2 at 32 rows and less than that
+// at 16) and scalar 256-point grids with g = 128 (64 rows: 68 -> 37, 64 -> 35;
+// 32 rows: 30 against 34). On long rows a layer of few outputs loses at small
+// batches (600 x 14336, 16 points: 20 us against 24 at 17 rows, 32 against 30
+// at 64), so the lines lie higher there. The limits on `in` keep byte offsets within 32 bits
 // and rows worth splitting.
-bool use_qgemm_wide(int64_t batch, int64_t in) {
-  return batch > 64 && batch < (int64_t(1) << 24) && in >= 512 && in <= (int64_t(1) << 20);
+bool use_qgemm_wide(int64_t batch, int64_t in, int p, int n, int g) {
+  if (batch >= (int64_t(1) << 24) || in < 512 || in > (int64_t(1) << 20)) return false;
+  const bool scalar = p == 1 && n == 256;
+  const bool long_rows = in > 6144;
+  const int64_t above = g == 64          ? (scalar ? (long_rows ? 32 : 8) : (long_rows ? 48 : 16))
+                        : g == 128 && scalar ? 32
+                                             : 64;
+  return batch > above;
 }
 
 int64_t qgemm_wide_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,

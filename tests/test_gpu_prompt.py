@@ -30,9 +30,14 @@ SIZES_G64 = [
     (65, 12000, 1088, 64),  # 256 x 128, five splits
     (128, 129, 576, 64),    # 128 x 128, nine stages
     (65, 100, 1088, 64),    # 128 x 128, five splits, the last one stage
+    (64, 1500, 1088, 64),   # 128 x 64 with four K-groups
+    (17, 129, 576, 64),
+    (33, 12000, 640, 64),   # 128 x 64 unsplit, K-groups of four and two stages
 ]
 CASES = [(p, n) + s for p, n in FORMATS for s in SIZES]
 CASES += [(p, n) + s for p, n in FORMATS if p == 1 for s in SIZES_G64]
+# scalar 256-point grid: 128 x 64 blocks from 33 rows (g = 128) or 9 (g = 64)
+CASES += [(1, 256, 33, 300, 640, 128), (1, 256, 64, 12000, 2048, 128), (1, 256, 9, 131, 512, 64)]
 
 
 def make_layer(p, n, out, inp, g, seed):
