@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import functools
 import os
 
 import numpy as np
@@ -98,19 +99,37 @@ def _check(status: int):
 
 
 def _ptr(t) -> int:
-    return int(t.data_ptr())
+    return t.data_ptr()
+
+
+# torch, imported at the first device call (the host entry points need none).
+# The small products take about as long on the GPU as their call takes here, so
+# the helpers of that path look nothing up twice: at batch 1, 4096 x 4096 an
+# eager call among others took 11.4 us, 7.4 now (its kernel 6.6).
+_torch = None
+_FLOATS = _F32 = _F16 = _U8 = _F64 = ()
+
+
+def _need_torch():
+    global _torch, _FLOATS, _F32, _F16, _U8, _F64
+    if _torch is None:
+        import torch
+        _FLOATS = (torch.float32, torch.bfloat16)
+        _F32, _F16, _U8 = (torch.float32,), (torch.float16,), (torch.uint8,)
+        _F64 = (torch.float64,)
+        _torch = torch
+    return _torch
 
 
 def _stream(stream):
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(stream.cuda_stream))
+        cuda = _need_torch()._C
+        return cuda._cuda_getCurrentRawStream(cuda._cuda_getDevice())
+    return int(stream.cuda_stream)
 
 
 def _need_cuda(name, t, dtypes):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _need_torch().Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype not in dtypes:
         raise ValueError(f"{name} must have dtype in {dtypes}, got {t.dtype}")
@@ -119,8 +138,44 @@ def _need_cuda(name, t, dtypes):
 
 
 def _dtype_code(t):
-    import torch
-    return HIGGS_F32 if t.dtype == torch.float32 else HIGGS_BF16
+    return HIGGS_F32 if t.dtype is _torch.float32 else HIGGS_BF16
+
+
+# The workspace sizes are pure functions of the sizes.
+@functools.lru_cache(maxsize=4096, typed=True)
+def _qmatmul_workspace(batch, out, inp, p, n, g):
+    return int(lib().higgs_qmatmul_workspace_bytes(batch, out, inp, p, n, g))
+
+
+@functools.lru_cache(maxsize=4096, typed=True)
+def _fused_workspace(batch, out, inp, p, n, g):
+    return int(lib().higgs_qmatmul_fused_workspace_bytes(batch, out, inp, p, n, g))
+
+
+@functools.lru_cache(maxsize=4096, typed=True)
+def _multi_workspace(batch, outs, inp, p, n, g):
+    arr = (ctypes.c_int64 * max(len(outs), 1))(*outs)
+    return int(lib().higgs_qmatmul_fused_multi_workspace_bytes(len(outs), batch, arr, inp, p, n,
+                                                               g))
+
+
+def _output(y, rows, cols, like):
+    """The caller's output, checked, or a new one."""
+    if y is None:
+        return like.new_empty((rows, cols), dtype=_torch.float32)
+    _need_cuda("y", y, _F32)
+    if y.numel() < rows * cols:
+        raise ValueError("y buffer too small")
+    return y
+
+
+def _workspace(workspace, need, like):
+    """(workspace to keep alive, its pointer, its bytes)."""
+    if need <= 0:
+        return None, None, 0
+    if workspace is None:
+        workspace = like.new_empty(need, dtype=_torch.uint8)
+    return workspace, workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 # ---------------------------------------------------------------------------
@@ -164,11 +219,11 @@ def codes_row_bytes(inp: int, p: int, n: int) -> int:
 
 
 def qmatmul_workspace_bytes(batch: int, out: int, inp: int, p: int, n: int, g: int) -> int:
-    return int(lib().higgs_qmatmul_workspace_bytes(batch, out, inp, p, n, g))
+    return _qmatmul_workspace(batch, out, inp, p, n, g)
 
 
 def qmatmul_fused_workspace_bytes(batch: int, out: int, inp: int, p: int, n: int, g: int) -> int:
-    return int(lib().higgs_qmatmul_fused_workspace_bytes(batch, out, inp, p, n, g))
+    return _fused_workspace(batch, out, inp, p, n, g)
 
 
 # ---------------------------------------------------------------------------
@@ -328,14 +383,15 @@ def quantize_gptq(w, grid, g: int, seed: int, factor, codes=None, scales=None, s
 
 def rht_activations(x, g: int, seed: int, out=None, stream=None):
     """x_rot = H (sigma * x_block) / sqrt(g) per block; x: [batch, in] float32 or bfloat16."""
-    import torch
-    _need_cuda("x", x, (torch.float32, torch.bfloat16))
+    torch = _need_torch()
+    _need_cuda("x", x, _FLOATS)
     batch, inp = x.shape
     if out is None:
-        out = torch.empty((batch, inp), dtype=torch.float32, device=x.device)
-    _need_cuda("out", out, (torch.float32,))
-    if out.numel() < batch * inp:
-        raise ValueError("out buffer too small")
+        out = x.new_empty((batch, inp), dtype=torch.float32)
+    else:
+        _need_cuda("out", out, _F32)
+        if out.numel() < batch * inp:
+            raise ValueError("out buffer too small")
     _check(lib().higgs_rht_activations(_ptr(x), _dtype_code(x), batch, inp, g, seed, _ptr(out),
                                        _stream(stream)))
     return out
@@ -344,24 +400,16 @@ def rht_activations(x, g: int, seed: int, out=None, stream=None):
 def qmatmul(x_rot, codes, scales, grid, g: int, out_features: int, y=None, workspace=None,
             stream=None):
     """y = rotated-space LUT product; x_rot: [batch, in] float32. Returns y [batch, out] float32."""
-    import torch
-    _need_cuda("x_rot", x_rot, (torch.float32,))
-    _need_cuda("codes", codes, (torch.uint8,))
-    _need_cuda("scales", scales, (torch.float16,))
-    _need_cuda("grid", grid, (torch.float32,))
+    _need_torch()
+    _need_cuda("x_rot", x_rot, _F32)
+    _need_cuda("codes", codes, _U8)
+    _need_cuda("scales", scales, _F16)
+    _need_cuda("grid", grid, _F32)
     batch, inp = x_rot.shape
     n, p = grid.shape
-    if y is None:
-        y = torch.empty((batch, out_features), dtype=torch.float32, device=x_rot.device)
-    _need_cuda("y", y, (torch.float32,))
-    if y.numel() < batch * out_features:
-        raise ValueError("y buffer too small")
-    need = qmatmul_workspace_bytes(batch, out_features, inp, p, n, g)
-    ws_ptr, ws_bytes = None, 0
-    if need > 0:
-        if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=x_rot.device)
-        ws_ptr, ws_bytes = _ptr(workspace), workspace.numel() * workspace.element_size()
+    y = _output(y, batch, out_features, x_rot)
+    workspace, ws_ptr, ws_bytes = _workspace(
+        workspace, _qmatmul_workspace(batch, out_features, inp, p, n, g), x_rot)
     _check(lib().higgs_qmatmul(_ptr(x_rot), batch, _ptr(codes), _ptr(scales), _ptr(grid), p, n, g,
                                out_features, inp, _ptr(y), ws_ptr, ws_bytes, _stream(stream)))
     return y
@@ -370,24 +418,16 @@ def qmatmul(x_rot, codes, scales, grid, g: int, out_features: int, y=None, works
 def qmatmul_fused(x, codes, scales, grid, g: int, seed: int, out_features: int, y=None,
                   workspace=None, stream=None):
     """y = x W_hat^T from raw activations x: [batch, in] float32 or bfloat16."""
-    import torch
-    _need_cuda("x", x, (torch.float32, torch.bfloat16))
-    _need_cuda("codes", codes, (torch.uint8,))
-    _need_cuda("scales", scales, (torch.float16,))
-    _need_cuda("grid", grid, (torch.float32,))
+    _need_torch()
+    _need_cuda("x", x, _FLOATS)
+    _need_cuda("codes", codes, _U8)
+    _need_cuda("scales", scales, _F16)
+    _need_cuda("grid", grid, _F32)
     batch, inp = x.shape
     n, p = grid.shape
-    if y is None:
-        y = torch.empty((batch, out_features), dtype=torch.float32, device=x.device)
-    _need_cuda("y", y, (torch.float32,))
-    if y.numel() < batch * out_features:
-        raise ValueError("y buffer too small")
-    need = qmatmul_fused_workspace_bytes(batch, out_features, inp, p, n, g)
-    ws_ptr, ws_bytes = None, 0
-    if need > 0:
-        if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-        ws_ptr, ws_bytes = _ptr(workspace), workspace.numel() * workspace.element_size()
+    y = _output(y, batch, out_features, x)
+    workspace, ws_ptr, ws_bytes = _workspace(
+        workspace, _fused_workspace(batch, out_features, inp, p, n, g), x)
     _check(lib().higgs_qmatmul_fused(_ptr(x), _dtype_code(x), batch, _ptr(codes), _ptr(scales),
                                      _ptr(grid), p, n, g, seed, out_features, inp, _ptr(y),
                                      ws_ptr, ws_bytes, _stream(stream)))
@@ -398,18 +438,14 @@ def qmatmul_fused_noalloc(x, codes, scales, grid, g: int, seed: int, out_feature
                           stream=None):
     """qmatmul_fused with the library's fixed scratch as the workspace (no
     device allocation by the library; calls on one device must not overlap)."""
-    import torch
-    _need_cuda("x", x, (torch.float32, torch.bfloat16))
-    _need_cuda("codes", codes, (torch.uint8,))
-    _need_cuda("scales", scales, (torch.float16,))
-    _need_cuda("grid", grid, (torch.float32,))
+    _need_torch()
+    _need_cuda("x", x, _FLOATS)
+    _need_cuda("codes", codes, _U8)
+    _need_cuda("scales", scales, _F16)
+    _need_cuda("grid", grid, _F32)
     batch, inp = x.shape
     n, p = grid.shape
-    if y is None:
-        y = torch.empty((batch, out_features), dtype=torch.float32, device=x.device)
-    _need_cuda("y", y, (torch.float32,))
-    if y.numel() < batch * out_features:
-        raise ValueError("y buffer too small")
+    y = _output(y, batch, out_features, x)
     _check(lib().higgs_qmatmul_fused_noalloc(_ptr(x), _dtype_code(x), batch, _ptr(codes),
                                              _ptr(scales), _ptr(grid), p, n, g, seed,
                                              out_features, inp, _ptr(y), _stream(stream)))
@@ -418,35 +454,32 @@ def qmatmul_fused_noalloc(x, codes, scales, grid, g: int, seed: int, out_feature
 
 def qmatmul_fused_multi_workspace_bytes(batch: int, outs, inp: int, p: int, n: int,
                                         g: int) -> int:
-    arr = (ctypes.c_int64 * max(len(outs), 1))(*outs)
-    return int(lib().higgs_qmatmul_fused_multi_workspace_bytes(len(outs), batch, arr, inp, p, n,
-                                                               g))
+    return _multi_workspace(batch, tuple(outs), inp, p, n, g)
 
 
 def qmatmul_fused_multi(x, layers, grid, g: int, ys=None, workspace=None, stream=None):
     """Outputs of up to 4 layers that read the same raw activations x:
     layers = [(codes, scales, seed, out_features), ...]; returns [y_l]."""
-    import torch
-    _need_cuda("x", x, (torch.float32, torch.bfloat16))
-    _need_cuda("grid", grid, (torch.float32,))
+    torch = _need_torch()
+    _need_cuda("x", x, _FLOATS)
+    _need_cuda("grid", grid, _F32)
     batch, inp = x.shape
     n, p = grid.shape
     k = len(layers)
     if ys is None:
-        ys = [torch.empty((batch, o), dtype=torch.float32, device=x.device)
-              for _, _, _, o in layers]
-    for (c, sc, _, o), y in zip(layers, ys):
-        _need_cuda("codes", c, (torch.uint8,))
-        _need_cuda("scales", sc, (torch.float16,))
-        _need_cuda("y", y, (torch.float32,))
-        if y.numel() < batch * o:
-            raise ValueError("y buffer too small")
-    need = qmatmul_fused_multi_workspace_bytes(batch, [o for *_, o in layers], inp, p, n, g)
-    ws_ptr, ws_bytes = None, 0
-    if need > 0:
-        if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-        ws_ptr, ws_bytes = _ptr(workspace), workspace.numel() * workspace.element_size()
+        ys = [x.new_empty((batch, o), dtype=torch.float32) for _, _, _, o in layers]
+        for c, sc, _, _ in layers:
+            _need_cuda("codes", c, _U8)
+            _need_cuda("scales", sc, _F16)
+    else:
+        for (c, sc, _, o), y in zip(layers, ys):
+            _need_cuda("codes", c, _U8)
+            _need_cuda("scales", sc, _F16)
+            _need_cuda("y", y, _F32)
+            if y.numel() < batch * o:
+                raise ValueError("y buffer too small")
+    workspace, ws_ptr, ws_bytes = _workspace(
+        workspace, _multi_workspace(batch, tuple([o for *_, o in layers]), inp, p, n, g), x)
     vpk = ctypes.c_void_p * max(k, 1)
     codes_a = vpk(*[_ptr(c) for c, *_ in layers])
     scales_a = vpk(*[_ptr(sc) for _, sc, *_ in layers])
