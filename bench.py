@@ -708,9 +708,8 @@ def llama70b_extra(H, synth, dev, flush, batches=(1, 64), reps=12):
 
 def kernel_sources(batch):
     """Sources of the kernels a --profile-pass at `batch` rows runs."""
-    k = "qgemv.hip" if batch == 1 else "qgemm.hip"
-    return [f"paper_2411_17525_amd/csrc/{k}", "paper_2411_17525_amd/csrc/wave_fwht.h",
-            "paper_2411_17525_amd/csrc/internal.h"]
+    ks = ["qgemv.hip"] if batch == 1 else ["qgemm.hip", "qgemm_common.h"]
+    return [f"paper_2411_17525_amd/csrc/{k}" for k in ks + ["wave_fwht.h", "internal.h"]]
 
 
 def summarize_counters(fetch_csv, write_csv, batch, out_json):
