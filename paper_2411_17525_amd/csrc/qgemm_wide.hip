@@ -76,27 +76,51 @@ __device__ inline int group_exponent(float m) {
   return (e < -112 || e > 112) ? e : (e + 7) & ~7;
 }
 
-// One wave per group of g = 64 E elements. 2048 x 4096 bf16
-// into two layers' copies: 25 us (38 us with four waves per group, a sign
-// generator per element and 2-byte stores).
-template <int E, typename InT, bool ROT>
-__global__ __launch_bounds__(256) void xprep_wide_kernel(const InT* __restrict__ x, int64_t batch,
+// One wave per group of g = 64 E elements, W waves per block. Bound by the
+// latency of one load, rotation and store per wave and by the signs that each
+// block makes (two 64-bit products per sign), so 16 waves share them and a
+// wave's first load is under way meanwhile: 2048 x 4096 bf16 into two layers'
+// copies 27.6 -> 22.3 us against blocks of four waves that load afterwards
+// (38 us with four waves per group, a sign generator per element and 2-byte
+// stores), 512 x 14336 13.4 -> 12.3 us.
+template <int E, typename InT, bool ROT, int W>
+__global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restrict__ x, int64_t batch,
                                                          int64_t in, XSeeds seeds, float rscale,
                                                          _Float16* __restrict__ x16,
                                                          float* __restrict__ xe) {
   constexpr int g = 64 * E;
   // g = 1024 rotates through LDS (half the instructions of the cross-lane form)
   constexpr bool kLds = ROT && E == 16;
-  __shared__ __align__(16) float s_rot[kLds ? 4 : 1][kLds ? kFwht1024Scratch : 4];
+  __shared__ __align__(16) float s_rot[kLds ? W : 1][kLds ? kFwht1024Scratch : 4];
   __shared__ uint64_t s_neg[kMaxGroup][E];  // sign bits of 64 elements each
   const int lane = int(threadIdx.x) & 63;
-  const int wave = int(threadIdx.x) >> 6;
+  int wave = int(threadIdx.x) >> 6;
+  if constexpr (ROT) wave = __builtin_amdgcn_readfirstlane(wave);
   const int64_t gpr = in / g, ngroups = batch * gpr;
-  const int64_t nwaves = int64_t(gridDim.x) * 4;
+  const int64_t nwaves = int64_t(gridDim.x) * W;
   const int nl = seeds.nl;
+  int64_t grp = int64_t(blockIdx.x) * W + wave;
+  const auto row_of = [gpr](int64_t i) HIGGS_INLINE {
+    if (ROT && (i >> 32) == 0) return int64_t(uint32_t(i) / uint32_t(gpr));
+    return i / gpr;
+  };
+  // a wave's first weights are on their way while the signs are made
+  constexpr bool kVec = E * sizeof(InT) % 16 == 0;
+  constexpr int kRaw = kVec ? E * int(sizeof(InT)) / 16 : 1;
+  u32x4 raw[kRaw];
+  const auto load = [&]() HIGGS_INLINE {
+    const int64_t row = row_of(grp);
+    const u32x4* src =
+        reinterpret_cast<const u32x4*>(x + row * in + (grp - row * gpr) * g + lane * E);
+#pragma unroll
+    for (int q = 0; q < kRaw; ++q) raw[q] = src[q];
+  };
+  if constexpr (kVec) {
+    if (grp < ngroups) load();
+  }
   uint64_t neg[kMaxGroup] = {0, 0, 0, 0};  // of the lane's E elements
   if constexpr (ROT) {
-    for (int w = wave; w < nl * E; w += 4) {
+    for (int w = wave; w < nl * E; w += W) {
       const int l = w / E, q = w % E;
       uint64_t seed = seeds.s[0];
 #pragma unroll
@@ -110,17 +134,17 @@ __global__ __launch_bounds__(256) void xprep_wide_kernel(const InT* __restrict__
     for (int l = 0; l < kMaxGroup; ++l)
       if (l < nl) neg[l] = s_neg[l][lane * E / 64] >> (lane * E % 64);
   }
-  for (int64_t grp = int64_t(blockIdx.x) * 4 + wave; grp < ngroups; grp += nwaves) {
-    const int64_t row = grp / gpr;
-    const int64_t kg = (grp - row * gpr) * g;
+  while (grp < ngroups) {
+    const int64_t cur = grp;
+    const int64_t row = row_of(cur);
+    const int64_t kg = (cur - row * gpr) * g;
     const int64_t k0 = kg + lane * E;
-    const InT* src = x + row * in + k0;
+    grp += nwaves;
     float u[E];
-    if constexpr (E * sizeof(InT) % 16 == 0) {
+    if constexpr (kVec) {
 #pragma unroll
-      for (int q = 0; q < E * int(sizeof(InT)) / 16; ++q) {
-        const u32x4 d = reinterpret_cast<const u32x4*>(src)[q];
-        const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+      for (int q = 0; q < kRaw; ++q) {
+        const uint32_t w[4] = {raw[q].x, raw[q].y, raw[q].z, raw[q].w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           if constexpr (sizeof(InT) == 4) {
@@ -131,7 +155,9 @@ __global__ __launch_bounds__(256) void xprep_wide_kernel(const InT* __restrict__
           }
         }
       }
+      if (grp < ngroups) load();
     } else {
+      const InT* src = x + row * in + k0;
 #pragma unroll
       for (int i = 0; i < E; ++i) {
         if constexpr (sizeof(InT) == 4)
@@ -186,7 +212,7 @@ __global__ __launch_bounds__(256) void xprep_wide_kernel(const InT* __restrict__
       } else {
         dst[xw_index(batch, in, row, k0)] = static_cast<_Float16>(ldexpf(v[0], -e));
       }
-      if (lane == 0) xe[int64_t(l) * ngroups + grp] = ldexpf(1.0f, e);
+      if (lane == 0) xe[int64_t(l) * ngroups + cur] = ldexpf(1.0f, e);
     }
   }
 }
@@ -888,12 +914,23 @@ hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, con
                              _Float16* x16, float* xe, hipStream_t stream) {
   const float rscale = float(1.0 / std::sqrt(double(g)));
   const int64_t groups = batch * (in / g);
-  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((groups + 3) / 4, 2048));
+  // 16 waves share a block's signs where that leaves a block for every compute
+  // unit, i.e. from 4096 groups; four below (600 groups in blocks of 16 would
+  // use 38 compute units) and where there are no signs (5.2 us either way at
+  // 300 x 5120)
+  const bool big = ROT && g <= 1024 && groups >= 4096;
+  const int w = big ? 16 : 4;
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((groups + w - 1) / w, 8192 / w));
   switch (g) {
 #define HIGGS_XPREP(G)                                                                         \
   case G:                                                                                      \
-    hipLaunchKernelGGL((xprep_wide_kernel<G / 64, InT, ROT>), dim3(unsigned(blocks)),         \
-                       dim3(256), 0, stream, x, batch, in, seeds, rscale, x16, xe);            \
+    if (big)                                                                                   \
+      hipLaunchKernelGGL((xprep_wide_kernel<G / 64, InT, ROT, ROT && G <= 1024 ? 16 : 4>),     \
+                         dim3(unsigned(blocks)), dim3(1024), 0, stream, x, batch, in, seeds,   \
+                         rscale, x16, xe);                                                     \
+    else                                                                                       \
+      hipLaunchKernelGGL((xprep_wide_kernel<G / 64, InT, ROT, 4>), dim3(unsigned(blocks)),     \
+                         dim3(256), 0, stream, x, batch, in, seeds, rscale, x16, xe);          \
     return hipGetLastError();
     HIGGS_XPREP(64)
     HIGGS_XPREP(128)
