@@ -264,10 +264,16 @@ __device__ inline void box_d2(const double* g, const double (&lo)[P], double w, 
   }
 }
 
-// Bucket index along one axis for |v| < kBR: floor((v + kBR) nb / (2 kBR)) as
+// Vectors with every |v| below this walk their bucket's list. Less than kBR by
+// the boxes' widening: the largest double below kBR would round up to the bucket
+// past the last one.
+constexpr double kBIn = kBR - kBEps;
+
+// Bucket index along one axis for |v| < kBIn: floor((v + kBR) nb / (2 kBR)) as
 // the nearest integer to that value less 1/2, read from the low mantissa bits
-// after adding 3 2^51 (no change of binade around it). On a bucket's edge it may name either neighbour, and its
-// roundings are below 1e-12: both are covered by the widening of the boxes.
+// after adding 3 2^51 (no change of binade around it). On a bucket's edge it
+// may name either neighbour, and its roundings are below 1e-12: both are
+// covered by the widening of the boxes.
 __device__ inline int bucket_axis(double v, int nb) {
   const double f = fma(v, double(nb) / (2.0 * kBR), 0.5 * double(nb) - 0.5) + 0x1.8p52;
   return int(uint32_t(__builtin_bit_cast(uint64_t, f)));
@@ -696,10 +702,10 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
       int steps = 0;
 #pragma unroll
       for (int j = 0; j < kVecPerLane; ++j) {
-        bool in_box = fabs(v[j * P]) < kBR;  // (false for NaN)
+        bool in_box = fabs(v[j * P]) < kBIn;  // (false for NaN)
         int b = bucket_axis(v[j * P], BK::kNB);
         if constexpr (P == 2) {
-          in_box = in_box && fabs(v[j * P + 1]) < kBR;
+          in_box = in_box && fabs(v[j * P + 1]) < kBIn;
           b += bucket_axis(v[j * P + 1], BK::kNB) * BK::kNB;
         }
         b = in_box ? b : 0;  // (its list is walked all the same)

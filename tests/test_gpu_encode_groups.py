@@ -68,3 +68,41 @@ def test_encode_ragged_groups(p, n, g, out, inp, dtype):
     rows = rows[(rows >= 0) & (rows < out)]
     ref = O.quantize(vals[rows].astype(np.float64), grid.astype(np.float64), g, 31)
     check_codes(codes, scales, ref, n, rows=rows, grid=grid)
+
+
+@pytest.mark.parametrize("p,n", [(1, 16), (1, 256), (2, 64), (2, 256), (2, 1024)])
+@pytest.mark.parametrize("g", [128, 1024])
+def test_encode_at_the_last_bucket_edge(p, n, g):
+    """Rotated values of exactly the largest double below 4 (and its negative),
+    the edge of the square that the search index covers, on either or both axes:
+    the codes are those of the full scan."""
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] encode edge p={p} n={n} g={g}", file=sys.stderr, flush=True)
+    # 16 equal weights: norm 4 * 49, each normalised to 49 * fl(1 / 196), which
+    # is the largest double below 1/4, and 16 of them add up without rounding
+    below = np.nextafter(4.0, 0.0)
+    assert 16 * (49.0 * (1.0 / 196.0)) == below
+    signs = O.rht_signs(31, g).astype(np.float64)
+    j = np.arange(g)
+    rows, want = [], []
+    for at in (j[:16], j[1:33:2], j[:32:2], j[g - 16:]):  # both parities, even only
+        for alternate in (0, 1):
+            for s in (1.0, -1.0):
+                x = np.zeros(g)
+                x[at] = s * 49.0 * (1 - 2 * (alternate * (at & 1)))
+                rows.append(x * signs)
+                h, step = x * (1.0 / 196.0), 1
+                while step < g:
+                    h = h.reshape(-1, 2, step)
+                    h = np.stack((h[:, 0] + h[:, 1], h[:, 0] - h[:, 1]), axis=1).reshape(-1)
+                    step *= 2
+                want.append(np.abs(h).reshape(-1, p))
+    want = np.concatenate(want)
+    assert bool((want == below).any(axis=0).all())
+    if p == 2:
+        assert bool((want == below).all(axis=1).any()) and bool((want == (below, 0)).all(1).any())
+    w = torch.from_numpy(np.stack(rows).astype(np.float32)).cuda()
+    gd = torch.from_numpy(grid_f32(p, n)).cuda()
+    codes, scales = H.quantize(w, gd, g, 31)
+    full, full_scales = H.quantize(w, gd, g, 31, index=False)
+    assert torch.equal(codes, full) and torch.equal(scales, full_scales)
