@@ -1418,7 +1418,7 @@ __global__ __launch_bounds__(64 * kGptqWaves, 2) void gptq_block_kernel(
       best = min_f64(best, lane_xor<8>(best, lane));
       if constexpr (LPR >= 32) best = min_f64(best, lane_xor<16>(best, lane));
       if constexpr (LPR == 64) best = min_f64(best, lane_xor<32>(best, lane));
-      uint32_t q = N - 1;  // (kept if no value compares equal: NaN)
+      uint32_t q = N;
 #pragma unroll
       for (int j = kCand - 1; j >= 0; --j) q = c[j] == best ? uint32_t(sub + LPR * j) : q;
       q = min(q, lane_xor_u32<1>(q, lane));
@@ -1427,6 +1427,7 @@ __global__ __launch_bounds__(64 * kGptqWaves, 2) void gptq_block_kernel(
       q = min(q, lane_xor_u32<8>(q, lane));
       if constexpr (LPR >= 32) q = min(q, lane_xor_u32<16>(q, lane));
       if constexpr (LPR == 64) q = min(q, lane_xor_u32<32>(q, lane));
+      q = q < N ? q : 0;  // (no value compares equal: NaN)
       double e[P], es[P];
 #pragma unroll
       for (int d = 0; d < P; ++d) e[d] = v[d] - back * s_grid[q * P + d];

@@ -37,3 +37,26 @@ def test_gptq_ragged_blocks(p, n, g, out, inp, dtype):
     assert np.array_equal(scales.cpu().numpy().view(np.uint16), ref["scales"].view(np.uint16))
     assert not ref["mismatch"].any()
     assert np.array_equal(got, ref["codes"])
+
+
+@pytest.mark.parametrize("p,n,g", [(1, 16, 64), (1, 256, 64), (2, 64, 128), (2, 256, 128),
+                                   (2, 1024, 128)])
+def test_gptq_nan_row_stays_apart(p, n, g):
+    """A NaN weight (outside the documented inputs): its row gets code 0 from its
+    group on, and no other row changes."""
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] gptq nan p={p} n={n} g={g}", file=sys.stderr, flush=True)
+    out, inp = 11, 3 * g
+    w = torch.from_numpy(synth.student_t_weight(out, inp, seed=n, dtype="f32").values).cuda()
+    gd = torch.from_numpy(grid_f32(p, n)).cuda()
+    factor = H.gptq_factor(torch.from_numpy(_calib(2 * inp, inp, 3)).cuda(), 0.01)
+    codes, scales = H.quantize_gptq(w, gd, g, 4, factor)
+    w[5, g + 3] = float("nan")
+    codes_nan, scales_nan = H.quantize_gptq(w, gd, g, 4, factor)
+    keep = torch.arange(out, device="cuda") != 5
+    assert torch.equal(codes_nan[keep], codes[keep])
+    assert torch.equal(scales_nan[keep], scales[keep])
+    got = O.unpack_codes(codes_nan.cpu().numpy(), n, inp // p)[5]
+    before = O.unpack_codes(codes.cpu().numpy(), n, inp // p)[5]
+    assert np.array_equal(got[:g // p], before[:g // p])
+    assert (got[g // p:] == 0).all()
