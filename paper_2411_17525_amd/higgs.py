@@ -107,16 +107,15 @@ def _ptr(t) -> int:
 # the helpers of that path look nothing up twice: at batch 1, 4096 x 4096 an
 # eager call among others took 11.4 us, 7.4 now (its kernel 6.6).
 _torch = None
-_FLOATS = _F32 = _F16 = _U8 = _F64 = ()
+_FLOATS = _F32 = _F16 = _U8 = ()
 
 
 def _need_torch():
-    global _torch, _FLOATS, _F32, _F16, _U8, _F64
+    global _torch, _FLOATS, _F32, _F16, _U8
     if _torch is None:
         import torch
         _FLOATS = (torch.float32, torch.bfloat16)
         _F32, _F16, _U8 = (torch.float32,), (torch.float16,), (torch.uint8,)
-        _F64 = (torch.float64,)
         _torch = torch
     return _torch
 
@@ -141,22 +140,28 @@ def _dtype_code(t):
     return HIGGS_F32 if t.dtype is _torch.float32 else HIGGS_BF16
 
 
-# The workspace sizes are pure functions of the sizes.
-@functools.lru_cache(maxsize=4096, typed=True)
+# The workspace sizes are pure functions of the sizes, kept for plain ints. Any
+# other whole number that ctypes takes (a 0-d array or tensor) may not hash, or
+# hash by its identity and change its value: it is read on every call.
+@functools.lru_cache(maxsize=4096)
 def _qmatmul_workspace(batch, out, inp, p, n, g):
     return int(lib().higgs_qmatmul_workspace_bytes(batch, out, inp, p, n, g))
 
 
-@functools.lru_cache(maxsize=4096, typed=True)
+@functools.lru_cache(maxsize=4096)
 def _fused_workspace(batch, out, inp, p, n, g):
     return int(lib().higgs_qmatmul_fused_workspace_bytes(batch, out, inp, p, n, g))
 
 
-@functools.lru_cache(maxsize=4096, typed=True)
+@functools.lru_cache(maxsize=4096)
 def _multi_workspace(batch, outs, inp, p, n, g):
     arr = (ctypes.c_int64 * max(len(outs), 1))(*outs)
     return int(lib().higgs_qmatmul_fused_multi_workspace_bytes(len(outs), batch, arr, inp, p, n,
                                                                g))
+
+
+def _of_sizes(kept, *sizes):
+    return (kept if all(type(v) is int for v in sizes) else kept.__wrapped__)(*sizes)
 
 
 def _output(y, rows, cols, like):
@@ -219,11 +224,11 @@ def codes_row_bytes(inp: int, p: int, n: int) -> int:
 
 
 def qmatmul_workspace_bytes(batch: int, out: int, inp: int, p: int, n: int, g: int) -> int:
-    return _qmatmul_workspace(batch, out, inp, p, n, g)
+    return _of_sizes(_qmatmul_workspace, batch, out, inp, p, n, g)
 
 
 def qmatmul_fused_workspace_bytes(batch: int, out: int, inp: int, p: int, n: int, g: int) -> int:
-    return _fused_workspace(batch, out, inp, p, n, g)
+    return _of_sizes(_fused_workspace, batch, out, inp, p, n, g)
 
 
 # ---------------------------------------------------------------------------
@@ -408,8 +413,10 @@ def qmatmul(x_rot, codes, scales, grid, g: int, out_features: int, y=None, works
     batch, inp = x_rot.shape
     n, p = grid.shape
     y = _output(y, batch, out_features, x_rot)
+    need = _qmatmul_workspace if type(out_features) is int is type(g) \
+        else _qmatmul_workspace.__wrapped__
     workspace, ws_ptr, ws_bytes = _workspace(
-        workspace, _qmatmul_workspace(batch, out_features, inp, p, n, g), x_rot)
+        workspace, need(batch, out_features, inp, p, n, g), x_rot)
     _check(lib().higgs_qmatmul(_ptr(x_rot), batch, _ptr(codes), _ptr(scales), _ptr(grid), p, n, g,
                                out_features, inp, _ptr(y), ws_ptr, ws_bytes, _stream(stream)))
     return y
@@ -426,8 +433,10 @@ def qmatmul_fused(x, codes, scales, grid, g: int, seed: int, out_features: int, 
     batch, inp = x.shape
     n, p = grid.shape
     y = _output(y, batch, out_features, x)
+    need = _fused_workspace if type(out_features) is int is type(g) \
+        else _fused_workspace.__wrapped__
     workspace, ws_ptr, ws_bytes = _workspace(
-        workspace, _fused_workspace(batch, out_features, inp, p, n, g), x)
+        workspace, need(batch, out_features, inp, p, n, g), x)
     _check(lib().higgs_qmatmul_fused(_ptr(x), _dtype_code(x), batch, _ptr(codes), _ptr(scales),
                                      _ptr(grid), p, n, g, seed, out_features, inp, _ptr(y),
                                      ws_ptr, ws_bytes, _stream(stream)))
@@ -454,7 +463,9 @@ def qmatmul_fused_noalloc(x, codes, scales, grid, g: int, seed: int, out_feature
 
 def qmatmul_fused_multi_workspace_bytes(batch: int, outs, inp: int, p: int, n: int,
                                         g: int) -> int:
-    return _multi_workspace(batch, tuple(outs), inp, p, n, g)
+    outs = tuple(outs)
+    plain = all(type(v) is int for v in (batch, *outs, inp, p, n, g))
+    return (_multi_workspace if plain else _multi_workspace.__wrapped__)(batch, outs, inp, p, n, g)
 
 
 def qmatmul_fused_multi(x, layers, grid, g: int, ys=None, workspace=None, stream=None):
@@ -479,7 +490,8 @@ def qmatmul_fused_multi(x, layers, grid, g: int, ys=None, workspace=None, stream
             if y.numel() < batch * o:
                 raise ValueError("y buffer too small")
     workspace, ws_ptr, ws_bytes = _workspace(
-        workspace, _multi_workspace(batch, tuple([o for *_, o in layers]), inp, p, n, g), x)
+        workspace, qmatmul_fused_multi_workspace_bytes(batch, [o for *_, o in layers], inp, p, n,
+                                                       g), x)
     vpk = ctypes.c_void_p * max(k, 1)
     codes_a = vpk(*[_ptr(c) for c, *_ in layers])
     scales_a = vpk(*[_ptr(sc) for _, sc, *_ in layers])

@@ -370,3 +370,27 @@ def test_qmatmul_fused_multi_rejects_bad_args_before_launch(L):
     assert H.qmatmul_fused_multi_workspace_bytes(1, outs, 4096, 2, 256, 1024) == 0
     assert H.qmatmul_fused_multi_workspace_bytes(1, [], 4096, 2, 256, 1024) == -1
     assert H.qmatmul_fused_multi_workspace_bytes(1, [16] * 5, 4096, 2, 256, 1024) == -1
+
+
+def test_workspace_sizes_read_whole_number_objects_anew(L):
+    """Sizes given as 0-d arrays or tensors (whole numbers to ctypes) are taken
+    as before, and by their value at each call."""
+    torch = pytest.importorskip("torch")
+    for size in (np.array(8192), torch.tensor(8192), np.int64(8192)):
+        args = (64, size, 4096, 2, 256, 1024)
+        want = L.higgs_qmatmul_workspace_bytes(64, 8192, 4096, 2, 256, 1024)
+        assert H.qmatmul_workspace_bytes(*args) == want
+        assert H.qmatmul_fused_workspace_bytes(*args) == want
+        multi = H.qmatmul_fused_multi_workspace_bytes(64, [8192, 8192], 4096, 2, 256, 1024)
+        assert H.qmatmul_fused_multi_workspace_bytes(64, [size, size], 4096, 2, 256,
+                                                     1024) == multi
+    size = torch.tensor(8192)
+    H.qmatmul_workspace_bytes(64, size, 4096, 2, 256, 1024)
+    size.fill_(1024)
+    assert H.qmatmul_workspace_bytes(64, size, 4096, 2, 256, 1024) == \
+        L.higgs_qmatmul_workspace_bytes(64, 1024, 4096, 2, 256, 1024)
+    assert H.qmatmul_workspace_bytes(64, size, 4096, 2, 256, 1024) != \
+        L.higgs_qmatmul_workspace_bytes(64, 8192, 4096, 2, 256, 1024)
+    for bad in (8192.0, "8192", None):
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            H.qmatmul_workspace_bytes(64, bad, 4096, 2, 256, 1024)
