@@ -164,10 +164,19 @@ def _of_sizes(kept, *sizes):
     return (kept if all(type(v) is int for v in sizes) else kept.__wrapped__)(*sizes)
 
 
+def _new_f32(like, rows, cols):
+    """A plain tensor on like's device (new_empty is the cheaper call, but gives
+    a tensor subclass its own type)."""
+    t = like.new_empty((rows, cols), dtype=_torch.float32)
+    if type(t) is not _torch.Tensor:
+        t = _torch.empty((rows, cols), dtype=_torch.float32, device=like.device)
+    return t
+
+
 def _output(y, rows, cols, like):
     """The caller's output, checked, or a new one."""
     if y is None:
-        return like.new_empty((rows, cols), dtype=_torch.float32)
+        return _new_f32(like, rows, cols)
     _need_cuda("y", y, _F32)
     if y.numel() < rows * cols:
         raise ValueError("y buffer too small")
@@ -388,11 +397,11 @@ def quantize_gptq(w, grid, g: int, seed: int, factor, codes=None, scales=None, s
 
 def rht_activations(x, g: int, seed: int, out=None, stream=None):
     """x_rot = H (sigma * x_block) / sqrt(g) per block; x: [batch, in] float32 or bfloat16."""
-    torch = _need_torch()
+    _need_torch()
     _need_cuda("x", x, _FLOATS)
     batch, inp = x.shape
     if out is None:
-        out = x.new_empty((batch, inp), dtype=torch.float32)
+        out = _new_f32(x, batch, inp)
     else:
         _need_cuda("out", out, _F32)
         if out.numel() < batch * inp:
@@ -471,14 +480,14 @@ def qmatmul_fused_multi_workspace_bytes(batch: int, outs, inp: int, p: int, n: i
 def qmatmul_fused_multi(x, layers, grid, g: int, ys=None, workspace=None, stream=None):
     """Outputs of up to 4 layers that read the same raw activations x:
     layers = [(codes, scales, seed, out_features), ...]; returns [y_l]."""
-    torch = _need_torch()
+    _need_torch()
     _need_cuda("x", x, _FLOATS)
     _need_cuda("grid", grid, _F32)
     batch, inp = x.shape
     n, p = grid.shape
     k = len(layers)
     if ys is None:
-        ys = [x.new_empty((batch, o), dtype=torch.float32) for _, _, _, o in layers]
+        ys = [_new_f32(x, batch, o) for _, _, _, o in layers]
         for c, sc, _, _ in layers:
             _need_cuda("codes", c, _U8)
             _need_cuda("scales", sc, _F16)
