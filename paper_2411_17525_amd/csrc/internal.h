@@ -173,6 +173,10 @@ hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64
                              const int64_t* outs, int64_t in, float* const* y, void* workspace,
                              hipStream_t stream);
 
+// What its launches are made of, for the tests (host only, no checks).
+extern "C" void higgs_internal_wide_range(int in, int kps, int split, int groups, int q,
+                                          int* first, int* stages, int* turns);
+
 // The library's fixed device scratch (scratch.hip): its device address on
 // the current device, resolved once per device (hipGetSymbolAddress).
 constexpr int64_t kScratchBytes = HIGGS_NOALLOC_SCRATCH_BYTES;

@@ -220,6 +220,26 @@ __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restric
 // ---------------------------------------------------------------------------
 // The product.
 // ---------------------------------------------------------------------------
+// The weights of K that K-group q of a block takes, the block's split covering
+// [split kps, split kps + kps) of them: equal parts (rounded up to 128) in turn,
+// so group 0 has the most stages of 64, and every group waits for as many (two
+// if group 0 has one). A group without stages still requests one of the row's,
+// which it does not use.
+struct WideRange {
+  int first;   // first weight
+  int stages;  // stages of the group
+  int turns;   // stages to wait for
+};
+
+__host__ __device__ inline WideRange wide_range(int in, int kps, int split, int groups, int q) {
+  const int kbeg = split * kps, kend = kbeg + kps < in ? kbeg + kps : in;
+  const int part = groups == 1 ? kend - kbeg
+                               : (kend - kbeg + 128 * groups - 1) / (128 * groups) * 128;
+  const int first = kbeg + q * part < kend ? kbeg + q * part : kend;
+  const int end = first + part < kend ? first + part : kend;
+  return WideRange{first < in - 64 ? first : in - 64, (end - first) >> 6, part >> 6};
+}
+
 // One launch covers nl layers (1..kMaxGroup) that read the same activations.
 // Work items are numbered layer by layer, row tile by row tile, then by
 // K-split, then by column tile; XCD x (blocks are dealt to the XCDs round
@@ -323,15 +343,11 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   const int split = wt - rtile * splits;
   const int row0 = rtile * kRows + rw * 64;  // the wave's first row
   const int col0 = ctile * kCols;                             // the block's first batch row
-  // the K-group's part of the block's K-range: with several, equal parts
-  // (rounded up to 128 weights) in turn, so group 0 has the most stages
-  int kbeg = split * kps;
-  int kend = min(in, kbeg + kps);
-  const int kpart = KG == 1 ? kend - kbeg : (kend - kbeg + 128 * KG - 1) / (128 * KG) * 128;
-  const int nmax = kpart >> 6;
-  kbeg = min(kend, kbeg + kgrp * kpart);
-  kend = min(kend, kbeg + kpart);
-  const int nst = (kend - kbeg) >> 6;  // stages (K-blocks of 64 weights)
+  // the K-group's part of the block's K-range
+  const WideRange range = wide_range(in, kps, split, KG, kgrp);
+  const int kbeg = range.first;
+  const int nmax = range.turns;
+  const int nst = range.stages;        // stages (K-blocks of 64 weights)
   const int last = max(nst - 1, 0);    // stage that requests past the end repeat
   dst += int64_t(split) * batch * out;
 
@@ -1088,6 +1104,14 @@ hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64
     if (err != hipSuccess) return err;
   }
   return hipSuccess;
+}
+
+extern "C" void higgs_internal_wide_range(int in, int kps, int split, int groups, int q,
+                                          int* first, int* stages, int* turns) {
+  const WideRange r = wide_range(in, kps, split, groups, q);
+  *first = r.first;
+  *stages = r.stages;
+  *turns = r.turns;
 }
 
 }  // namespace higgs
