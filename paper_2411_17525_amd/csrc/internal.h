@@ -174,6 +174,10 @@ hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64
                              hipStream_t stream);
 
 // What its launches are made of, for the tests (host only, no checks).
+// _plan: the block shape (index in qgemm_wide.hip's table; -1 where
+// use_qgemm_wide says no) and the K-splits of a layer; _range: see wide_range.
+extern "C" int higgs_internal_wide_plan(int64_t batch, int64_t out, int64_t in, int p, int n,
+                                        int g, int64_t* splits);
 extern "C" void higgs_internal_wide_range(int in, int kps, int split, int groups, int q,
                                           int* first, int* stages, int* turns);
 

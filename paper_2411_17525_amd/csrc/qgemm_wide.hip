@@ -1,35 +1,30 @@
 // Lookup-table GEMM for HIGGS layers at prompt-sized batches (more than 64
 // rows; fewer for small groups, use_qgemm_wide) on the matrix cores: the product of qgemm.hip,
 //   y[b][o] = sum_i scale[o][i] * sum_j < G[code(o,i,j)], x_rot[b, ig+jp : ig+(j+1)p] >,
-// in blocks of 128 or 256 rows x 64 to 256 batch columns instead of one
-// launch per 64 columns, so that a code is decoded once per 256 columns and the
-// products of a block outweigh what it reads. Measured on MI355X against the
-// 64-column launches: two 14336 x 4096 layers at 2048 rows 987 -> 472 us
-// (1.02 PFLOP/s; a plain fp16 product of that size in torch: 427 us), 4096 x
-// 14336 with 10-bit codes at 512 rows 217 -> 110 us, 11003 x 5120 at 300 rows
-// 153 -> 95 us. With nothing but the matrix instructions and barriers left in
-// the loop the first takes about 400 us: at full load the matrix cores run at
-// reduced clocks, and 896 blocks on 256 compute units leave half a round idle.
+// in blocks of 128 or 256 rows x 64 or 128 batch columns instead of one launch
+// per 64 columns. Measured on MI355X against the 64-column launches (rotated
+// fp32 input): 28672 x 4096 at 2048 rows 939 -> 504 us (0.95 PFLOP/s; a plain
+// fp16 product of that size in torch: 427 us), 4096 x 14336 with 10-bit codes
+// at 512 rows 215 -> 110 us, 11003 x 5120 at 300 rows 150 -> 98 us.
 //   * xprep_wide_kernel converts (and rotates) the activations once, to fp16
 //     with one power of two per (batch row, scale group), in the layout the
 //     product stages: per 256-row chunk, per 64 weights of K, one 128-byte
 //     row per batch row whose 16-byte pieces are permuted by the row's low
 //     bits, so that a stage goes to LDS as it lies in memory and is read back
 //     as matrix operands without bank conflicts.
-//   * qgemm_wide_kernel: 8 waves (two per SIMD), each owning 64 rows x 32 NB
-//     columns of the block in matrix registers. Activation stages of 64
-//     weights go straight from memory to LDS (no registers), three buffers
-//     deep; codes are read in the operand layout two stages at a time and
-//     turned into fp16 operands through the replicated LDS table as in
-//     qgemm.hip.
-// Scale groups: the sums are kept in units of the current group's scale times
-// activation exponent, u(o, b); at a group's end they are multiplied by
-// u(this group) / u(next group) (one rounding in fp32), so a wave needs one
-// set of accumulators, not a second one for the scaled totals. Where that
-// ratio cannot be formed (a zero, infinite or NaN scale) or the exponents
-// move by more than 2^20 from where the sums began, the wave adds its sums,
-// scaled, to y (or to the split's partial sums), which it alone owns, and
-// starts again from zero. Between such points |sum / u| stays below 2^120.
+//   * qgemm_wide_kernel: 4 waves (one per SIMD, 512 registers), each owning 64
+//     rows x 128 columns of the block, or 8 (two per SIMD) with 64 x 64 each.
+//     Activation stages of 64 weights go straight from memory to LDS (no
+//     registers), three buffers deep; codes are read in the operand layout two
+//     stages at a time and turned into fp16 operands through the replicated
+//     LDS table as in qgemm.hip.
+// Scale groups: a group's sums start at zero and are added, times scale and
+// activation exponent, to fp32 totals at its end, as in qgemm.hip (one
+// rounding). Sums and totals of 64 x 128 take half of one wave's registers, so
+// that two such waves per SIMD have no room for the totals. One running sum
+// per wave, rescaled by the ratio of the scales at each group's end, let 8 of
+// them work a 256 x 256 block and was 7% faster at 2048 rows (470 us), but its
+// sums had about three times the rounding error.
 
 #include <algorithm>
 #include <cmath>
@@ -42,8 +37,6 @@
 namespace higgs {
 namespace {
 
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
 constexpr int kChunk = 256;  // batch rows per chunk of the fp16 activations
 constexpr int kBufs = 3;     // activation stages in LDS
 
@@ -273,9 +266,10 @@ __device__ inline void wait_loads() {
 // G64: groups of 64 weights, which end at every stage; larger groups end at
 // even stages only (K-ranges start at multiples of 128, and such rows have an
 // even number of stages).
-template <int BITS, int NB, int CW, int KG, bool G64>
-__global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
+template <int BITS, int NB, int CW, int KG, int kWaves, bool G64>
+__global__ __launch_bounds__(64 * kWaves, kWaves / 4) void qgemm_wide_kernel(const QW a) {
   using F = GFmt<BITS>;
+  constexpr int kThreads = 64 * kWaves;
   constexpr int kW = F::kWords;
   // 256-byte entry slots hold 32 copies in their low halves; the high halves
   // of 16 slots hold the waves' row factors (rows_of below). 10-bit codes: 16
@@ -289,7 +283,6 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   constexpr int kRows = 64 * kWaves / (CW * KG);
   constexpr int kGWaves = kWaves / KG;  // waves of a K-group
   constexpr int kDma = kCols / 8 / kGWaves;  // activation loads per wave and stage
-  constexpr bool kTotals = NB == 2;
   constexpr int kStageBytes = kCols * 128;  // 64 weights of kCols batch rows
   constexpr bool kPair = BITS != 16;        // codes requested for two stages at a time
   // code loads per stage: one per row set, two for 10- and 16-bit pairs
@@ -421,11 +414,9 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   issue_x(2, 2);
   __builtin_amdgcn_sched_barrier(0);
   int grp = kbeg >> log2g;
-  float s_cur, s_nxt, x_cur[NB], x_nxt[NB], x_ref[NB];
+  float s_cur, s_nxt, x_cur[NB], x_nxt[NB];
   load_units(grp, s_cur, x_cur);
   load_units(grp + 1, s_nxt, x_nxt);
-#pragma unroll
-  for (int t = 0; t < NB; ++t) x_ref[t] = x_cur[t];
 
   // ---- the table: kCopies copies of each entry, whole 16-byte words ----
   {
@@ -445,17 +436,14 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   }
   const uint32_t copy_off = uint32_t(lane & (kCopies - 1)) << 2;
 
-  f16x_acc acc[2][NB];
-  f16x_acc total[kTotals ? 2 : 1][kTotals ? NB : 1];  // scaled sums of whole groups
+  f16x_acc acc[2][NB];    // sums of the current scale group
+  f16x_acc total[2][NB];  // scaled sums of the groups before it
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
     for (int t = 0; t < NB; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        acc[m][t][r] = 0.f;
-        if constexpr (kTotals) total[m][t][r] = 0.f;
-      }
+      for (int r = 0; r < 16; ++r) acc[m][t][r] = total[m][t][r] = 0.f;
 
   // B operand of step s, tile t: piece 4 ahalf + s of column 32 t + l % 32
   const int bcol = (cw * 32 * NB + (lane & 31)) * 128;
@@ -464,43 +452,6 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   for (int s = 0; s < 4; ++s) bpos[s] = uint32_t(bcol + (((4 * ahalf + s) ^ (lane & 7)) << 4));
 
   int buf = 0;  // the current stage's buffer
-
-  // Adds the wave's sums, scaled, to its part of dst (first time: stores
-  // them). Loads and stores are unconditional (out-of-range offsets
-  // read zero and store nothing), so the path is short; it is rarely taken.
-  bool flushed = false;
-  auto flush = [&]() HIGGS_INLINE {
-    // opaque, so that the 128 offsets below are formed here and not kept in
-    // registers through the main loop
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    __amdgpu_buffer_rsrc_t drs[NB];
-#pragma unroll
-    for (int t = 0; t < NB; ++t)
-      drs[t] = rsrc(dst + int64_t(col0 + cw * 32 * NB + 32 * t) * out, 0x7fffffffu);
-    const uint32_t coff = (uint32_t(ln & 31) * uint32_t(out) + uint32_t(row0)) * 4u;
-    const int cleft = batch - (col0 + cw * 32 * NB) - (ln & 31);  // t < cleft / 32: stored
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl = 32 * m + 8 * (r / 4) + 4 * (ln >> 5) + (r % 4);
-        const float sr = __shfl(s_cur, rl, 64);
-        const uint32_t roff = row0 + rl < out ? coff + 4u * uint32_t(rl) : kOffNone;
-#pragma unroll
-        for (int t = 0; t < NB; ++t) {
-          const uint32_t off = 32 * t < cleft ? roff : kOffNone;
-          const float old = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(drs[t], int(flushed ? off : kOffNone),
-                                                          0, 0));
-          const float v = acc[m][t][r] * (sr * x_cur[t]);
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, flushed ? old + v : v),
-                                                drs[t], int(off), 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    flushed = true;
-  };
 
   // ---- a stage: 4 steps of 16 weights per K-half, each 2 NB products. The
   //      operands of a step are read from LDS while the step before it
@@ -599,95 +550,31 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
       for (int k = 0; k < 4; ++k) f[k] = __shfl(row_f, 32 * m + 8 * q + half4 + k, 64);
     }
   };
-  // Totals (NB = 2): in units of x_ref per column while every column's
-  // exponent stays what it was at the first group, else absolute (x_ref = 1).
+  // Adds the group's sums, in units of the row's scale times the column's power
+  // of two, to the totals: one rounding (the power of two is exact).
   auto add_totals = [&]() HIGGS_INLINE {
-    if constexpr (kTotals) {
-      bool same = true;
+    put_rows(s_cur);
 #pragma unroll
-      for (int t = 0; t < NB; ++t) same = same && x_cur[t] == x_ref[t];
-      const bool fast = __all(same);  // uniform
-      if (!fast) {
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int t = 0; t < NB; ++t) {
+      for (int q = 0; q < 4; ++q) {
+        float f[4];
+        row_quad(m, q, f);
 #pragma unroll
-          for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) total[m][t][r] *= x_ref[t];
-          x_ref[t] = 1.f;
-        }
-      }
-      put_rows(s_cur);
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float f[4];
-          row_quad(m, q, f);
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int t = 0; t < NB; ++t) {
-              const int r = 4 * q + k;
-              if (!fast) acc[m][t][r] *= x_cur[t];
-              total[m][t][r] = fmaf(acc[m][t][r], f[k], total[m][t][r]);
-              acc[m][t][r] = 0.f;
-            }
-        }
-    }
-  };
-  // after stage st: at the end of a scale group inside the block's K-range,
-  // the change of units
-  auto change_units = [&](int st) HIGGS_INLINE {
-    const int gn = (kbeg + (st + 1) * 64) >> log2g;
-    if (st + 1 < nst && gn != grp) {
-      if constexpr (kTotals) {
-        add_totals();
-      } else {
-        // exponents are powers of two (normal numbers): compared and divided
-        // by their bit patterns
-        bool ok = s_cur != 0.f && s_nxt != 0.f && fabsf(s_cur) <= 65504.f &&
-                  fabsf(s_nxt) <= 65504.f;
-        bool same = true;
-#pragma unroll
-        for (int t = 0; t < NB; ++t) {
-          const int d = __float_as_int(x_nxt[t]) - __float_as_int(x_ref[t]);
-          ok = ok && d >= -(20 << 23) && d <= (20 << 23);
-          same = same && x_nxt[t] == x_cur[t];
-        }
-        const bool keep = __all(ok);  // uniform
-        if (!keep) flush();
-        const int keep_bits = keep ? -1 : 0;
-        // the columns' part of the ratio, where there is one
-        if (keep && !__all(same)) {
+        for (int k = 0; k < 4; ++k)
 #pragma unroll
           for (int t = 0; t < NB; ++t) {
-            const float rx = __int_as_float(__float_as_int(x_cur[t]) - __float_as_int(x_nxt[t]) +
-                                            0x3f800000);
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) acc[m][t][r] *= rx;
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < NB; ++t)
-          x_ref[t] = __int_as_float((__float_as_int(x_ref[t]) & keep_bits) |
-                                    (__float_as_int(x_nxt[t]) & ~keep_bits));
-        // the rows' part; zero where the sums start again
-        put_rows(keep ? s_cur / s_nxt : 0.f);
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float f[4];
-            row_quad(m, q, f);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-              for (int t = 0; t < NB; ++t) acc[m][t][4 * q + k] *= f[k];
+            const int r = 4 * q + k;
+            total[m][t][r] = fmaf(acc[m][t][r] * x_cur[t], f[k], total[m][t][r]);
+            acc[m][t][r] = 0.f;
           }
       }
+  };
+  // after stage st: at the end of a scale group inside the block's K-range
+  auto end_group = [&](int st) HIGGS_INLINE {
+    const int gn = (kbeg + (st + 1) * 64) >> log2g;
+    if (st + 1 < nst && gn != grp) {
+      add_totals();
       s_cur = s_nxt;
 #pragma unroll
       for (int t = 0; t < NB; ++t) x_cur[t] = x_nxt[t];
@@ -725,10 +612,10 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
       fetch(st + 3, nxt1);
       __builtin_amdgcn_sched_barrier(0);
       stage(st, cod0, cod1, std::integral_constant<int, kLate>{});
-      if constexpr (G64) change_units(st);
+      if constexpr (G64) end_group(st);
       if (!G64 || st + 1 < nst) {
         stage(st + 1, cod1, nxt0, std::integral_constant<int, 0>{});
-        change_units(st + 1);
+        end_group(st + 1);
       } else {
         idle();
       }
@@ -743,12 +630,12 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
       fetch(st + 1, cod1);
       __builtin_amdgcn_sched_barrier(0);
       stage(st, cod0, cod1, std::integral_constant<int, kLate>{});
-      if constexpr (G64) change_units(st);
+      if constexpr (G64) end_group(st);
       if (!G64 || st + 1 < nst) {
         fetch(st + 2, cod0);
         __builtin_amdgcn_sched_barrier(0);
         stage(st + 1, cod1, cod0, std::integral_constant<int, kLate>{});
-        change_units(st + 1);
+        end_group(st + 1);
       } else {
         idle();
       }
@@ -759,12 +646,6 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
   // No load may be on its way into LDS when a wave leaves or reuses a buffer.
   wait_loads<0>();
   __syncthreads();
-  if constexpr (!kTotals) {
-    if (flushed) {
-      flush();
-      return;
-    }
-  }
   // ---- store through LDS (the activation buffers are free) so that lanes
   //      write consecutive rows: 32 x 32 tiles; with several K-groups, group 0
   //      adds the others' sums for the same rows and columns, in turn ----
@@ -778,12 +659,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm_wide_kernel(const QW a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int rl = 8 * (r / 4) + 4 * ahalf + (r % 4);
-      float v;
-      if constexpr (kTotals)
-        v = total[m][t][r] * x_ref[t];
-      else
-        v = acc[m][t][r] * (__shfl(s_cur, 32 * m + rl, 64) * x_cur[t]);
-      o[(lane & 31) * kORow + rl] = v;
+      o[(lane & 31) * kORow + rl] = total[m][t][r];
     }
   };
   auto store_tile = [&](int m, int t, const float* o) HIGGS_INLINE {
@@ -846,16 +722,16 @@ int pair_bits(int p, int n) { return p == 1 ? 2 * code_bits(p, n) : code_bits(p,
 // Block shapes: rows x batch columns, and the waves' arrangement; times in us
 // measured on MI355X for 8-bit codes: a stage of 64 weights of K with few
 // blocks running and with one on every compute unit (clocks and L2 shared),
-// and the change of units at a scale group's end.
+// and the fold of a scale group into the totals.
 struct WShape {
   int rows, cols;
   double stage_few, stage_full, unit;
 };
 constexpr int kShapes = 4;
 constexpr WShape kShape[kShapes] = {
-    {256, 256, 1.15, 1.70, 1.3},   // one K-group of 8 waves, 64 x 128 each
-    {256, 128, 0.75, 1.10, 1.0},   // one K-group of 8 waves, 64 x 64 each
-    {128, 128, 0.44, 0.63, 0.55},  // two K-groups of 4 waves, 64 x 64 each
+    {256, 128, 0.62, 0.93, 1.2},   // one K-group of 4 waves, 64 x 128 each
+    {256, 128, 0.77, 1.06, 0.7},   // one K-group of 8 waves, 64 x 64 each
+    {128, 128, 0.42, 0.58, 0.4},   // two K-groups of 4 waves, 64 x 64 each
     {128, 64, 0.26, 0.36, 0.20},   // four K-groups of 2 waves, 64 x 64 each
 };
 
@@ -870,7 +746,7 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // The shape and split with the least modelled time: rounds of one block per
 // compute unit, each a start and end (5 us) and its stages; a split adds the
 // reduction launch and the partial sums' traffic. Large tiles decode a code
-// for more columns; small ones, and splits, fill the chip when the layer or
+// for more columns and read less; small ones, and splits, fill the chip when the layer or
 // the batch is small. The plan depends on the sizes only, and a split's
 // partial sums have to leave the workspace within the library's fixed scratch
 // (so every call that fits the 64-column product's workspace in there fits
@@ -880,12 +756,16 @@ WPlan plan_wide(int64_t batch, int64_t out, int64_t in, int g, int bits) {
   const int64_t x_bytes = align256(batch * in * 2) + align256(batch * (in / g) * 4);
   // measured stage times of the other code widths against 8-bit codes
   const double width = bits == 8 ? 1.0 : bits == 6 ? 1.08 : bits == 10 ? 1.5 : 1.3;
-  WPlan best{batch <= 64 ? 3 : 1, ceil_div(in, 256) * 256, 1};
+  // The 256-row shape: from g = 256 the one that decodes a code for twice the
+  // columns, below it the one whose folds, two or one stage apart, cost less
+  // (28672 x 4096 at 2048 rows: g = 1024 504 us against 531, 256: 593 and 588,
+  // scalar 16 points with g = 128: 705 and 648); 10-bit codes, whose decoding
+  // costs most, take the first at g = 128 as well (and g = 64 is scalar).
+  const int large = g < 256 && bits != 10 ? 1 : 0;
+  const int first = batch <= 64 ? 3 : large, last = batch <= 64 ? 3 : 2;
+  WPlan best{first, ceil_div(in, 256) * 256, 1};
   double best_t = 1e30;
-  // (g = 64: a change of units every stage, which 64 x 128 wave tiles have no
-  // registers for)
-  const int first = batch <= 64 ? 3 : g == 64 ? 1 : 0, end = batch <= 64 ? 4 : 3;
-  for (int sh = first; sh < end; ++sh) {
+  for (int sh = first; sh <= last; sh += 2 - large) {
     const WShape& S = kShape[sh];
     const int64_t blocks = ceil_div(out, S.rows) * ceil_div(batch, S.cols);
     for (const int s : kSplits) {
@@ -961,27 +841,33 @@ hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, con
   }
 }
 
-template <int BITS, int NB, int CW, int KG>
+template <int BITS, int NB, int CW, int KG, int W, bool G64>
 hipError_t launch_shape(const QW& a, hipStream_t stream) {
-  // g = 64 exists for scalar grids only (8- and 16-bit pairs), and takes no
-  // 256 x 256 blocks (plan_wide)
-  if constexpr ((BITS == 8 || BITS == 16) && NB == 2)
-    if (a.log2g == 6) {
-      hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, CW, KG, true>), dim3(unsigned(a.items)),
-                         dim3(kThreads), 0, stream, a);
-      return hipGetLastError();
-    }
-  hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, CW, KG, false>), dim3(unsigned(a.items)),
-                     dim3(kThreads), 0, stream, a);
+  hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, CW, KG, W, G64>), dim3(unsigned(a.items)),
+                     dim3(64 * W), 0, stream, a);
   return hipGetLastError();
 }
 
+// The shapes that plan_wide gives a code width and group size (g = 64 exists
+// for scalar grids only; up to 64 rows, shape 3, so do the calls).
 template <int BITS>
 hipError_t launch_bits(const QW& a, int shape, hipStream_t stream) {
-  return shape == 0   ? launch_shape<BITS, 4, 2, 1>(a, stream)
-         : shape == 1 ? launch_shape<BITS, 2, 2, 1>(a, stream)
-         : shape == 2 ? launch_shape<BITS, 2, 2, 2>(a, stream)
-                      : launch_shape<BITS, 2, 1, 4>(a, stream);
+  constexpr bool kScalar = BITS == 8 || BITS == 16;
+  if (a.log2g == 6) {
+    if constexpr (kScalar) {
+      if (shape == 1) return launch_shape<BITS, 2, 2, 1, 8, true>(a, stream);
+      if (shape == 2) return launch_shape<BITS, 2, 2, 2, 8, true>(a, stream);
+      if (shape == 3) return launch_shape<BITS, 2, 1, 4, 8, true>(a, stream);
+    }
+    return hipErrorInvalidValue;
+  }
+  if (shape == 0) return launch_shape<BITS, 4, 1, 1, 4, false>(a, stream);
+  if (shape == 2) return launch_shape<BITS, 2, 2, 2, 8, false>(a, stream);
+  if constexpr (BITS != 10)
+    if (shape == 1) return launch_shape<BITS, 2, 2, 1, 8, false>(a, stream);
+  if constexpr (BITS == 16)
+    if (shape == 3) return launch_shape<BITS, 2, 1, 4, 8, false>(a, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -1006,6 +892,14 @@ bool use_qgemm_wide(int64_t batch, int64_t in, int p, int n, int g) {
                         : g == 128 && scalar ? 32
                                              : 64;
   return batch > above;
+}
+
+extern "C" int higgs_internal_wide_plan(int64_t batch, int64_t out, int64_t in, int p, int n,
+                                        int g, int64_t* splits) {
+  if (!use_qgemm_wide(batch, in, p, n, g)) return -1;
+  const WPlan plan = plan_wide(batch, out, in, g, pair_bits(p, n));
+  *splits = plan.splits;
+  return plan.shape;
 }
 
 int64_t qgemm_wide_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,

@@ -1,9 +1,10 @@
 """GPU parity of the product at prompt-sized batches (more than 64 rows) against
 a plain PyTorch fp64 product of the same rotated activations, codes and scales.
 
-The sizes reach every block shape (256 x 256, 256 x 128, 128 x 128 with two
-K-groups), with and without a K-split, for every code width: one row past a
-tile, ragged rows, rows of an odd number of 64-weight blocks (g = 64)."""
+The sizes reach every block shape that a code width has (256 x 128 in waves of
+64 x 128 or 64 x 64, 128 x 128 with two K-groups, 128 x 64 with four), with and
+without a K-split (test_wide_plan.py holds them to that): one row past a tile,
+ragged rows, rows of an odd number of 64-weight blocks (g = 64)."""
 import sys
 
 import numpy as np
@@ -16,28 +17,37 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 FORMATS = ((2, 64), (2, 256), (2, 1024), (1, 16), (1, 256))
-# batch, out, in, g: shape and splits of the plan for 8-bit codes in the comments
+# batch, out, in, g
 SIZES = [
-    (1000, 8200, 512, 128),   # 256 x 256
-    (129, 17000, 2048, 256),  # 256 x 256 or 256 x 128, three splits
-    (129, 17000, 512, 512),   # 256 x 128
-    (65, 100, 512, 128),      # 128 x 128
-    (65, 100, 640, 128),      # 128 x 128, three splits, the last one short
+    (1000, 8200, 512, 128),
+    (129, 17000, 2048, 256),
+    (129, 17000, 512, 512),
+    (129, 4200, 2560, 512),   # splits of two or more stages each
+    (129, 4200, 5120, 256),
+    (129, 9000, 5120, 128),
+    (300, 9000, 4096, 1024),
+    (385, 1000, 1024, 1024),
+    (65, 100, 512, 128),
+    (65, 100, 640, 128),      # three splits, the last one short
     (257, 513, 4096, 4096),   # one group per row
 ]
 SIZES_G64 = [
-    (129, 17000, 512, 64),  # 256 x 128
-    (65, 12000, 1088, 64),  # 256 x 128, five splits
-    (128, 129, 576, 64),    # 128 x 128, nine stages
-    (65, 100, 1088, 64),    # 128 x 128, five splits, the last one stage
-    (64, 1500, 1088, 64),   # 128 x 64 with four K-groups
+    (129, 17000, 512, 64),
+    (65, 12000, 1088, 64),
+    (129, 9000, 4160, 64),
+    (128, 129, 576, 64),    # three splits, the last one stage
+    (65, 100, 1088, 64),    # five splits, the last one stage
+    (257, 2000, 576, 64),
+    (64, 1500, 1088, 64),
     (17, 129, 576, 64),
-    (33, 12000, 640, 64),   # 128 x 64 unsplit, K-groups of four and two stages
+    (33, 12000, 640, 64),   # K-groups of four and two stages, one of none
+    (49, 200, 6208, 64),    # long rows start at 49 rows (16 points)
 ]
 CASES = [(p, n) + s for p, n in FORMATS for s in SIZES]
 CASES += [(p, n) + s for p, n in FORMATS if p == 1 for s in SIZES_G64]
 # scalar 256-point grid: 128 x 64 blocks from 33 rows (g = 128) or 9 (g = 64)
-CASES += [(1, 256, 33, 300, 640, 128), (1, 256, 64, 12000, 2048, 128), (1, 256, 9, 131, 512, 64)]
+CASES += [(1, 256, 33, 300, 640, 128), (1, 256, 64, 12000, 2048, 128), (1, 256, 9, 131, 512, 64),
+          (1, 256, 33, 300, 8192, 128), (1, 256, 33, 200, 6208, 64)]
 # activations converted by blocks of 16 waves (from 4096 groups): a last block
 # of four waves; waves with two groups, the second pass partial
 CASES += [(2, 256, 1025, 129, 4096, 1024), (1, 16, 137, 131, 4160, 64), (2, 64, 300, 100, 4096, 128)]
@@ -83,8 +93,8 @@ def test_prompt_product(p, n, batch, out, inp, g):
     (2, 64, 65, 100, 1024, 128), (1, 16, 65, 100, 1088, 64)])
 def test_prompt_product_unit_changes(p, n, batch, out, inp, g):
     """Scale groups whose magnitudes, and scales, differ by up to 2^90, zero
-    scales and zero activation groups: the sums change units at every group,
-    or are written out and started again."""
+    scales and zero activation groups: every group's sums are added to totals
+    of another magnitude."""
     from paper_2411_17525_amd import higgs as H
     print(f"[gpu-case] prompt units p={p} n={n} batch={batch} {out}x{inp} g={g}",
           file=sys.stderr, flush=True)
@@ -109,6 +119,33 @@ def test_prompt_product_unit_changes(p, n, batch, out, inp, g):
     assert bool(torch.isfinite(y).all())
     assert bool(((y.double() - ref).abs() <= 1.02 * 2.0 ** -10 * terms).all())
     assert bool((y[:, 3] == 0).all())
+
+
+@pytest.mark.parametrize("p,n,batch,out,inp,g", CASES)
+def test_prompt_product_whole_numbers(p, n, batch, out, inp, g):
+    """Whole grid points, activations (times powers of two that differ by row
+    and group) and scales whose sums of magnitudes stay below 2^24: every
+    operand is exact in fp16 and every sum in fp32, in any order, so a product
+    whose sums are kept per group and added to totals once per group is exact.
+    A sum carried over groups in units of the last one's scale is not."""
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] prompt whole p={p} n={n} batch={batch} {out}x{inp} g={g}", file=sys.stderr,
+          flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+
+    def ints(lo, hi, shape):
+        return torch.randint(lo, hi + 1, shape, generator=gen, device="cuda").float()
+
+    grid = ints(-3, 3, (n, p))
+    codes, _, idx = make_layer(p, n, out, inp, g, 11)
+    scales = (2 * ints(0, 3, (out, inp // g)) + 1).half()  # 1, 3, 5, 7
+    x = ints(-3, 3, (batch, inp // g, g)) * torch.exp2(ints(0, 3, (batch, inp // g, 1)))
+    x = x.reshape(batch, inp)
+    y = H.qmatmul(x, codes, scales, grid, g, out)
+    ref, terms = reference(x, idx, scales, grid, g)
+    assert float(terms.max()) < 2 ** 24
+    assert torch.equal(y.double(), ref)
 
 
 def test_prompt_group_and_noalloc_match_single_calls():

@@ -1,4 +1,5 @@
-"""The prompt-sized product's division of K among splits and K-groups (host)."""
+"""The prompt-sized product's plans and its division of K among splits and
+K-groups (host)."""
 import ctypes
 
 import pytest
@@ -42,3 +43,43 @@ def test_k_groups_cover_k_and_stay_inside(groups, step):
                 assert len(turns) == 1
             assert covered == list(range(0, inp, 64))
     assert (empty > 0) == (groups > 1)
+
+
+def plan(p, n, batch, out, inp, g):
+    f = H.lib().higgs_internal_wide_plan
+    f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 3 + [ctypes.c_void_p]
+    splits = ctypes.c_int64()
+    return f(batch, out, inp, p, n, g, ctypes.byref(splits)), splits.value
+
+
+@pytest.mark.parametrize("p,n", [(2, 64), (2, 256), (2, 1024), (1, 16), (1, 256)])
+def test_gpu_cases_reach_every_plan(p, n):
+    """The sizes of the GPU tests take every kernel instance of the code width,
+    with and without a K-split."""
+    pytest.importorskip("torch")
+    from test_gpu_prompt import CASES
+    got = set()
+    for case in CASES:
+        if case[:2] == (p, n):
+            shape, splits = plan(*case)
+            assert shape >= 0, case
+            got.add(("g64" if case[5] == 64 else "", shape, splits > 1))
+    want = {("", 0), ("", 2)}
+    if n != 1024:
+        want |= {("", 1)}
+    if p == 1:
+        want |= {("g64", 1), ("g64", 2), ("g64", 3)}
+    if (p, n) == (1, 256):
+        want |= {("", 3)}
+    assert {k[:2] for k in got} == want
+    missing = {(*k, split) for k in want for split in (False, True)} - got
+    assert not missing, missing
+
+
+def test_plan_starts_where_the_rule_says():
+    for (p, n, g, inp), first in {(2, 256, 1024, 4096): 65, (1, 16, 64, 4096): 17,
+                                  (1, 16, 64, 6208): 49, (1, 256, 64, 4096): 9,
+                                  (1, 256, 64, 6208): 33, (1, 256, 128, 4096): 33,
+                                  (1, 256, 128, 8192): 33, (1, 16, 128, 4096): 65}.items():
+        assert plan(p, n, first - 1, 512, inp, g)[0] == -1
+        assert plan(p, n, first, 512, inp, g)[0] >= 0
