@@ -57,16 +57,12 @@ __device__ inline int64_t xw_index(int64_t batch, int64_t in, int64_t row, int64
          (k & 7);
 }
 
-// The power of two that a group's fp16 values are in units of: the group's
-// largest magnitude m scaled into [2^7, 2^15). The exponent is a multiple of
-// 8, so that neighbouring groups and rows mostly share it (the product's unit
-// changes are then cheap); fp16 keeps full precision down to 2^-21 of the
-// group's largest value. Near the ends of the fp32 range it is exact instead.
+// The power of two that a group's fp16 values are in units of, as in qgemm.hip:
+// the group's largest magnitude m lies in [2^14, 2^15), so that fp16 keeps all
+// its bits down to 2^-28 of it.
 __device__ inline int group_exponent(float m) {
-  if (!(m > 0.f)) return -8;
-  int e = ilogbf(m) - 14;
-  e = e < -126 ? -126 : (e > 127 ? 127 : e);
-  return (e < -112 || e > 112) ? e : (e + 7) & ~7;
+  const int e = m > 0.f ? ilogbf(m) - 14 : 0;
+  return e < -126 ? -126 : (e > 127 ? 127 : e);
 }
 
 // One wave per group of g = 64 E elements, W waves per block. Bound by the

@@ -148,6 +148,45 @@ def test_prompt_product_whole_numbers(p, n, batch, out, inp, g):
     assert torch.equal(y.double(), ref)
 
 
+@pytest.mark.parametrize("p,n", FORMATS)
+@pytest.mark.parametrize("batch", [40, 130])
+def test_values_far_below_the_largest_keep_their_bits(p, n, batch):
+    """One value of every group is 2^24 times the others, which have 11
+    significant bits; its grid point is the origin, so the product is that of the
+    others. In units that put the largest value just below 2^15 they are normal
+    fp16 numbers: every operand is exact and only the fp32 sums round."""
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] small values p={p} n={n} batch={batch}", file=sys.stderr, flush=True)
+    out, inp, g = 300, 2048, 256
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(10)
+
+    def ints(lo, hi, shape):
+        return torch.randint(lo, hi + 1, shape, generator=gen, device="cuda").float()
+
+    grid = ints(1, 40, (n, p)) * (2 * ints(0, 1, (n, p)) - 1)
+    grid[0] = 0
+    from oracle import higgs_oracle as O
+    idx = np.maximum(synth.random_codes(out, inp // p, n, 13), 1)
+    idx.reshape(out, inp // g, g // p)[:, :, 5] = 0
+    codes = torch.from_numpy(O.pack_codes(idx, n)).cuda()
+    idx = torch.from_numpy(idx.astype(np.int64)).cuda()
+    scales = torch.exp2(ints(-9, -5, (out, inp // g))).half()
+    # largest value in [2^k, 2^(k+1)) for k over a run of exponents
+    x = ints(1024, 2047, (batch, inp // g, g)) * 2.0 ** -34  # [2^-24, 2^-23)
+    x *= 2 * ints(0, 1, x.shape) - 1
+    x[:, :, 5 * p] = 1.5
+    x *= torch.exp2(ints(0, 20, (batch, inp // g, 1)))
+    x = x.reshape(batch, inp)
+    y = H.qmatmul(x, codes, scales, grid, g, out)
+    ref, terms = reference(x, idx, scales, grid, g)
+    # products exact (11 + 6 bits); each term passes at most in + in / g fp32
+    # additions, each within 2^-24 of a partial sum of magnitudes
+    assert bool(((y.double() - ref).abs() <= (inp + inp // g) * 2.0 ** -24 * terms).all())
+    # which 2^-8, what a value that lost four bits would show, is far above
+    assert (inp + inp // g) * 2.0 ** -24 < 2.0 ** -12
+
+
 def test_prompt_group_and_noalloc_match_single_calls():
     from paper_2411_17525_amd import higgs as H
     p, n, g, batch, inp = 2, 256, 256, 300, 1024
