@@ -700,13 +700,21 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void qgemm_wide_kernel(con
 }
 
 // y = sum over splits of the partial products, in split order (split 0's
-// value first); one element per thread, grid-stride.
+// value first); one element per thread, grid-stride. Eight splits' values are
+// requested at a time: a layer of few outputs is bound by the round trips.
 __global__ __launch_bounds__(256) void wide_reduce_kernel(const float* __restrict__ part,
                                                           int64_t n, int splits,
                                                           float* __restrict__ y) {
   for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
-    float s = part[i];
-    for (int k = 1; k < splits; ++k) s += part[int64_t(k) * n + i];
+    float s = 0.f;
+    for (int k = 0; k < splits; k += 8) {
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = part[int64_t(min(k + q, splits - 1)) * n + i];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (k + q < splits) s = k + q == 0 ? v[q] : s + v[q];
+    }
     y[i] = s;
   }
 }

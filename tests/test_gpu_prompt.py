@@ -48,6 +48,8 @@ CASES += [(p, n) + s for p, n in FORMATS if p == 1 for s in SIZES_G64]
 # scalar 256-point grid: 128 x 64 blocks from 33 rows (g = 128) or 9 (g = 64)
 CASES += [(1, 256, 33, 300, 640, 128), (1, 256, 64, 12000, 2048, 128), (1, 256, 9, 131, 512, 64),
           (1, 256, 33, 300, 8192, 128), (1, 256, 33, 200, 6208, 64)]
+# partial sums of 12, 20 or more and 28 splits
+CASES += [(2, 256, 65, 100, 9216, 1024), (1, 16, 70, 33, 20480, 1024), (1, 256, 33, 300, 28672, 128)]
 # activations converted by blocks of 16 waves (from 4096 groups): a last block
 # of four waves; waves with two groups, the second pass partial
 CASES += [(2, 256, 1025, 129, 4096, 1024), (1, 16, 137, 131, 4160, 64), (2, 64, 300, 100, 4096, 128)]
