@@ -161,6 +161,10 @@ hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint6
                               int g, const int64_t* outs, int64_t in, float* const* y,
                               void* workspace, hipStream_t stream);
 
+// The workspace of one layer's product in 64-column launches (qgemm.hip),
+// whichever path the call takes; pair_bits: code bits per pair of weights.
+int64_t qgemm64_workspace_bytes(int64_t batch, int64_t out, int64_t in, int g, int pair_bits);
+
 // The matrix-core product for prompt-sized batches (qgemm_wide.hip), same
 // arguments; launch_qgemm[_group] and the workspace sizes above go to it when
 // use_qgemm_wide says so.

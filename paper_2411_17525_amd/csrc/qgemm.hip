@@ -1187,9 +1187,13 @@ int pair_bits(int p, int n) { return p == 1 ? 2 * code_bits(p, n) : code_bits(p,
 
 }  // namespace
 
+int64_t qgemm64_workspace_bytes(int64_t batch, int64_t out, int64_t in, int g, int pair_bits) {
+  return layout(batch, &out, 1, 1, in, g, pair_bits).total;
+}
+
 int64_t qgemm_workspace_bytes(int64_t batch, int64_t out, int64_t in, int p, int n, int g) {
   if (use_qgemm_wide(batch, in, p, n, g)) return qgemm_wide_workspace_bytes(1, batch, &out, in, p, n, g);
-  return layout(batch, &out, 1, 1, in, g, pair_bits(p, n)).total;
+  return qgemm64_workspace_bytes(batch, out, in, g, pair_bits(p, n));
 }
 
 int64_t qgemm_group_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,

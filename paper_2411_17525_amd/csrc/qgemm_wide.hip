@@ -749,14 +749,17 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // The shape and split with the least modelled time: rounds of one block per
 // compute unit, each a start and end (5 us) and its stages; a split adds the
-// reduction launch and the partial sums' traffic. Large tiles decode a code
-// for more columns and read less; small ones, and splits, fill the chip when the layer or
-// the batch is small. The plan depends on the sizes only, and a split's
-// partial sums have to leave the workspace within the library's fixed scratch
-// (so every call that fits the 64-column product's workspace in there fits
-// here too, unsplit if need be).
+// reduction launch, its round trips and the partial sums' traffic. Large tiles
+// decode a code for more columns and read less; small ones, and splits, fill
+// the chip when the layer or the batch is small. The plan depends on the sizes
+// only. Where the 64-column product's workspace fits in the library's fixed
+// scratch, so does the plan's (unsplit if need be): the calls that use it take
+// what they took with that product. Elsewhere the partial sums take what
+// they need (128 x 131072, 129 rows: 819 us unsplit, 45 with 128 splits, 83
+// in 64-column launches).
 WPlan plan_wide(int64_t batch, int64_t out, int64_t in, int g, int bits) {
-  constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 19, 24, 28, 32, 48, 56};
+  constexpr int kSplits[] = {1,  2,  3,  4,  5,  6,  7,  8,  10, 12,  14,
+                             16, 19, 24, 28, 32, 48, 56, 64, 96, 128, 256};
   const int64_t x_bytes = align256(batch * in * 2) + align256(batch * (in / g) * 4);
   // measured stage times of the other code widths against 8-bit codes
   const double width = bits == 8 ? 1.0 : bits == 6 ? 1.08 : bits == 10 ? 1.5 : 1.3;
@@ -772,15 +775,21 @@ WPlan plan_wide(int64_t batch, int64_t out, int64_t in, int g, int bits) {
   for (int sh = first; sh <= last; sh += 2 - large) {
     const WShape& S = kShape[sh];
     const int64_t blocks = ceil_div(out, S.rows) * ceil_div(batch, S.cols);
-    for (const int s : kSplits) {
-      const int64_t kps = ceil_div(ceil_div(in, s), 256) * 256;
-      if (ceil_div(in, kps) != s) continue;
-      if (s > 1 && x_bytes + align256(s * batch * out * 4) > kScratchBytes) break;
+    int64_t last_kps = 0;
+    for (const int want : kSplits) {
+      const int64_t kps = ceil_div(ceil_div(in, want), 256) * 256;
+      if (kps == last_kps) continue;
+      last_kps = kps;
+      const int64_t s = ceil_div(in, kps);
+      if (s > 1 && x_bytes + align256(s * batch * out * 4) > kScratchBytes &&
+          qgemm64_workspace_bytes(batch, out, in, g, bits) <= kScratchBytes)
+        break;
       const double used = std::min(1.0, double(blocks * s) / 256.0);
       const double stage = (S.stage_few + (S.stage_full - S.stage_few) * used) * width;
       const double t = double(ceil_div(blocks * s, 256)) *
                            (double(kps) / 64 * stage + double(kps) / g * S.unit + 5.0) +
-                       (s > 1 ? 4.0 + double((2 * s + 1) * batch * out) * 1e-6 : 0.0);
+                       (s > 1 ? 4.0 + 0.09 * double(s) + double((2 * s + 1) * batch * out) * 1e-6
+                              : 0.0);
       if (t < best_t * 0.97) {
         best_t = t;
         best = WPlan{sh, kps, s};

@@ -83,3 +83,26 @@ def test_plan_starts_where_the_rule_says():
                                   (1, 256, 128, 8192): 33, (1, 16, 128, 4096): 65}.items():
         assert plan(p, n, first - 1, 512, inp, g)[0] == -1
         assert plan(p, n, first, 512, inp, g)[0] >= 0
+
+
+def test_plans_split_long_rows_and_keep_the_fixed_scratch_calls():
+    """Rows too long for the fixed scratch are split all the same; calls whose
+    64-column product fits in the scratch still fit."""
+    need64 = H.lib()["_ZN5higgs23qgemm64_workspace_bytesElllii"]
+    need64.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 2
+    need64.restype = ctypes.c_int64
+    scratch = 32 << 20
+    for batch, out, inp in ((127, 128, 131072), (129, 128, 131072), (300, 128, 65536),
+                            (250, 128, 65536), (2048, 512, 8192), (65, 1, 1 << 20)):
+        shape, splits = plan(2, 256, batch, out, inp, 1024)
+        tiles = -(-out // 128) * -(-batch // 128)
+        assert shape == 2 and tiles * splits >= 64, (batch, out, inp, splits)
+    kept = 0
+    for p, n, bits in ((2, 64, 6), (2, 256, 8), (2, 1024, 10), (1, 16, 8), (1, 256, 16)):
+        for batch in (65, 100, 128, 250, 500, 1000, 1900, 2040):
+            for out in (1, 128, 1000, 4096, 14336):
+                for inp in (1024, 4096, 8192, 14336, 32768, 65536, 130048, 131072, 262144):
+                    if need64(batch, out, inp, 1024, bits) <= scratch:
+                        kept += 1
+                        assert H.qmatmul_workspace_bytes(batch, out, inp, p, n, 1024) <= scratch
+    assert kept > 500
