@@ -159,8 +159,19 @@ __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restric
     for (int l = 0; l < kMaxGroup; ++l) {
       if (l >= nl) break;  // uniform
       float v[E];
+      if constexpr (ROT) {
+        // (opaque: kept as they are, not as one 64-lane mask per element, which
+        // overflow the scalar registers from g = 1024)
+        uint32_t bits[2] = {uint32_t(neg[l]), uint32_t(neg[l] >> 32)};
+        asm volatile("" : "+v"(bits[0]), "+v"(bits[1]));
 #pragma unroll
-      for (int i = 0; i < E; ++i) v[i] = ROT && ((neg[l] >> i) & 1) ? -u[i] : u[i];
+        for (int i = 0; i < E; ++i)
+          v[i] = __uint_as_float(__float_as_uint(u[i]) ^
+                                 ((bits[i / 32] << (31 - i % 32)) & 0x80000000u));
+      } else {
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[i] = u[i];
+      }
       if constexpr (ROT) {
         if constexpr (kLds)
           fwht1024_lds(v, s_rot[wave], lane);
