@@ -87,7 +87,10 @@ __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restric
   if constexpr (ROT) wave = __builtin_amdgcn_readfirstlane(wave);
   const int64_t gpr = in / g, ngroups = batch * gpr;
   const int64_t nwaves = int64_t(gridDim.x) * W;
-  const int nl = seeds.nl;
+  // the layers of this block's groups: all of them, or one (a row of the grid
+  // per layer)
+  const int l0 = gridDim.y > 1 ? int(blockIdx.y) : 0;
+  const int l1 = gridDim.y > 1 ? l0 + 1 : seeds.nl;
   int64_t grp = int64_t(blockIdx.x) * W + wave;
   const auto row_of = [gpr](int64_t i) HIGGS_INLINE {
     if (ROT && (i >> 32) == 0) return int64_t(uint32_t(i) / uint32_t(gpr));
@@ -109,8 +112,8 @@ __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restric
   }
   uint64_t neg[kMaxGroup] = {0, 0, 0, 0};  // of the lane's E elements
   if constexpr (ROT) {
-    for (int w = wave; w < nl * E; w += W) {
-      const int l = w / E, q = w % E;
+    for (int w = wave; w < (l1 - l0) * E; w += W) {
+      const int l = l0 + w / E, q = w % E;
       uint64_t seed = seeds.s[0];
 #pragma unroll
       for (int k = 1; k < kMaxGroup; ++k)
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restric
     __syncthreads();
 #pragma unroll
     for (int l = 0; l < kMaxGroup; ++l)
-      if (l < nl) neg[l] = s_neg[l][lane * E / 64] >> (lane * E % 64);
+      if (l >= l0 && l < l1) neg[l] = s_neg[l][lane * E / 64] >> (lane * E % 64);
   }
   while (grp < ngroups) {
     const int64_t cur = grp;
@@ -157,7 +160,8 @@ __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restric
     }
 #pragma unroll
     for (int l = 0; l < kMaxGroup; ++l) {
-      if (l >= nl) break;  // uniform
+      if (l >= l1) break;  // uniform
+      if (l < l0) continue;
       float v[E];
       if constexpr (ROT) {
         // (opaque: kept as they are, not as one 64-lane mask per element, which
@@ -841,16 +845,19 @@ hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, con
   const bool big = ROT && g <= 1024 && groups >= 4096;
   const int w = big ? 16 : 4;
   const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((groups + w - 1) / w, 8192 / w));
+  // few groups: a wave makes one layer's copy of its groups, not all of them
+  const unsigned rows = big ? 1 : unsigned(seeds.nl);
   switch (g) {
 #define HIGGS_XPREP(G)                                                                         \
   case G:                                                                                      \
     if (big)                                                                                   \
       hipLaunchKernelGGL((xprep_wide_kernel<G / 64, InT, ROT, ROT && G <= 1024 ? 16 : 4>),     \
-                         dim3(unsigned(blocks)), dim3(1024), 0, stream, x, batch, in, seeds,   \
-                         rscale, x16, xe);                                                     \
+                         dim3(unsigned(blocks), rows), dim3(1024), 0, stream, x, batch, in,    \
+                         seeds, rscale, x16, xe);                                                     \
     else                                                                                       \
-      hipLaunchKernelGGL((xprep_wide_kernel<G / 64, InT, ROT, 4>), dim3(unsigned(blocks)),     \
-                         dim3(256), 0, stream, x, batch, in, seeds, rscale, x16, xe);          \
+      hipLaunchKernelGGL((xprep_wide_kernel<G / 64, InT, ROT, 4>),                             \
+                         dim3(unsigned(blocks), rows), dim3(256), 0, stream, x, batch, in,     \
+                         seeds, rscale, x16, xe);                                              \
     return hipGetLastError();
     HIGGS_XPREP(64)
     HIGGS_XPREP(128)
