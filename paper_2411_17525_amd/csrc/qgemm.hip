@@ -957,81 +957,6 @@ __global__ __launch_bounds__(kThreads * KG) void qgemm_kernel(const QG a) {
   }
 }
 
-// The layers' partial products of one launch: layer l's [splits[l]][n[l]]
-// at part[l], its output (n[l] floats) at y[l]; off[l] = n[0] + ... +
-// n[l - 1]. A layer without a K-split has n[l] = 0 (its product wrote y), so
-// index i belongs to the last layer l with off[l] <= i.
-struct RG {
-  const float* part[kMaxGroup];
-  float* y[kMaxGroup];
-  int64_t n[kMaxGroup];
-  int64_t off[kMaxGroup + 1];
-  int splits[kMaxGroup];
-  int nl;
-};
-
-// y = sum over splits of the partial products, in split order.
-__global__ __launch_bounds__(256) void qgemm_reduce(const RG r) {
-  // every argument in one round trip; the layer of an index is then picked
-  // by selects (an indexed read would be a second round trip)
-  const float* part_l[kMaxGroup];
-  float* y_l[kMaxGroup];
-  int64_t n_l[kMaxGroup], off_l[kMaxGroup + 1];
-  int splits_l[kMaxGroup];
-#pragma unroll
-  for (int l = 0; l < kMaxGroup; ++l) {
-    part_l[l] = r.part[l];
-    y_l[l] = r.y[l];
-    n_l[l] = r.n[l];
-    off_l[l] = r.off[l];
-    splits_l[l] = r.splits[l];
-  }
-  off_l[kMaxGroup] = r.off[kMaxGroup];
-  const int nl = r.nl;
-  static_assert(kMaxGroup == 4, "the read below names four layers");
-  HIGGS_READ_NOW("s"(part_l[0]), "s"(part_l[1]), "s"(part_l[2]), "s"(part_l[3]), "s"(y_l[0]),
-                 "s"(y_l[1]), "s"(y_l[2]), "s"(y_l[3]), "s"(n_l[0]), "s"(n_l[1]), "s"(n_l[2]),
-                 "s"(n_l[3]), "s"(off_l[1]), "s"(off_l[2]), "s"(off_l[3]), "s"(off_l[4]),
-                 "s"(splits_l[0]), "s"(splits_l[1]), "s"(splits_l[2]), "s"(splits_l[3]),
-                 "s"(nl), "s"(gridDim.x));
-  int64_t total = off_l[1];
-#pragma unroll
-  for (int l = 2; l <= kMaxGroup; ++l)
-    if (l == nl) total = off_l[l];
-  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < total;
-       i += int64_t(gridDim.x) * 256) {
-    int L = 0;
-#pragma unroll
-    for (int l = 1; l < kMaxGroup; ++l)
-      if (l < nl && i >= off_l[l]) L = l;
-    const float* part = part_l[0];
-    float* y = y_l[0];
-    int64_t n = n_l[0], j = i;
-    int splits = splits_l[0];
-#pragma unroll
-    for (int l = 1; l < kMaxGroup; ++l)
-      if (L == l) {
-        part = part_l[l];
-        y = y_l[l];
-        n = n_l[l];
-        j = i - off_l[l];
-        splits = splits_l[l];
-      }
-    // loads eight splits at a time (one memory round trip for up to eight),
-    // adds in split order starting from split 0's value
-    float s = 0.f;
-    for (int k = 0; k < splits; k += 8) {
-      float v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = part[int64_t(min(k + q, splits - 1)) * n + j];
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (k + q < splits) s = k + q == 0 ? v[q] : s + v[q];
-    }
-    y[j] = s;
-  }
-}
-
 // Throughput of a block with two K-groups relative to the 64-cycle rate of
 // one matrix instruction per wave that the split model was built on
 // (measured on the 8B shapes at batch 16-64: 1.0 keeps gate/up unsplit and

@@ -714,26 +714,6 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void qgemm_wide_kernel(con
   }
 }
 
-// y = sum over splits of the partial products, in split order (split 0's
-// value first); one element per thread, grid-stride. Eight splits' values are
-// requested at a time: a layer of few outputs is bound by the round trips.
-__global__ __launch_bounds__(256) void wide_reduce_kernel(const float* __restrict__ part,
-                                                          int64_t n, int splits,
-                                                          float* __restrict__ y) {
-  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
-    float s = 0.f;
-    for (int k = 0; k < splits; k += 8) {
-      float v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = part[int64_t(min(k + q, splits - 1)) * n + i];
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (k + q < splits) s = k + q == 0 ? v[q] : s + v[q];
-    }
-    y[i] = s;
-  }
-}
-
 int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
 
 int pair_bits(int p, int n) { return p == 1 ? 2 * code_bits(p, n) : code_bits(p, n); }
@@ -1019,14 +999,20 @@ hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64
     }
     if (err != hipSuccess) return err;
   }
+  // the split layers' partial sums, all in one launch
+  RG r{};
+  r.nl = layers;
   for (int l = 0; l < layers; ++l) {
-    if (plan[l].splits == 1) continue;
-    const int64_t count = batch * outs[l];
-    const int64_t blocks = std::min<int64_t>((count + 255) / 256, 8192);
-    hipLaunchKernelGGL(wide_reduce_kernel, dim3(unsigned(blocks)), dim3(256), 0, stream, part[l],
-                       count, int(plan[l].splits), y[l]);
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
+    r.part[l] = part[l];
+    r.y[l] = y[l];
+    r.n[l] = plan[l].splits > 1 ? batch * outs[l] : 0;
+    r.splits[l] = int(plan[l].splits);
+    r.off[l + 1] = r.off[l] + r.n[l];
+  }
+  if (r.off[layers] > 0) {
+    const int64_t blocks = std::min<int64_t>((r.off[layers] + 255) / 256, 8192);
+    hipLaunchKernelGGL(qgemm_reduce, dim3(unsigned(blocks)), dim3(256), 0, stream, r);
+    return hipGetLastError();
   }
   return hipSuccess;
 }
