@@ -246,17 +246,26 @@ __host__ __device__ inline WideRange wide_range(int in, int kps, int split, int 
 
 // One launch covers nl layers (1..kMaxGroup) that read the same activations.
 // Work items are numbered layer by layer, row tile by row tile, then by
-// K-split, then by column tile; XCD x (blocks are dealt to the XCDs round
-// robin) takes the x-th eighth of them, so that the column tiles that decode
-// the same codes, and neighbouring row tiles, which read the same
-// activations, run on one XCD and meet in its L2.
+// K-split, then by column tile. Consecutive layers with items of one length
+// form a run; XCD x (blocks are dealt to the XCDs round robin) takes the x-th
+// eighth of each run, so that the column tiles that decode the same codes, and
+// neighbouring row tiles, which read the same activations, run on one XCD and
+// meet in its L2, and every XCD has its part of the longest items, which come
+// first. (With eighths of all items together some XCDs had only long ones:
+// 8192, 1024 and 1024 rows x 8192, 10-bit codes, g = 128, 257 batch rows 410 us,
+// 176 now, 250 in 64-column launches; with every layer dealt by itself each
+// XCD reads every layer's copy of the activations: four layers of 512 x 1024 at
+// 700 rows 28.9 -> 31.4 us.)
 struct QW {
   const _Float16* x16;  // copy c: + c * x16_stride
   const float* xe;      // [batch][gpr] powers of two (copy c: + c * xe_stride)
   int64_t x16_stride, xe_stride;
   const float* grid;
-  int batch, pair_table, log2g, in, gpr, nl, ctiles, items;
+  int batch, pair_table, log2g, in, gpr, nl, ctiles;
   int item0[kMaxGroup];   // layer l's first work item
+  int run0[kMaxGroup];    // its run's first work item
+  int run[kMaxGroup];     // its run's number of work items
+  int turn0[kMaxGroup];   // blocks per XCD before its run's first
   int xcopy[kMaxGroup];   // the layer's copy of the activations
   int kps[kMaxGroup];     // weights of K per split (a multiple of 256)
   int splits[kMaxGroup];
@@ -315,9 +324,18 @@ __global__ __launch_bounds__(64 * kWaves, kWaves / 4) void qgemm_wide_kernel(con
   const int ahalf = lane >> 5;
 
   // ---- work item ----
-  const int per = a.items / 8, rem = a.items % 8;
-  const int xcd = int(blockIdx.x) % 8;
-  const int item = xcd * per + min(xcd, rem) + int(blockIdx.x) / 8;
+  const int xcd = int(blockIdx.x) % 8, turn = int(blockIdx.x) / 8;
+  int run0 = 0, run = a.run[0], turn0 = 0;
+#pragma unroll
+  for (int l = 1; l < kMaxGroup; ++l)
+    if (l < a.nl && turn >= a.turn0[l]) {
+      run0 = a.run0[l];
+      run = a.run[l];
+      turn0 = a.turn0[l];
+    }
+  const int per = run / 8, rem = run % 8;
+  if (turn - turn0 >= per + int(xcd < rem)) return;  // the run's last turn is not full
+  const int item = run0 + xcd * per + min(xcd, rem) + turn - turn0;
   int L = 0;
 #pragma unroll
   for (int l = 1; l < kMaxGroup; ++l)
@@ -853,8 +871,8 @@ hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, con
 }
 
 template <int BITS, int NB, int CW, int KG, int W, bool G64>
-hipError_t launch_shape(const QW& a, hipStream_t stream) {
-  hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, CW, KG, W, G64>), dim3(unsigned(a.items)),
+hipError_t launch_shape(const QW& a, unsigned blocks, hipStream_t stream) {
+  hipLaunchKernelGGL((qgemm_wide_kernel<BITS, NB, CW, KG, W, G64>), dim3(blocks),
                      dim3(64 * W), 0, stream, a);
   return hipGetLastError();
 }
@@ -862,22 +880,22 @@ hipError_t launch_shape(const QW& a, hipStream_t stream) {
 // The shapes that plan_wide gives a code width and group size (g = 64 exists
 // for scalar grids only; up to 64 rows, shape 3, so do the calls).
 template <int BITS>
-hipError_t launch_bits(const QW& a, int shape, hipStream_t stream) {
+hipError_t launch_bits(const QW& a, int shape, unsigned blocks, hipStream_t stream) {
   constexpr bool kScalar = BITS == 8 || BITS == 16;
   if (a.log2g == 6) {
     if constexpr (kScalar) {
-      if (shape == 1) return launch_shape<BITS, 2, 2, 1, 8, true>(a, stream);
-      if (shape == 2) return launch_shape<BITS, 2, 2, 2, 8, true>(a, stream);
-      if (shape == 3) return launch_shape<BITS, 2, 1, 4, 8, true>(a, stream);
+      if (shape == 1) return launch_shape<BITS, 2, 2, 1, 8, true>(a, blocks, stream);
+      if (shape == 2) return launch_shape<BITS, 2, 2, 2, 8, true>(a, blocks, stream);
+      if (shape == 3) return launch_shape<BITS, 2, 1, 4, 8, true>(a, blocks, stream);
     }
     return hipErrorInvalidValue;
   }
-  if (shape == 0) return launch_shape<BITS, 4, 1, 1, 4, false>(a, stream);
-  if (shape == 2) return launch_shape<BITS, 2, 2, 2, 8, false>(a, stream);
+  if (shape == 0) return launch_shape<BITS, 4, 1, 1, 4, false>(a, blocks, stream);
+  if (shape == 2) return launch_shape<BITS, 2, 2, 2, 8, false>(a, blocks, stream);
   if constexpr (BITS != 10)
-    if (shape == 1) return launch_shape<BITS, 2, 2, 1, 8, false>(a, stream);
+    if (shape == 1) return launch_shape<BITS, 2, 2, 1, 8, false>(a, blocks, stream);
   if constexpr (BITS == 16)
-    if (shape == 3) return launch_shape<BITS, 2, 1, 4, 8, false>(a, stream);
+    if (shape == 3) return launch_shape<BITS, 2, 1, 4, 8, false>(a, blocks, stream);
   return hipErrorInvalidValue;
 }
 
@@ -959,6 +977,10 @@ hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64
     plan[l] = plan_wide(batch, outs[l], in, g, bits);
     part[l] = plan[l].splits > 1 ? reinterpret_cast<float*>(ws + L.part[l]) : y[l];
   }
+  int order[kMaxGroup];  // longest work items first
+  for (int l = 0; l < layers; ++l) order[l] = l;
+  std::stable_sort(order, order + layers,
+                   [&](int a, int b) { return plan[a].kps > plan[b].kps; });
   // one launch per block shape that the layers use
   for (int shape = 0; shape < kShapes; ++shape) {
     QW a{};
@@ -973,13 +995,26 @@ hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64
     a.in = int(in);
     a.gpr = int(in / g);
     a.ctiles = int(ceil_div(batch, kShape[shape].cols));
-    int64_t items = 0;
-    for (int l = 0; l < layers; ++l) {
+    int64_t items = 0, turns = 0, run = 0;
+    for (int i = 0; i < layers; ++i) {
+      const int l = order[i];
       if (plan[l].shape != shape) continue;
       const int k = a.nl++;
+      if (k == 0 || a.kps[k - 1] != int(plan[l].kps)) {
+        turns += ceil_div(run, 8);
+        run = 0;
+        a.run0[k] = int(items);
+      } else {
+        a.run0[k] = a.run0[k - 1];
+      }
+      a.turn0[k] = int(turns);
       a.item0[k] = int(items);
-      items += ceil_div(outs[l], kShape[shape].rows) * plan[l].splits * a.ctiles;
-      if (items >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+      const int64_t n = ceil_div(outs[l], kShape[shape].rows) * plan[l].splits * a.ctiles;
+      items += n;
+      run += n;
+      if (8 * turns + run >= (int64_t(1) << 31) - 8) return hipErrorInvalidValue;
+      for (int j = 0; j <= k; ++j)
+        if (a.run0[j] == a.run0[k]) a.run[j] = int(run);
       a.xcopy[k] = nx > 1 ? l : 0;
       a.kps[k] = int(plan[l].kps);
       a.splits[k] = int(plan[l].splits);
@@ -989,12 +1024,12 @@ hipError_t launch_qgemm_wide(const void* x, int x_kind, int layers, const uint64
       a.dst[k] = part[l];
     }
     if (a.nl == 0) continue;
-    a.items = int(items);
+    turns += ceil_div(run, 8);
     switch (bits) {
-      case 6: err = launch_bits<6>(a, shape, stream); break;
-      case 8: err = launch_bits<8>(a, shape, stream); break;
-      case 10: err = launch_bits<10>(a, shape, stream); break;
-      case 16: err = launch_bits<16>(a, shape, stream); break;
+      case 6: err = launch_bits<6>(a, shape, unsigned(8 * turns), stream); break;
+      case 8: err = launch_bits<8>(a, shape, unsigned(8 * turns), stream); break;
+      case 10: err = launch_bits<10>(a, shape, unsigned(8 * turns), stream); break;
+      case 16: err = launch_bits<16>(a, shape, unsigned(8 * turns), stream); break;
       default: return hipErrorInvalidValue;
     }
     if (err != hipSuccess) return err;

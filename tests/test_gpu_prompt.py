@@ -202,3 +202,32 @@ def test_prompt_group_and_noalloc_match_single_calls():
     for (codes, scales, seed, out), y in zip(layers, ys):
         assert torch.equal(y, H.qmatmul_fused(x, codes, scales, grid, g, seed, out))
         assert torch.equal(y, H.qmatmul_fused_noalloc(x, codes, scales, grid, g, seed, out))
+
+
+# layers of one call: K-splits of several lengths in one launch, with numbers of
+# work items that are no multiple of eight; equal layers; one split layer among
+# unsplit ones; one group per row
+GROUPS = [
+    (2, 1024, 128, 257, 8192, (8192, 260, 130)),
+    (2, 256, 1024, 65, 4096, (4096, 1024, 1000)),
+    (1, 16, 64, 33, 1024, (512, 512, 512, 512)),
+    (1, 256, 128, 130, 2048, (17000, 129, 900)),
+    (2, 64, 4096, 65, 4096, (300, 100, 200)),
+]
+
+
+@pytest.mark.parametrize("p,n,g,batch,inp,outs", GROUPS)
+def test_prompt_groups_match_single_calls(p, n, g, batch, inp, outs):
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] prompt group p={p} n={n} batch={batch} {outs}x{inp} g={g}",
+          file=sys.stderr, flush=True)
+    grid = torch.from_numpy(grid_f32(p, n)).cuda()
+    x = torch.randn((batch, inp), device="cuda").to(torch.bfloat16)
+    layers = []
+    for k, out in enumerate(outs):
+        codes, scales, _ = make_layer(p, n, out, inp, g, 20 + k)
+        layers.append((codes, scales, 40 + k, out))
+    for call in (layers, [(c, sc, 9, out) for c, sc, _, out in layers]):  # own and shared seeds
+        ys = H.qmatmul_fused_multi(x, call, grid, g)
+        for (codes, scales, seed, out), y in zip(call, ys):
+            assert torch.equal(y, H.qmatmul_fused(x, codes, scales, grid, g, seed, out))

@@ -76,6 +76,22 @@ def test_gpu_cases_reach_every_plan(p, n):
     assert not missing, missing
 
 
+def test_gpu_groups_mix_splits():
+    """Among the groups of the GPU tests: layers of one block shape with
+    different and with equal K-splits, split and unsplit layers."""
+    pytest.importorskip("torch")
+    from test_gpu_prompt import GROUPS
+    mixed = same = some = 0
+    for p, n, g, batch, inp, outs in GROUPS:
+        plans = [plan(p, n, batch, out, inp, g) for out in outs]
+        assert all(s >= 0 for s, _ in plans)
+        by_shape = {s: {k for t, k in plans if t == s} for s, _ in plans}
+        mixed += any(len(v) > 1 for v in by_shape.values())
+        same += len(set(plans)) == 1
+        some += {k > 1 for _, k in plans} == {False, True}
+    assert mixed and same and some
+
+
 def test_plan_starts_where_the_rule_says():
     for (p, n, g, inp), first in {(2, 256, 1024, 4096): 65, (1, 16, 64, 4096): 17,
                                   (1, 16, 64, 6208): 49, (1, 256, 64, 4096): 9,
