@@ -327,7 +327,16 @@ higgs_status higgs_rht_activations(const void *x, higgs_dtype x_dtype, int64_t b
  *   y         [out] device, batch*out floats, row-major [batch][out].
  *   workspace [in]  device scratch of at least
  *                   higgs_qmatmul_workspace_bytes(...) bytes (may be NULL
- *                   when that is 0); its contents are not preserved.
+ *                   when that is 0); its contents are not preserved. On the
+ *                   matrix-core path it holds the fp16 activations (batch *
+ *                   in * 2 bytes and their exponents) and the partial sums of
+ *                   rows split along `in` (up to tens of MiB). The size does
+ *                   not always grow with the batch: above 64 rows (above 8
+ *                   with g = 64, 32 with g = 128 and (1,256)) smaller batches
+ *                   are split more. A call there also takes a smaller
+ *                   workspace, of the size that a larger batch asks for, and
+ *                   is then computed in steps of 64 rows: slower, and rounded
+ *                   in another order.
  * Requires batch >= 1, out >= 1, in % g == 0, (p, n) supported, 64*p <= g
  * <= 4096, x_rot finite with magnitudes below 2^100. in <= 32768 for every
  * format unless the call takes the matrix-core path (in <= 2^23 there);
@@ -381,7 +390,8 @@ higgs_status higgs_qmatmul_fused(const void *x, higgs_dtype x_dtype, int64_t bat
  * allocating library routine); the first call on a device resolves the
  * array's device address (hipGetSymbolAddress) and keeps it.
  *   - Calls whose workspace (higgs_qmatmul_fused_workspace_bytes) exceeds
- *     the scratch return HIGGS_ERR_UNSUPPORTED with nothing enqueued.
+ *     the scratch return HIGGS_ERR_UNSUPPORTED with nothing enqueued, unless
+ *     the call takes a smaller one (see higgs_qmatmul) that fits.
  *   - All calls on one device share its scratch: calls that overlap on one
  *     device (concurrent streams, several host threads) race and may corrupt
  *     each other's results. Serialise them, e.g. on one stream.

@@ -325,7 +325,9 @@ higgs_status higgs_qmatmul(const float* x_rot, int64_t batch, const uint8_t* cod
   higgs_status st = check_layer(p, n, g, out, in);
   if (st == HIGGS_OK) st = check_product(batch, p, n, in, g);
   if (st != HIGGS_OK) return st;
-  const int64_t need = higgs_qmatmul_workspace_bytes(batch, out, in, p, n, g);
+  const bool matrix_cores = higgs::use_qgemm(batch, p, n, in, g);
+  const int64_t need =
+      matrix_cores ? higgs::qgemm_least_workspace_bytes(batch, out, in, p, n, g) : 0;
   if (workspace_bytes < need || (need > 0 && workspace == nullptr))
     return fail(HIGGS_ERR_INVALID_ARG, "workspace too small: %lld bytes needed",
                 (long long)need);
@@ -334,9 +336,10 @@ higgs_status higgs_qmatmul(const float* x_rot, int64_t batch, const uint8_t* cod
     return fail(HIGGS_ERR_INVALID_ARG,
                 "x_rot, codes and workspace must be 16-byte aligned, y and grid 4, scales 2");
   const hipError_t err =
-      higgs::use_qgemm(batch, p, n, in, g)
+      matrix_cores
           ? higgs::launch_qgemm(x_rot, higgs::kQgemmRotated, 0, batch, codes, scales, grid, p, n, g,
-                                out, in, y, workspace, static_cast<hipStream_t>(stream))
+                                out, in, y, workspace, workspace_bytes,
+                                static_cast<hipStream_t>(stream))
           : higgs::launch_qgemv(x_rot, batch, codes, scales, grid, p, n, g, out, in, y,
                                 static_cast<hipStream_t>(stream));
   return device_status(err, "higgs_qmatmul launch");
@@ -356,7 +359,7 @@ int64_t higgs_qmatmul_fused_workspace_bytes(int64_t batch, int64_t out, int64_t 
 }  // extern "C"
 
 // Validation of higgs_qmatmul_fused's arguments (also per layer of
-// higgs_qmatmul_fused_multi); returns the workspace the call needs in *need.
+// higgs_qmatmul_fused_multi); returns the least workspace of the call in *need.
 // check_ws = false skips the checks of the caller's workspace (the
 // allocation-free entry point brings its own).
 static higgs_status check_fused(const void* x, higgs_dtype x_dtype, int64_t batch,
@@ -372,7 +375,9 @@ static higgs_status check_fused(const void* x, higgs_dtype x_dtype, int64_t batc
   higgs_status st = check_layer(p, n, g, out, in);
   if (st == HIGGS_OK) st = check_product(batch, p, n, in, g);
   if (st != HIGGS_OK) return st;
-  *need = higgs_qmatmul_fused_workspace_bytes(batch, out, in, p, n, g);
+  *need = higgs::use_qgemm(batch, p, n, in, g)
+              ? higgs::qgemm_least_workspace_bytes(batch, out, in, p, n, g)
+              : higgs_qmatmul_fused_workspace_bytes(batch, out, in, p, n, g);
   if (check_ws && (workspace_bytes < *need || (*need > 0 && workspace == nullptr)))
     return fail(HIGGS_ERR_INVALID_ARG, "workspace too small: %lld bytes needed",
                 (long long)*need);
@@ -387,11 +392,12 @@ static higgs_status check_fused(const void* x, higgs_dtype x_dtype, int64_t batc
 static higgs_status run_fused(const void* x, higgs_dtype x_dtype, int64_t batch,
                               const uint8_t* codes, const uint16_t* scales, const float* grid,
                               int p, int n, int g, uint64_t rht_seed, int64_t out, int64_t in,
-                              float* y, void* workspace, int64_t need, hipStream_t s) {
+                              float* y, void* workspace, int64_t workspace_bytes, int64_t need,
+                              hipStream_t s) {
   if (higgs::use_qgemm(batch, p, n, in, g)) {
     const hipError_t err = higgs::launch_qgemm(
         x, x_dtype == HIGGS_BF16 ? higgs::kQgemmRawBF16 : higgs::kQgemmRawF32, rht_seed, batch,
-        codes, scales, grid, p, n, g, out, in, y, workspace, s);
+        codes, scales, grid, p, n, g, out, in, y, workspace, workspace_bytes, s);
     return device_status(err, "higgs_qmatmul_fused launch");
   }
   if (need == 0) {
@@ -418,7 +424,7 @@ higgs_status higgs_qmatmul_fused(const void* x, higgs_dtype x_dtype, int64_t bat
                                       workspace, workspace_bytes, &need);
   if (st != HIGGS_OK) return st;
   return run_fused(x, x_dtype, batch, codes, scales, grid, p, n, g, rht_seed, out, in, y,
-                   workspace, need, static_cast<hipStream_t>(stream));
+                   workspace, workspace_bytes, need, static_cast<hipStream_t>(stream));
 }
 
 higgs_status higgs_qmatmul_fused_noalloc(const void* x, higgs_dtype x_dtype, int64_t batch,
@@ -441,7 +447,7 @@ higgs_status higgs_qmatmul_fused_noalloc(const void* x, higgs_dtype x_dtype, int
     if (err != hipSuccess) return device_status(err, "higgs_qmatmul_fused_noalloc scratch");
   }
   return run_fused(x, x_dtype, batch, codes, scales, grid, p, n, g, rht_seed, out, in, y, ws,
-                   need, static_cast<hipStream_t>(stream));
+                   higgs::kScratchBytes, need, static_cast<hipStream_t>(stream));
 }
 
 int64_t higgs_qmatmul_fused_multi_workspace_bytes(int layers, int64_t batch, const int64_t* out,
@@ -477,7 +483,9 @@ higgs_status higgs_qmatmul_fused_multi(int layers, const void* x, higgs_dtype x_
     if (st != HIGGS_OK) return fail(st, "layer %d: %s", l, higgs_last_error());
   }
   const int64_t need_all =
-      higgs_qmatmul_fused_multi_workspace_bytes(layers, batch, out, in, p, n, g);
+      higgs::use_qgemm(batch, p, n, in, g)
+          ? higgs::qgemm_group_least_workspace_bytes(layers, batch, out, in, p, n, g)
+          : higgs_qmatmul_fused_multi_workspace_bytes(layers, batch, out, in, p, n, g);
   if (workspace_bytes < need_all || (need_all > 0 && workspace == nullptr))
     return fail(HIGGS_ERR_INVALID_ARG, "workspace too small: %lld bytes needed",
                 (long long)need_all);
@@ -486,7 +494,7 @@ higgs_status higgs_qmatmul_fused_multi(int layers, const void* x, higgs_dtype x_
   if (higgs::use_qgemm(batch, p, n, in, g)) {  // shared activation conversion
     const hipError_t err = higgs::launch_qgemm_group(
         x, x_bf16 ? higgs::kQgemmRawBF16 : higgs::kQgemmRawF32, layers, rht_seeds, batch, codes,
-        scales, grid, p, n, g, out, in, y, workspace, s);
+        scales, grid, p, n, g, out, in, y, workspace, workspace_bytes, s);
     return device_status(err, "higgs_qmatmul_fused_multi launch");
   }
   if (need_all == 0) {  // rotation inside the small-batch product: one launch
@@ -496,7 +504,8 @@ higgs_status higgs_qmatmul_fused_multi(int layers, const void* x, higgs_dtype x_
   }
   for (int l = 0; l < layers; ++l) {
     const higgs_status st = run_fused(x, x_dtype, batch, codes[l], scales[l], grid, p, n, g,
-                                      rht_seeds[l], out[l], in, y[l], workspace, need[l], s);
+                                      rht_seeds[l], out[l], in, y[l], workspace, workspace_bytes,
+                                      need[l], s);
     if (st != HIGGS_OK) return st;
   }
   return ok();

@@ -144,30 +144,36 @@ bool qgemv_rotates(int p, int n, int g);
 constexpr int kQgemmRotated = 0;
 constexpr int kQgemmRawF32 = 1;
 constexpr int kQgemmRawBF16 = 2;
+// _workspace_bytes: what a caller is asked for. A call takes any workspace of at
+// least _least_workspace_bytes; launch_qgemm[_group] computes prompt-sized
+// batches in 64-column launches where the workspace holds only those.
 int64_t qgemm_workspace_bytes(int64_t batch, int64_t out, int64_t in, int p, int n, int g);
+int64_t qgemm_least_workspace_bytes(int64_t batch, int64_t out, int64_t in, int p, int n, int g);
 hipError_t launch_qgemm(const void* x, int x_kind, uint64_t seed, int64_t batch,
                         const uint8_t* codes, const uint16_t* scales, const float* grid, int p,
                         int n, int g, int64_t out, int64_t in, float* y, void* workspace,
-                        hipStream_t stream);
+                        int64_t workspace_bytes, hipStream_t stream);
 
 // Up to 4 layers that read the same activations (own codes, scales, rows,
 // seed and output) in one activation conversion and, up to 64 batch rows, one
 // product launch and at most one reduction launch.
 int64_t qgemm_group_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
                                     int p, int n, int g);
+int64_t qgemm_group_least_workspace_bytes(int layers, int64_t batch, const int64_t* outs,
+                                          int64_t in, int p, int n, int g);
 hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint64_t* seeds,
                               int64_t batch, const uint8_t* const* codes,
                               const uint16_t* const* scales, const float* grid, int p, int n,
                               int g, const int64_t* outs, int64_t in, float* const* y,
-                              void* workspace, hipStream_t stream);
+                              void* workspace, int64_t workspace_bytes, hipStream_t stream);
 
 // The workspace of one layer's product in 64-column launches (qgemm.hip),
 // whichever path the call takes; pair_bits: code bits per pair of weights.
 int64_t qgemm64_workspace_bytes(int64_t batch, int64_t out, int64_t in, int g, int pair_bits);
 
 // The matrix-core product for prompt-sized batches (qgemm_wide.hip), same
-// arguments; launch_qgemm[_group] and the workspace sizes above go to it when
-// use_qgemm_wide says so.
+// arguments; launch_qgemm[_group] goes to it when use_qgemm_wide says so and
+// the workspace holds its plan.
 bool use_qgemm_wide(int64_t batch, int64_t in, int p, int n, int g);
 int64_t qgemm_wide_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
                                    int p, int n, int g);

@@ -1117,25 +1117,44 @@ int64_t qgemm64_workspace_bytes(int64_t batch, int64_t out, int64_t in, int g, i
 }
 
 int64_t qgemm_workspace_bytes(int64_t batch, int64_t out, int64_t in, int p, int n, int g) {
-  if (use_qgemm_wide(batch, in, p, n, g)) return qgemm_wide_workspace_bytes(1, batch, &out, in, p, n, g);
-  return qgemm64_workspace_bytes(batch, out, in, g, pair_bits(p, n));
+  return qgemm_group_workspace_bytes(1, batch, &out, in, p, n, g);
 }
+
+int64_t qgemm_least_workspace_bytes(int64_t batch, int64_t out, int64_t in, int p, int n, int g) {
+  return qgemm_group_least_workspace_bytes(1, batch, &out, in, p, n, g);
+}
+
+// A smaller prompt-sized batch can have a plan with more splits and so a larger
+// workspace, so a program that keeps the workspace of its largest batch brings
+// less than such a batch's plan takes. The 64-column launches take about the
+// same at every batch: asking for the larger of the two, and accepting the
+// smaller, leaves those calls valid.
 
 int64_t qgemm_group_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
                                     int p, int n, int g) {
   if (layers < 1 || layers > kMaxGroup) return -1;
-  if (use_qgemm_wide(batch, in, p, n, g)) return qgemm_wide_workspace_bytes(layers, batch, outs, in, p, n, g);
-  return layout(batch, outs, layers, layers, in, g, pair_bits(p, n)).total;
+  const int64_t need64 = layout(batch, outs, layers, layers, in, g, pair_bits(p, n)).total;
+  if (!use_qgemm_wide(batch, in, p, n, g)) return need64;
+  return std::max(need64, qgemm_wide_workspace_bytes(layers, batch, outs, in, p, n, g));
+}
+
+int64_t qgemm_group_least_workspace_bytes(int layers, int64_t batch, const int64_t* outs,
+                                          int64_t in, int p, int n, int g) {
+  if (layers < 1 || layers > kMaxGroup) return -1;
+  const int64_t need64 = layout(batch, outs, layers, layers, in, g, pair_bits(p, n)).total;
+  if (!use_qgemm_wide(batch, in, p, n, g)) return need64;
+  return std::min(need64, qgemm_wide_workspace_bytes(layers, batch, outs, in, p, n, g));
 }
 
 hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint64_t* seeds,
                               int64_t batch, const uint8_t* const* codes,
                               const uint16_t* const* scales, const float* grid, int p, int n,
                               int g, const int64_t* outs, int64_t in, float* const* y,
-                              void* workspace, hipStream_t stream) {
+                              void* workspace, int64_t workspace_bytes, hipStream_t stream) {
   if (!qgemm_format(p, n) || layers < 1 || layers > kMaxGroup)
     return hipErrorInvalidValue;
-  if (use_qgemm_wide(batch, in, p, n, g))
+  if (use_qgemm_wide(batch, in, p, n, g) &&
+      workspace_bytes >= qgemm_wide_workspace_bytes(layers, batch, outs, in, p, n, g))
     return launch_qgemm_wide(x, x_kind, layers, seeds, batch, codes, scales, grid, p, n, g, outs,
                              in, y, workspace, stream);
   const int bits = pair_bits(p, n);
@@ -1227,9 +1246,9 @@ hipError_t launch_qgemm_group(const void* x, int x_kind, int layers, const uint6
 hipError_t launch_qgemm(const void* x, int x_kind, uint64_t seed, int64_t batch,
                         const uint8_t* codes, const uint16_t* scales, const float* grid, int p,
                         int n, int g, int64_t out, int64_t in, float* y, void* workspace,
-                        hipStream_t stream) {
+                        int64_t workspace_bytes, hipStream_t stream) {
   return launch_qgemm_group(x, x_kind, 1, &seed, batch, &codes, &scales, grid, p, n, g, &out, in,
-                            &y, workspace, stream);
+                            &y, workspace, workspace_bytes, stream);
 }
 
 }  // namespace higgs

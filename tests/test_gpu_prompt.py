@@ -231,3 +231,35 @@ def test_prompt_groups_match_single_calls(p, n, g, batch, inp, outs):
         ys = H.qmatmul_fused_multi(x, call, grid, g)
         for (codes, scales, seed, out), y in zip(call, ys):
             assert torch.equal(y, H.qmatmul_fused(x, codes, scales, grid, g, seed, out))
+
+
+@pytest.mark.parametrize("p,n,g,out,inp,small,large", [
+    (2, 256, 1024, 4096, 4096, 160, 257), (2, 1024, 1024, 14336, 4096, 80, 129),
+    (1, 16, 64, 14336, 4096, 32, 129), (1, 256, 64, 1024, 1024, 160, 768)])
+def test_workspace_of_a_larger_batch(p, n, g, out, inp, small, large):
+    """A workspace kept for a larger batch, smaller than the small batch's plan
+    takes: the call computes the same product; a byte less than the least is
+    refused."""
+    from paper_2411_17525_amd import higgs as H
+    print(f"[gpu-case] kept workspace p={p} n={n} {out}x{inp} g={g} {small} of {large}",
+          file=sys.stderr, flush=True)
+    kept = H.qmatmul_fused_workspace_bytes(large, out, inp, p, n, g)
+    assert kept < H.qmatmul_fused_workspace_bytes(small, out, inp, p, n, g)
+    grid = torch.from_numpy(grid_f32(p, n)).cuda()
+    codes, scales, idx = make_layer(p, n, out, inp, g, 31)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+    x = torch.randn((small, inp), generator=gen, device="cuda")
+    x_rot = H.rht_activations(x, g, 3)
+    ws = torch.empty(kept, dtype=torch.uint8, device="cuda")
+    ref, _ = reference(x_rot, idx, scales, grid, g)
+    y = H.qmatmul(x_rot, codes, scales, grid, g, out, workspace=ws)
+    check_qmm(y.cpu().numpy(), ref.cpu().numpy())
+    assert torch.equal(y, H.qmatmul_fused(x, codes, scales, grid, g, 3, out, workspace=ws))
+    multi = H.qmatmul_fused_multi_workspace_bytes(large, (out, out), inp, p, n, g)
+    ws = torch.empty(multi, dtype=torch.uint8, device="cuda")
+    ys = H.qmatmul_fused_multi(x, [(codes, scales, 3, out)] * 2, grid, g, workspace=ws)
+    for y in ys:
+        check_qmm(y.cpu().numpy(), ref.cpu().numpy())
+    with pytest.raises(H.HiggsError):
+        H.qmatmul(x_rot, codes, scales, grid, g, out, workspace=ws[:small * inp * 2])

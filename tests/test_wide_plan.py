@@ -122,3 +122,35 @@ def test_plans_split_long_rows_and_keep_the_fixed_scratch_calls():
                         kept += 1
                         assert H.qmatmul_workspace_bytes(batch, out, inp, p, n, 1024) <= scratch
     assert kept > 500
+
+
+def test_workspace_of_a_larger_batch_is_taken():
+    """A program may keep the workspace of its largest batch: where the
+    64-column product's need for a batch is no larger, the call takes it, though
+    a smaller batch's plan may have more splits."""
+    def c_fn(name, types):
+        f = H.lib()[name]
+        f.argtypes, f.restype = types, ctypes.c_int64
+        return f
+    i64, i32 = ctypes.c_int64, ctypes.c_int
+    need64 = c_fn("_ZN5higgs23qgemm64_workspace_bytesElllii", [i64] * 3 + [i32] * 2)
+    least = c_fn("_ZN5higgs27qgemm_least_workspace_bytesElllii" + "i", [i64] * 3 + [i32] * 3)
+    group = c_fn("_ZN5higgs33qgemm_group_least_workspace_bytesEilPKlliii",
+                 [i32, i64, ctypes.c_void_p, i64, i32, i32, i32])
+    batches = (9, 17, 33, 64, 65, 80, 129, 160, 257, 300, 600, 2048)
+    larger_plan = 0
+    for p, n, bits, g in ((2, 64, 6, 1024), (2, 256, 8, 1024), (2, 1024, 10, 128),
+                          (1, 16, 8, 64), (1, 256, 16, 64), (1, 256, 16, 128)):
+        for out, inp in ((4096, 4096), (14336, 4096), (4096, 14336), (1024, 1024), (500, 8192)):
+            for i, small in enumerate(batches):
+                own = H.qmatmul_workspace_bytes(small, out, inp, p, n, g)
+                assert least(small, out, inp, p, n, g) <= own
+                for large in batches[i + 1:]:
+                    kept = H.qmatmul_workspace_bytes(large, out, inp, p, n, g)
+                    larger_plan += own > kept
+                    if need64(small, out, inp, g, bits) <= need64(large, out, inp, g, bits):
+                        assert least(small, out, inp, p, n, g) <= kept
+                        outs = (i64 * 2)(out, out)
+                        assert group(2, small, outs, inp, p, n, g) <= \
+                            H.qmatmul_fused_multi_workspace_bytes(large, (out, out), inp, p, n, g)
+    assert larger_plan > 50
