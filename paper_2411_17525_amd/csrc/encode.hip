@@ -539,11 +539,15 @@ __device__ inline void copy_to_lds(const uint8_t* src, void* dst, int bytes, int
 // on its own; 4096 x 4096 fp32, 1024 points, G = 256: 97 us
 // against 87; 256-point scalar grid, G = 128: 88 against 45). The waves of a
 // block share the grid and the index in LDS and then take their weights
-// independently (no block barrier after the prologue).
+// independently (no block barrier after the prologue). Without an index and
+// with few weights (`shared`: the block's waves would leave half the chip idle)
+// all the waves of a block take the same 1024 weights, each scans its part of
+// the points, and the first one writes the least: 16 x 4096 bf16 with 256 scalar
+// points, g = 64: 62 us -> 13, 1024 points, g = 128: 246 -> 28.
 template <int G, int P, int BITS, int kQW, typename InT>
 __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
     const InT* __restrict__ w, int64_t groups, uint64_t seed, const float* __restrict__ grid, int n,
-    const uint8_t* __restrict__ index, uint8_t* __restrict__ codes,
+    const uint8_t* __restrict__ index, bool shared, uint8_t* __restrict__ codes,
     uint16_t* __restrict__ scales) {
   constexpr int E = 16;           // weights per lane
   constexpr int kSeg = 64 * E;    // per wave and turn
@@ -559,6 +563,12 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
   constexpr IndexLayout kL = index_layout(P, kN);
   using CodeT = typename std::conditional<(BITS <= 8), uint8_t, uint16_t>::type;
 
+  // whether the waves of a block can share their weights (a scan of few points
+  // is short)
+  constexpr bool kShare = kN > 16;
+  // their values take the place of the lists, where those are large
+  constexpr bool kInList = kCap * 2 >= kSegCodes * 8;
+
   // the rotation's scratch, which then takes the codes
   static_assert(kFwhtRows * 4 >= int(kSegCodes * sizeof(CodeT)), "codes fit the scratch");
   __shared__ GridPt s_grid[kN];
@@ -566,6 +576,7 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
   __shared__ uint64_t s_neg[G / 64];
   __shared__ __align__(16) uint16_t s_off[align16((BK::kCells + 1) * 2) / 2];
   __shared__ __align__(16) uint16_t s_list[kCap];
+  __shared__ unsigned long long s_values[kShare && !kInList ? kSegCodes : 1];
   __shared__ double s_r2[kQW];
   __shared__ uint64_t s_hash[kQW];
 
@@ -643,8 +654,8 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
   // groups, their scales and their codes all lie back to back; the next turn's
   // weights are requested one turn ahead. Past the last group a lane has zeros.
   const int64_t segs = (groups + kSegGroups - 1) / kSegGroups;
-  const int64_t step = int64_t(gridDim.x) * kQW;
-  int64_t seg = int64_t(blockIdx.x) * kQW + wave;
+  const int64_t step = shared ? int64_t(gridDim.x) : int64_t(gridDim.x) * kQW;
+  int64_t seg = shared ? int64_t(blockIdx.x) : int64_t(blockIdx.x) * kQW + wave;
   RawGroup<E, InT> raw = {};
   auto request = [&](int64_t sg) {
     if (kSegGroups == 1 || sg * kSegGroups + lane / kGroupLanes < groups)
@@ -737,8 +748,10 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
     // waits for (14336 x 4096, 256 points: 247 us against 189; 4096 x 4096, 1024
     // points, g = 256: 268 against 110).
     if (!pruned) {
+      const int part = shared ? (n + kQW - 1) / kQW : n;
+      const int k0 = shared ? min(wave * part, n) : 0, k1 = min(k0 + part, n);
 #pragma unroll 4
-      for (int k = 0; k < n; ++k) {
+      for (int k = k0; k < k1; ++k) {
         const GridPt q = s_grid[k];
 #pragma unroll
         for (int j = 0; j < kVecPerLane; ++j) fold(j, k, q);
@@ -771,6 +784,33 @@ __global__ __launch_bounds__(64 * kQW) void quantize_kernel(
           b = wave_min(b, lane);
           if (lane == src) best[j] = b;
         }
+      }
+    }
+
+    if constexpr (kShare) {
+      if (shared) {
+        // least over the waves: search values are positive, so their bits are
+        // in their order
+        unsigned long long* const s_best =
+            kInList ? reinterpret_cast<unsigned long long*>(s_list) : s_values;
+        if (wave == 0) {
+#pragma unroll
+          for (int j = 0; j < kVecPerLane; ++j)
+            s_best[64 * j + lane] = __builtin_bit_cast(unsigned long long, best[j]);
+        }
+        __syncthreads();
+        if (wave != 0) {
+#pragma unroll
+          for (int j = 0; j < kVecPerLane; ++j)
+            atomicMin(&s_best[64 * j + lane], __builtin_bit_cast(unsigned long long, best[j]));
+        }
+        __syncthreads();
+        // (the others' next use of s_best is behind the barrier that the first
+        // wave reaches after this read)
+        if (wave != 0) continue;
+#pragma unroll
+        for (int j = 0; j < kVecPerLane; ++j)
+          best[j] = __builtin_bit_cast(double, s_best[64 * j + lane]);
       }
     }
 
@@ -1167,14 +1207,18 @@ hipError_t launch_bits(const InT* w, int64_t out, int64_t in, const float* grid,
   constexpr int kQW = P == 1 ? 8 : (BITS >= 8 ? 12 : 4);
   constexpr int64_t kMaxBlocks = kQW == 4 ? 2048 : 256;
   const int64_t segs = (total + std::max(1, 1024 / g) - 1) / std::max(1, 1024 / g);
-  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((segs + kQW - 1) / kQW, kMaxBlocks));
+  // no index and weights for at most half the compute units: the waves of a
+  // block share 1024 weights (quantize_kernel)
+  const bool shared = index == nullptr && BITS > 4 && segs <= 128 * kQW;
+  const int64_t blocks = std::max<int64_t>(
+      1, std::min<int64_t>(shared ? segs : (segs + kQW - 1) / kQW, kMaxBlocks));
   const dim3 grid_dim{unsigned(blocks)}, block{64 * kQW}, scan_block{64 * kWaves};
   switch (g) {
 #define HIGGS_Q_CASE(GV)                                                                     \
   case GV:                                                                                   \
     if constexpr (GV >= 64 * P) {                                                            \
       hipLaunchKernelGGL((quantize_kernel<GV, P, BITS, kQW, InT>), grid_dim, block, 0,       \
-                         stream, w, total, seed, grid, n, index, codes, scales);             \
+                         stream, w, total, seed, grid, n, index, shared, codes, scales);     \
       return hipGetLastError();                                                              \
     }                                                                                        \
     break;

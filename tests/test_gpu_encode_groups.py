@@ -106,3 +106,29 @@ def test_encode_at_the_last_bucket_edge(p, n, g):
     codes, scales = H.quantize(w, gd, g, 31)
     full, full_scales = H.quantize(w, gd, g, 31, index=False)
     assert torch.equal(codes, full) and torch.equal(scales, full_scales)
+
+
+# 1024-weight turns below, at and above the line where a block's waves share
+# their weights (512, 1024 and 1536 turns of blocks of 4, 8 and 12 waves), a last
+# turn that is not full, and more turns than blocks
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("p,n,line", [(1, 16, 1024), (1, 256, 1024), (2, 64, 512), (2, 256, 1536),
+                                      (2, 1024, 1536)])
+def test_few_rows_without_an_index(p, n, line, dtype):
+    from paper_2411_17525_amd import higgs as H
+    grid = torch.from_numpy(grid_f32(p, n)).cuda()
+    index = H.search_index(grid)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    for g in (64 * p, 256, 1024):
+        for out, inp in ((1, 1024), (3, 3072), (5, 1024 + g % 1024), (line, 1024),
+                         (line + 1, 1024), (300, 1024)):
+            print(f"[gpu-case] no index p={p} n={n} g={g} {out}x{inp} {dtype}", file=sys.stderr,
+                  flush=True)
+            w = torch.randn((out, inp), generator=gen, device="cuda")
+            w[0, :g] = 0  # a group of zeros
+            w = w if dtype == "f32" else w.to(torch.bfloat16)
+            codes, scales = H.quantize(w, grid, g, 5, index=False)[:2]
+            want, ws = H.quantize(w, grid, g, 5, index=index)[:2]
+            assert torch.equal(codes, want)
+            assert torch.equal(scales.view(torch.int16), ws.view(torch.int16))
