@@ -252,12 +252,16 @@ higgs_status higgs_layer_error(const void *W, higgs_dtype w_dtype, int64_t out, 
  * point of v sqrt(g) / s (lowest index on ties), and with e = v - (s /
  * sqrt(g)) G[q] and E = e U_pp^-1 (U_pp the diagonal p x p block of U) every
  * later column j moves by -E U[p-vector, j]. fp64 throughout; the update of a
- * block of 64 columns runs in the block, later columns are updated by one GEMM per
- * block. With a diagonal H the codes are those of higgs_quantize (up to the
+ * block of 64 columns runs in the block. Later columns get it from GEMMs, one
+ * after each block: after block b (from 0) the errors of the last 2^k blocks
+ * update the next 2^k blocks of columns, 2^k the largest power of two that
+ * divides b + 1, so every error reaches every later column before that is
+ * rounded. With a diagonal H the codes are those of higgs_quantize (up to the
  * fp64 rounding of the normalisation).
  *   factor     [in]  device, as written by higgs_gptq_factor for this `in`.
  *   workspace  device, >= higgs_quantize_gptq_workspace_bytes(out, in, g),
- *              256-byte aligned (rotated weights, norms, block errors: fp64).
+ *              256-byte aligned (rotated weights, which the errors E replace
+ *              block by block, and norms: fp64).
  * Requires the higgs_quantize conditions, out * in < 2^31, in <= 65536.
  * ------------------------------------------------------------------------- */
 int64_t higgs_gptq_factor_workspace_bytes(int64_t samples, int64_t in);
@@ -412,16 +416,20 @@ higgs_status higgs_qmatmul_fused_noalloc(const void *x, higgs_dtype x_dtype, int
  * up projections), each quantized on its own (own codes, scales, rows and
  * rotation seed, App. G):
  *   y[l] = x W_hat_l^T,  l < layers.
- * Bit-identical to one higgs_qmatmul_fused call per layer. When the rotation
+ * Bit-identical to one higgs_qmatmul_fused call per layer (workspaces of the
+ * sizes that the calls ask for). When the rotation
  * runs inside the small-batch product kernel (see higgs_qmatmul_fused) all
  * layers are computed by ONE launch: each block of the launch takes rows of
  * one layer, so the launch and prologue cost is paid once. On the
- * matrix-core path the layers share one activation conversion
- * launch (one rotated copy per distinct seed) and, up to 64 batch rows, one
- * product launch and at most one reduction launch; above, a product launch
- * per block shape that the layers use (at most three) and a reduction launch
- * per layer whose rows are split. Otherwise the layers are computed
- * one after another on the stream, sharing the workspace.
+ * matrix-core path the layers share one activation conversion launch (one
+ * rotated copy, or one per layer where their seeds differ), the product
+ * launches and at most one reduction launch: one product launch for batches
+ * up to 64 rows (with g = 64 up to 8 or 16 rows, on rows longer than 6144 32
+ * or 48; with g = 128 and (1,256) 32), above that one per block shape that the
+ * layers' sizes call for (at most two). Otherwise the layers are computed one
+ * after another on the stream, sharing the workspace. With a workspace smaller
+ * than the size below that the call still takes (see higgs_qmatmul), each step
+ * of 64 rows has a product launch and at most one reduction launch.
  *
  *   layers     1..4.
  *   x          [in]  device, batch*in values of x_dtype, row-major, shared.

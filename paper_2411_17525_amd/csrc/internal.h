@@ -155,8 +155,9 @@ hipError_t launch_qgemm(const void* x, int x_kind, uint64_t seed, int64_t batch,
                         int64_t workspace_bytes, hipStream_t stream);
 
 // Up to 4 layers that read the same activations (own codes, scales, rows,
-// seed and output) in one activation conversion and, up to 64 batch rows, one
-// product launch and at most one reduction launch.
+// seed and output) in one activation conversion, a product launch (64-column
+// product: per 64 rows; prompt-sized product: per block shape) and at most one
+// reduction launch (64-column product: per 64 rows).
 int64_t qgemm_group_workspace_bytes(int layers, int64_t batch, const int64_t* outs, int64_t in,
                                     int p, int n, int g);
 int64_t qgemm_group_least_workspace_bytes(int layers, int64_t batch, const int64_t* outs,

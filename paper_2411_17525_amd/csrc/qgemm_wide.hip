@@ -71,7 +71,8 @@ __device__ inline int group_exponent(float m) {
 // wave's first load is under way meanwhile: 2048 x 4096 bf16 into two layers'
 // copies 27.6 -> 22.3 us against blocks of four waves that load afterwards
 // (38 us with four waves per group, a sign generator per element and 2-byte
-// stores), 512 x 14336 13.4 -> 12.3 us.
+// stores), 512 x 14336 13.4 -> 12.3 us; 20.8 and 10.6 with the signs applied as
+// integers.
 template <int E, typename InT, bool ROT, int W>
 __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restrict__ x, int64_t batch,
                                                          int64_t in, XSeeds seeds, float rscale,
@@ -901,9 +902,16 @@ hipError_t launch_bits(const QW& a, int shape, unsigned blocks, hipStream_t stre
 
 }  // namespace
 
-// From 65 rows the wide blocks were never slower than the 64-column launches
-// (65 rows: 4096 x 4096 25.9 -> 25.7 us, 14336 x 4096 46 -> 33; 129 rows: 41 ->
-// 30, 72 -> 44). Up to 64 rows those are as fast or faster (64 rows, 4096 x
+// From 65 rows the wide blocks are the faster ones for single layers (65 rows:
+// 4096 x 4096 25 -> 23 us, 14336 x 4096 46 -> 34; 129 rows: 39 -> 27, 72 -> 42)
+// but for a few (28672 x 8192, 10-bit codes, g = 128: 214 us against 243 at 129
+// rows; 4096 x 4096, g = 4096: 27.3 against 28.6 at 65). Calls of two layers of
+// 14336 x 4096 lose at 65 and 80 rows (50 us against 57, 53 against 58), with
+// 10-bit codes up to 160 (129 rows: 100 against 118; g = 128, 257 rows: 220
+// against 254): each layer has the K-split of a single call, whose result it has
+// to match bit for bit, and whose blocks fill the chip alone. Plans that weigh
+// such a pair in made it 44 us at 80 rows, and single layers of 65 to 512 rows
+// up to 35% slower. Up to 64 rows those are as fast or faster (64 rows, 4096 x
 // 14336, 256 points: 28 us against 34) except where their folds of many small
 // groups or two lookups per pair weigh: g = 64 (64 rows, 4096 x 14336: 16 points
 // 82 -> 38, 256 scalar points 167 -> 42; 32 rows, 14336 x 4096: 65 -> 32, 89 ->
