@@ -222,6 +222,94 @@ __global__ __launch_bounds__(64 * W) void xprep_wide_kernel(const InT* __restric
   }
 }
 
+// The same with one group per block of four waves (g = 256 E): a wave's serial
+// chain of loads, butterflies and stores is a quarter as long, and 64 elements
+// per lane took all of a wave's registers. Thread t holds elements
+// [tE, (t + 1)E); butterflies over the top two element bits go through LDS. The
+// stages run in the same order and each is (a + b, a - b): the same values bit
+// for bit. Block b takes group grp0 + b of layer blockIdx.y (one group: with a
+// loop over groups the signs move out of it, into more registers than there
+// are). Whole calls of 256 outputs against a wave per group, 4096 weights per
+// row: g = 4096 23.3 -> 18.5 us at 65 rows, 44 -> 36 at 2048 (fp32); g = 2048
+// 22.1 -> 19.4 at 200 rows, 36.8 -> 37.3 at 2048; g = 1024 19.0 -> 18.5 at 65
+// rows, 31 -> 37 at 2048.
+template <int E, typename InT, bool ROT>
+__global__ __launch_bounds__(256) void xprep_wide4_kernel(const InT* __restrict__ x, int64_t batch,
+                                                          int64_t in, int64_t grp0, XSeeds seeds,
+                                                          float rscale,
+                                                          _Float16* __restrict__ x16,
+                                                          float* __restrict__ xe) {
+  constexpr int g = 256 * E;
+  __shared__ float s_v[2][ROT ? g : 1];
+  __shared__ float s_m[4];
+  const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+  const int64_t gpr = in / g, grp = grp0 + blockIdx.x;
+  const int64_t row = uint32_t(grp) / uint32_t(gpr);
+  const int64_t k0 = (grp - row * gpr) * g + tid * E;
+  float v[E];
+  const InT* src = x + row * in + k0;
+  if constexpr (sizeof(InT) == 4) {
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+      const f32x4 u = reinterpret_cast<const f32x4*>(src)[q];
+      v[4 * q] = u.x; v[4 * q + 1] = u.y; v[4 * q + 2] = u.z; v[4 * q + 3] = u.w;
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+      const uint2 u = reinterpret_cast<const uint2*>(src)[q];
+      v[4 * q] = __uint_as_float(u.x << 16);
+      v[4 * q + 1] = __uint_as_float(u.x & 0xffff0000u);
+      v[4 * q + 2] = __uint_as_float(u.y << 16);
+      v[4 * q + 3] = __uint_as_float(u.y & 0xffff0000u);
+    }
+  }
+  const int64_t layer = blockIdx.y;
+  if constexpr (ROT) {
+    uint64_t seed = seeds.s[0];
+#pragma unroll
+    for (int l = 1; l < kMaxGroup; ++l)
+      if (layer == l) seed = seeds.s[l];
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+      if (rht_sign_negative(seed, uint32_t(tid * E + i))) v[i] = -v[i];
+    fwht_in_lane<E>(v);
+    fwht_cross_lane<E>(v, lane, 64 * E);
+    // wave bits 0 and 1: the lower wave of a pair keeps a + b, the upper one
+    // a - b (a the lower wave's value)
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const int bit = 1 << st;
+      float* buf = s_v[st];
+#pragma unroll
+      for (int i = 0; i < E; ++i) buf[tid * E + i] = v[i];
+      __syncthreads();
+      const float* o = buf + (tid ^ (64 * bit)) * E;
+#pragma unroll
+      for (int i = 0; i < E; ++i) v[i] = (wave & bit) ? o[i] - v[i] : v[i] + o[i];
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i] *= rscale;
+  }
+  float m = 0.f;
+#pragma unroll
+  for (int i = 0; i < E; ++i) m = fmaxf(m, fabsf(v[i]));
+  m = wave_max(m, lane);
+  if (lane == 0) s_m[wave] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+  const int e = group_exponent(m);
+  _Float16* dst = x16 + layer * batch * in;
+#pragma unroll
+  for (int q = 0; q < E / 4; ++q) {
+    uint2 w;
+    w.x = pack_h2(ldexpf(v[4 * q], -e), ldexpf(v[4 * q + 1], -e));
+    w.y = pack_h2(ldexpf(v[4 * q + 2], -e), ldexpf(v[4 * q + 3], -e));
+    *reinterpret_cast<uint2*>(dst + xw_index(batch, in, row, k0 + 4 * q)) = w;
+  }
+  if (tid == 0) xe[layer * batch * gpr + grp] = ldexpf(1.0f, e);
+}
+
 // ---------------------------------------------------------------------------
 // The product.
 // ---------------------------------------------------------------------------
@@ -837,6 +925,21 @@ hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, con
                              _Float16* x16, float* xe, hipStream_t stream) {
   const float rscale = float(1.0 / std::sqrt(double(g)));
   const int64_t groups = batch * (in / g);
+  // a block per group (xprep_wide4_kernel): g = 4096 always; g = 2048 where a
+  // wave per group would be few waves
+  if (g == 4096 || (g == 2048 && groups * seeds.nl <= 1400)) {
+    constexpr int64_t kMost = 1 << 23;  // blocks of a launch: below 2^32 threads
+    for (int64_t g0 = 0; g0 < groups; g0 += kMost) {
+      const dim3 grid{unsigned(std::min(kMost, groups - g0)), unsigned(seeds.nl)}, block{256};
+      if (g == 2048)
+        hipLaunchKernelGGL((xprep_wide4_kernel<8, InT, ROT>), grid, block, 0, stream, x, batch,
+                           in, g0, seeds, rscale, x16, xe);
+      else
+        hipLaunchKernelGGL((xprep_wide4_kernel<16, InT, ROT>), grid, block, 0, stream, x, batch,
+                           in, g0, seeds, rscale, x16, xe);
+    }
+    return hipGetLastError();
+  }
   // 16 waves share a block's signs where that leaves a block for every compute
   // unit, i.e. from 4096 groups; four below (600 groups in blocks of 16 would
   // use 38 compute units) and where there are no signs (5.2 us either way at
@@ -864,7 +967,6 @@ hipError_t launch_xprep_wide(const InT* x, int64_t batch, int64_t in, int g, con
     HIGGS_XPREP(512)
     HIGGS_XPREP(1024)
     HIGGS_XPREP(2048)
-    HIGGS_XPREP(4096)
 #undef HIGGS_XPREP
     default:
       return hipErrorInvalidValue;

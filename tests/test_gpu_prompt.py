@@ -53,6 +53,8 @@ CASES += [(2, 256, 65, 100, 9216, 1024), (1, 16, 70, 33, 20480, 1024), (1, 256, 
 # activations converted by blocks of 16 waves (from 4096 groups): a last block
 # of four waves; waves with two groups, the second pass partial
 CASES += [(2, 256, 1025, 129, 4096, 1024), (1, 16, 137, 131, 4160, 64), (2, 64, 300, 100, 4096, 128)]
+# by a block per group (g = 4096, and 2048 up to 1400 groups)
+CASES += [(2, 256, 70, 100, 4096, 2048), (1, 16, 1401, 33, 2048, 2048), (2, 64, 131, 70, 12288, 4096)]
 
 
 def make_layer(p, n, out, inp, g, seed):
@@ -213,6 +215,7 @@ GROUPS = [
     (1, 16, 64, 33, 1024, (512, 512, 512, 512)),
     (1, 256, 128, 130, 2048, (17000, 129, 900)),
     (2, 64, 4096, 65, 4096, (300, 100, 200)),
+    (2, 256, 2048, 66, 6144, (300, 100)),
 ]
 
 
@@ -231,6 +234,8 @@ def test_prompt_groups_match_single_calls(p, n, g, batch, inp, outs):
         ys = H.qmatmul_fused_multi(x, call, grid, g)
         for (codes, scales, seed, out), y in zip(call, ys):
             assert torch.equal(y, H.qmatmul_fused(x, codes, scales, grid, g, seed, out))
+            x_rot = H.rht_activations(x, g, seed)
+            assert torch.equal(y, H.qmatmul(x_rot, codes, scales, grid, g, out))
 
 
 @pytest.mark.parametrize("p,n,g,out,inp,small,large", [
