@@ -1007,10 +1007,9 @@ hipError_t launch_bits(const QW& a, int shape, unsigned blocks, hipStream_t stre
 // From 65 rows the wide blocks are the faster ones for single layers (65 rows:
 // 4096 x 4096 25 -> 23 us, 14336 x 4096 46 -> 34; 129 rows: 39 -> 27, 72 -> 42)
 // but for a few (28672 x 8192, 10-bit codes, g = 128: 214 us against 243 at 129
-// rows; 4096 x 4096, g = 4096: 27.3 against 28.6 at 65). Calls of two layers of
-// 14336 x 4096 lose at 65 and 80 rows (50 us against 57, 53 against 58), with
-// 10-bit codes up to 160 (129 rows: 100 against 118; g = 128, 257 rows: 220
-// against 254): each layer has the K-split of a single call, whose result it has
+// rows). Calls of two layers of 14336 x 4096 lose at 65 and 80 rows (50 us
+// against 57, 53 against 58), with 10-bit codes up to 160 (129 rows: 100 against
+// 118; g = 128, 257 rows: 220 against 254): each layer has the K-split of a single call, whose result it has
 // to match bit for bit, and whose blocks fill the chip alone. Plans that weigh
 // such a pair in made it 44 us at 80 rows, and single layers of 65 to 512 rows
 // up to 35% slower. Up to 64 rows those are as fast or faster (64 rows, 4096 x
